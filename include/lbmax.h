@@ -275,6 +275,9 @@ lb_status lb_load_state(lb_handle *h, const void *d_src);
  * lane width in use and the chunk count.  lb_set_graph(h, s) replays s steps per hipGraph launch inside
  * lb_step (0 = plain launches).  All take effect at the next lb_step; only
  * the chunk split changes results, and only through rounding order.
+ * (Inside a call of several blocks one reading of the window may serve up to
+ * 128 steps, see lb_set_block; the replayed steps per launch then follow that
+ * span.)
  */
 int32_t lb_max_chunks(const lb_handle *h, int32_t ch);
 lb_status lb_set_tiling(lb_handle *h, int32_t ch, int32_t n_chunks,
@@ -297,6 +300,17 @@ lb_status lb_set_graph(lb_handle *h, int32_t steps_per_graph);
  * stepping only by rounding order.  A change takes effect at the next step
  * (which starts a new block); the graph length (lb_set_graph) must be a
  * multiple of it.  Default 1.
+ *
+ * Inside one lb_step call, channels with the integral law in the simple-shear
+ * reduction and a window of at least 128 entries may take spans of up to 128
+ * steps per reading of the window: the sums of all of a span's steps come from
+ * an expansion of the decay factors in the entries' rates, to the rounding of
+ * the history precision (where the rates are spread too widely for it, 64
+ * nodes at a time take the pass described above).  Such calls run in blocks of
+ * 32 steps whatever the setting -- the last of them ends with the call when
+ * the setting is 1 -- except for handles of 1 step per pass whose channels all
+ * are of the kind the adjoint covers.  Nothing of a span outlives the call, and
+ * the state written by lb_save_state is as described above.
  */
 lb_status lb_set_block(lb_handle *h, int32_t steps_per_pass);
 int32_t lb_get_block(const lb_handle *h);

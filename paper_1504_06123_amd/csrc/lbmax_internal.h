@@ -39,6 +39,19 @@ constexpr int kTileCounters = 8;   // persistent-pass tile counters (one per til
 // total deformation (4 planes).
 constexpr int kFingerPartPlanes = 3 * kMaxBlock + 4;
 constexpr int kMaxFingerBlock = 16;
+// Far sums (k_far_pass): steps served by one far pass at most, the most terms
+// of its expansion, and the bound z on (rate spread) x (half the span).
+constexpr int kFarMaxSteps = 128;
+constexpr int kFarClasses = 3;  // spans of 32, 64 and 128 steps
+constexpr int kFarMaxTerms = 18;
+constexpr int kFarNearBlock = 32;  // steps served by one near pass
+constexpr int kFarMinWindow = 4;   // windows of at least this many spans take far sums
+
+// Expansion terms by history type (code 0: FP64) and the bound z: the
+// expansion of exp(-z u v) on |u|, |v| <= 1 is good to 8e-9 with 12 terms and
+// to the rounding of its FP64 evaluation with 18.
+inline constexpr int far_terms(int prec) { return prec == 0 ? 18 : 12; }
+constexpr double kFarZ = 1.8;
 
 // Per-channel parameters and workspace offsets, read by every kernel.
 // 256 bytes so a table row never straddles two scalar cache lines twice.
@@ -76,6 +89,10 @@ struct alignas(256) ChanDev {
     // adjoint's step record).
     int64_t rec;
     int64_t rec_t0;
+    int64_t off_far;                // [2 terms][max_chunks][np] doubles: far sums
+    int32_t far;                    // most steps of a far span (0: takes no far sums)
+    int32_t far_t;                  // plane of off_far with the far entries' strain;
+                                    // the next one holds the tiles' markers
 };
 static_assert(sizeof(ChanDev) == 256, "ChanDev layout");
 
@@ -103,17 +120,40 @@ void launch_init(int prec, char *ws, const ChanDev *chans, int ch,
                  const NodeTile *tiles, int n_tiles, const double *u0_dev,
                  hipStream_t st);
 void launch_fill_zero(void *p, size_t bytes, hipStream_t st);
-// The lattice kernel also zeroes the persistent-pass tile counters.
+// The lattice kernel also zeroes the persistent-pass tile counters and, at the
+// first step of a channel's far span (block blk of a span of `span` steps; 0:
+// none), its far tiles' markers.
 void launch_lb(int prec, char *ws, const ChanDev *chans, const NodeTile *tiles,
                int n_tiles, const int64_t *tcount, int trel, int *tile_counters,
-               hipStream_t st);
+               int span, int blk, hipStream_t st);
 // History pass (first step of a block of `block` steps) for the tiles of the
 // channels whose lane width is `vec`.  persistent_grid > 0 launches that many
-// persistent workgroups claiming tiles from *counter.
+// persistent workgroups claiming tiles from *counter.  With `far` (32 steps
+// per pass), tiles whose far sums hold are skipped.
 void launch_hist_pass(int prec, int vec, int block, char *ws, const ChanDev *chans,
                       const HistTile *tiles, int n_tiles, const int64_t *tcount,
-                      int trel, int persistent_grid, int *counter, hipStream_t st);
+                      int trel, int persistent_grid, int *counter, bool far, hipStream_t st);
 int hist_pass_blocks_per_cu(int prec, int vec, int block);
+// Far sums.  A call-level span of `span` steps (32, 64 or 128) is cut into
+// blocks of 32 and, per channel, into spans of min(ChanDev::far, span) steps;
+// at block blk of it (first step *tcount + trel) the far pass runs for the
+// channels whose span starts there, each tile split over `sub` wavefronts (1, 4
+// or 8).
+void launch_far_pass(int prec, int sub, char *ws, const ChanDev *chans, const HistTile *tiles,
+                     int n_tiles, const int64_t *tcount, int trel, int span, int blk,
+                     hipStream_t st);
+// Near pass of block blk: sigma of the block's first step and the block sums
+// of the rest, from the far sums, the entries pushed since the channel's span
+// began and the window's end.  Tiles whose far sums do not hold (and channels
+// without) are combined from the chunk partials of launch_hist_pass.  `tabs`:
+// the expansion coefficients, [kFarClasses][kFarMaxSteps][far_terms(prec)]
+// (fill_far_table).
+void launch_near_pass(int prec, bool split, char *ws, const ChanDev *chans,
+                      const NodeTile *tiles, int n_tiles, const int64_t *tcount, int trel,
+                      int span, int blk, const double *tabs, hipStream_t st);
+inline constexpr int far_class(int span) { return span >= 128 ? 2 : (span >= 64 ? 1 : 0); }
+// Coefficients d_p(m), m < span, p < far_terms(prec).
+void fill_far_table(int prec, int span, double *out);
 // Full-tensor pass for the tiles of the full-tensor channels (block <= 16).
 void launch_finger_pass(int prec, int block, char *ws, const ChanDev *chans,
                         const HistTile *tiles, int n_tiles, const int64_t *tcount, int trel,
@@ -125,9 +165,10 @@ void launch_wm_pass(int prec, int block, char *ws, const ChanDev *chans, const H
 // Instantaneous law (Eq. inlM), every step, node-local (other channels return).
 void launch_inst_step(int prec, char *ws, const ChanDev *chans, const NodeTile *tiles,
                       int n_tiles, const int64_t *tcount, int trel, hipStream_t st);
-// FP64 combine of chunk partials into sigma and the block sums.
+// FP64 combine of chunk partials into sigma and the block sums (far: of the
+// full-tensor channels; the near pass takes the others).
 void launch_combine(int prec, int block, char *ws, const ChanDev *chans,
-                    const NodeTile *tiles, int n_tiles, hipStream_t st);
+                    const NodeTile *tiles, int n_tiles, bool far, hipStream_t st);
 // Step m (1 <= m < block) of a block: gradient, push, sigma from the block sums.
 void launch_hist_step(int prec, int m, char *ws, const ChanDev *chans,
                       const NodeTile *tiles, int n_tiles, const int64_t *tcount,

@@ -535,12 +535,30 @@ __device__ __forceinline__ int xcd_tile(int b, int n)
     return x * q + min(x, r) + i;
 }
 
+// Marker of the 64-node tile from n0 (in the plane behind the far entries'
+// strain): zeroed by the lattice kernel of the span's first step, set by the
+// far pass where the tile's far sums do not hold.
+__device__ __forceinline__ double *far_marker(char *ws, const ChanDev *c, int n0)
+{
+    return reinterpret_cast<double *>(ws + c->off_far) +
+           (size_t)(c->far_t + 1) * c->max_chunks * c->np + n0;
+}
+
+// Steps of channel c's spans inside a call-level span of `span` steps.
+__device__ __forceinline__ int far_span(const ChanDev *c, int span) { return min(c->far, span); }
+
+__device__ __forceinline__ bool far_holds(char *ws, const ChanDev *c, int n0)
+{
+    return c->far && *far_marker(ws, c, n0) == 0.0;
+}
+
 template <typename P, typename S>
 __global__ __launch_bounds__(kBlock, 5) void k_lb(char *__restrict__ ws,
                                                const ChanDev *__restrict__ chans,
                                                const NodeTile *__restrict__ tiles,
                                                const int64_t *__restrict__ tcount,
-                                               int trel, int *__restrict__ tile_counters)
+                                               int trel, int *__restrict__ tile_counters,
+                                               int span, int blk)
 {
     const NodeTile tl = tiles[xcd_tile((int)blockIdx.x, (int)gridDim.x)];
     const ChanDev *c = chans + tl.ch;
@@ -551,6 +569,10 @@ __global__ __launch_bounds__(kBlock, 5) void k_lb(char *__restrict__ ws,
         tile_counters[threadIdx.x] = 0;
     if (n >= c->n)
         return;
+    // first step of a far span of this channel (span = 0: not a span's step)
+    if (span && c->far && threadIdx.x % kWave == 0 &&
+        (blk * kFarNearBlock) % far_span(c, span) == 0)
+        *far_marker(ws, c, n) = 0.0;
     lb_node<P, S>(ws, c, n, *tcount + trel);
 }
 
@@ -718,6 +740,19 @@ __device__ __forceinline__ void tail_entry(R s, R r, int k, int H, R g, const De
         if (m + 1 < M)
             e = e * q;
     }
+}
+
+// The newest entry (age 0 at the block's first step, in the window through the
+// block) into the partial sums of steps m0 .. m0 + M - 1; it has no strain.
+template <typename R, int M>
+__device__ __forceinline__ void tail_entry_newest(R s, R r, int m0, const Decay<R> &dec,
+                                                  R (&pa)[M][1])
+{
+#pragma clang fp contract(off)
+    const R rate = decay_rate<R>(dec, r);
+#pragma unroll
+    for (int i = 0; i < M; ++i)
+        pa[i][0] = pa[i][0] + (m0 + i == 0 ? R(0.5) : R(1)) * s * decay_pow(R(m0 + i), rate);
 }
 
 // One entry's terms for the M steps of a block: x q^m into pa[m][v] and
@@ -1056,6 +1091,580 @@ __device__ __forceinline__ void pass_tile(char *__restrict__ ws, const ChanDev *
     }
 }
 
+template <typename P>
+__device__ __forceinline__ void combine_node(char *__restrict__ ws, const ChanDev *c, int n, int m);
+
+// ---------------------------------------------------------------------------
+// Far sums: one pass over the window for a span of up to 128 steps.
+//
+// The sums A_m, B_m of an entry set over m < S follow from a few moments of
+// it.  With rate = 1/tau + rho, rho = r / gamma_c, a centre rho_0 per node, the
+// span's middle mbar = (S - 1)/2 and rho_h = z / mbar,
+//   E(k + m) = E(k + mbar) exp(-(m - mbar)(1/tau + rho_0)) exp(-z u v_m),
+//   u = (rho - rho_0) / rho_h,  v_m = (m - mbar) / mbar,
+// and for |u| <= 1 exp(-z u v) = sum_p d_p(v) u^p with P terms (the Chebyshev
+// expansion in u, its coefficients a table of the span).  So
+//   A_m = F_m sum_p d_p(v_m) MA_p,  MA_p = sum_e s_e E(k + mbar, r_e) u_e^p,
+// likewise B_m with gamma(t0, e) in each term, for every m of the span: the
+// pass costs one exponential and about 3 P operations per entry instead of
+// two and 2 S, and one reading of the window serves S steps instead of 32.
+// Entries stay inside the window with weight 1 through the span (ages 1 ..
+// H - S - 1 at its start); the rest is the near pass's.
+//
+// rho_0 is the rho of the entry pushed last before the span (moved towards
+// rho_h where it lies above it, so that a start from rest is inside), so in a
+// slowly changing flow |u| is small and A_m is a well-conditioned sum.  A tile
+// with an entry beyond |u| = 1 (or a NaN) is marked, and takes the general
+// pass, block by block, for the whole span.
+//
+// What bounds it: the window's bytes for wide channels (1024 x 512 nodes, 4096
+// entries: 3.30 ms, 5.2 TB/s, the rate of a large copy; the general pass 5.27
+// ms, and four times as often), vector issue for narrow ones, whose tiles are
+// split over 4 or 8 wavefronts of a workgroup and put together in LDS (1 x 256
+// nodes, 8192 entries in 8 chunks: 29 us against 211 us).  256 steps of the
+// 1024 x 512 channel, far and near passes: 9 ms against 42 ms.
+// ---------------------------------------------------------------------------
+template <typename R>
+constexpr int kFarP = sizeof(R) == 8 ? far_terms(0) : far_terms(1);
+
+// Rates of the expansion at a node; t_s: the span's first step.
+template <typename R>
+struct FarRates {
+    R a, b;     // E(k + mbar) = exp(-(2 k + S - 1) (a + b r)), FP32: in powers of 2
+    R cu, c0;   // u = cu r - c0
+    double rho0;
+
+    __device__ __forceinline__ FarRates(const ChanDev *c, R r0, int S)
+    {
+        const Decay<R> dec(c);
+        a = R(0.5) * dec.a;
+        b = R(0.5) * dec.b;
+        const double h = kFarZ / (0.5 * (S - 1));
+        const double rho = c->inv_gc * (double)r0;
+        rho0 = rho > h ? fmax(h, rho - 0.5 * h) : rho;
+        cu = (R)(c->inv_gc / h);
+        c0 = (R)(rho0 / h);
+    }
+};
+
+// |gamma_dot| of the entry pushed before step t_s at a node.
+template <typename R>
+__device__ __forceinline__ R far_center(const char *__restrict__ ws, const ChanDev *c, int node,
+                                        int64_t t_s)
+{
+    const int H = c->n_hist;
+    const int p = (int)(t_s % H);
+    const size_t at = (size_t)(p == 0 ? H - 1 : p - 1) * c->np + node;
+    return c->has_r ? reinterpret_cast<const R *>(ws + c->off_ring_r)[at]
+                    : fabs(reinterpret_cast<const R *>(ws + c->off_ring_s)[at]);
+}
+
+// Rows of slots slot, slot - 1, .., of which the first `count` are wanted (at
+// most G); the others come as zero entries.
+template <typename R, int G, bool HAS_R>
+__device__ __forceinline__ void load_rows_masked(const R *__restrict__ ring_s,
+                                                 const R *__restrict__ ring_r, size_t np,
+                                                 uint32_t off, int slot, int count,
+                                                 Pack<R, 1> (&sv)[G], Pack<R, 1> (&rv)[G])
+{
+#pragma unroll
+    for (int u = 0; u < G; ++u) {
+        const size_t row = (size_t)max(slot - u, 0) * np;
+        sv[u] = load_pack<R, 1>(ring_s + row, off);
+        if (HAS_R)
+            rv[u] = load_pack<R, 1>(ring_r + row, off);
+    }
+#pragma unroll
+    for (int u = 1; u < G; ++u) {
+        sv[u].v[0] = u < count ? sv[u].v[0] : R(0);
+        if (HAS_R)
+            rv[u].v[0] = u < count ? rv[u].v[0] : rv[0].v[0];
+    }
+}
+
+// Rows of ages [k, kend), newest to oldest, in groups of G with the loads of
+// one group in flight while the other is used: fn(sv, rv, age) sums a group.
+// The last rows of a run (before the ring wraps, or of the range) come in
+// groups filled up with zero entries.  block() is called every F rows at
+// most, and ends the walk when it returns false.
+template <typename R, int G, int F, bool HAS_R, typename Fn, typename Block>
+__device__ __forceinline__ bool walk_rows(const R *__restrict__ ring_s,
+                                          const R *__restrict__ ring_r, size_t np,
+                                          uint32_t off, int H, int p, int k, int kend, Fn &&fn,
+                                          Block &&block)
+{
+    static_assert(F % (2 * G) == 0, "a block of rows is whole pairs of groups");
+    int slot = p - k;
+    if (slot < 0)
+        slot += H;
+    while (k < kend) {
+        const int run = min(kend - k, slot + 1);
+        int j = 0;
+        Pack<R, 1> as[G], ar[G], bs[G], br[G];
+        if (run >= 2 * G)
+            load_rows<R, 1, G, HAS_R>(ring_s, ring_r, np, off, slot, as, ar);
+        while (j + 2 * G <= run) {
+            const int end = min(j + F, run);
+            for (; j + 2 * G <= end; j += 2 * G) {
+                load_rows<R, 1, G, HAS_R>(ring_s, ring_r, np, off, slot - j - G, bs, br);
+                fn(as, ar, k + j);
+                // past the run's pairs: clamped rows, not used
+                load_rows<R, 1, G, HAS_R>(ring_s, ring_r, np, off,
+                                          max(slot - j - 2 * G, G - 1), as, ar);
+                fn(bs, br, k + j + G);
+            }
+            if (!block())
+                return false;
+        }
+        if (j < run) {
+            for (; j < run; j += G) {
+                load_rows_masked<R, G, HAS_R>(ring_s, ring_r, np, off, slot - j, run - j, as,
+                                              ar);
+                fn(as, ar, k + j);
+            }
+            if (!block())
+                return false;
+        }
+        k += run;
+        slot = H - 1;
+    }
+    return true;
+}
+
+// Moments of ages [ka, kb) at one node, in partial sums of F rows added in
+// FP64.  Returns false when an entry's u is outside [-1, 1]; looked at every F
+// rows.  All sums of a span come from the same moments, so their rounding
+// acts in the same sense on every step of it, where the general pass has new
+// rounding for each: the partial sums are short (16 rows: a third of the
+// rounding of 128), so that the error of the velocity it drives stays below
+// the general pass's (u_y of the 1024 x 512 FP32 channel after 256 steps:
+// 5.0e-7 of its norm, 1.16e-6 with 128 rows, 1.04e-6 by the general pass).
+template <typename R, int F, bool HAS_R>
+__device__ __forceinline__ bool far_moments(const R *__restrict__ ring_s,
+                                            const R *__restrict__ ring_r, size_t np,
+                                            uint32_t off, int H, int p, int ka, int kb, int S,
+                                            const FarRates<R> &fr, double (&A)[kFarP<R>],
+                                            double (&B)[kFarP<R>], double &loc)
+{
+    constexpr int P = kFarP<R>;
+    constexpr int G = sizeof(R) == 4 ? 8 : 4;
+    R pa[P], pb[P];
+#pragma unroll
+    for (int q = 0; q < P; ++q)
+        pa[q] = pb[q] = R(0);
+    bool bad = false;
+    return walk_rows<R, G, F, HAS_R>(
+        ring_s, ring_r, np, off, H, p, ka, kb,
+        [&](const Pack<R, 1>(&sv)[G], const Pack<R, 1>(&rv)[G], int k) {
+#pragma clang fp contract(off)
+#pragma unroll
+            for (int u = 0; u < G; ++u) {
+                // 2 (k + u + mbar), below 2^24 (windows of at most 2^22 entries)
+                const int k2 = 2 * (k + u) + S - 1;
+                const R kf =
+                    sizeof(R) == 4
+                        ? R(small_uniform_to_float((uint32_t)__builtin_amdgcn_readfirstlane(k2)))
+                        : R(k2);
+                const R s = sv[u].v[0];
+                const R r = HAS_R ? rv[u].v[0] : fabs(s);
+                // a filled-up row of a channel without |gamma_dot| rows has r = 0
+                const R w = fused(fr.cu, r, -fr.c0);
+                bad |= !(fabs(w) <= R(1)) && (HAS_R || s != R(0));
+                loc += (double)s;
+                const R g = (R)loc;
+                R x = s * decay_pow(kf, fused(fr.b, r, fr.a));
+#pragma unroll
+                for (int q = 0; q < P; ++q) {
+                    pa[q] = pa[q] + x;
+                    pb[q] = fused(x, g, pb[q]);
+                    if (q + 1 < P)
+                        x = x * w;
+                }
+                // a row's (FP32: two rows') operations stay together: spread
+                // over the group they would take the registers of more
+                // wavefronts than they hide latency
+                if (sizeof(R) == 8 || u % 2 == 1)
+                    __builtin_amdgcn_sched_barrier(0);
+            }
+        },
+        [&]() {
+#pragma unroll
+            for (int q = 0; q < P; ++q) {
+                A[q] += (double)pa[q];
+                B[q] += (double)pb[q];
+                pa[q] = pb[q] = R(0);
+            }
+            return !__any(bad);
+        });
+}
+
+// One tile: 64 nodes, the part [k0, k1) of the far ages, SUB wavefronts.
+template <typename R, int SUB, bool HAS_R>
+__device__ __forceinline__ void far_tile(char *__restrict__ ws, const ChanDev *c,
+                                         const HistTile &tl, int64_t t_s, int S)
+{
+    constexpr int P = kFarP<R>;
+    const int H = c->n_hist;
+    const size_t np = (size_t)c->np;
+    const int lane = (int)(threadIdx.x % kWave);
+    const int first = tl.n0 + lane;
+    const int node = min(first, c->n - 1);  // shadow lanes past the end
+    const uint32_t off = (uint32_t)node * (uint32_t)sizeof(R);
+    const int p = (int)(t_s % H);
+    const R *ring_s = reinterpret_cast<const R *>(ws + c->off_ring_s);
+    const R *ring_r = reinterpret_cast<const R *>(ws + c->off_ring_r);
+    const FarRates<R> fr(c, far_center<R>(ws, c, node, t_s), S);
+    int ka = max(tl.k0, 1), kb = min(tl.k1, H - S);
+    const int w = SUB == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    if (SUB > 1) {
+        const int len = (max(kb - ka, 0) + 16 * SUB - 1) / (16 * SUB) * 16;
+        ka = ka + w * len;
+        kb = min(kb, ka + len);
+    }
+    double A[P] = {}, B[P] = {}, loc = 0.0;
+    const bool ok =
+        far_moments<R, 16, HAS_R>(ring_s, ring_r, np, off, H, p, ka, kb, S, fr, A, B, loc);
+    double *far = reinterpret_cast<double *>(ws + c->off_far) + (size_t)tl.chunk * np + node;
+    const size_t fplane = (size_t)c->max_chunks * np;
+    if constexpr (SUB == 1) {
+        if (first >= c->n)
+            return;
+        if (!ok) {
+            if (lane == 0)
+                *far_marker(ws, c, tl.n0) = 1.0;
+            return;
+        }
+        far[c->far_t * fplane] = loc;
+#pragma unroll
+        for (int q = 0; q < P; ++q) {
+            far[q * fplane] = A[q];
+            far[(P + q) * fplane] = B[q];
+        }
+    } else {
+        // the parts newest first: B_c shifted by the strain of the newer parts
+        __shared__ double s_T[SUB][kWave];
+        constexpr int kRound = 8;  // planes per round through LDS
+        __shared__ double s_v[SUB][kRound][kWave];
+        __shared__ int s_bad[SUB];
+        s_T[w][lane] = loc;
+        if (lane == 0)
+            s_bad[w] = ok ? 0 : 1;
+        __syncthreads();
+        double O = 0.0, T = 0.0;
+#pragma unroll
+        for (int i = 0; i < SUB; ++i) {
+            const double ti = s_T[i][lane];
+            if (i < w)
+                O += ti;
+            T += ti;
+        }
+        int bad = 0;
+#pragma unroll
+        for (int i = 0; i < SUB; ++i)
+            bad |= s_bad[i];
+        if (__builtin_amdgcn_readfirstlane(bad)) {  // the same in every wavefront
+            if (threadIdx.x == 0)
+                *far_marker(ws, c, tl.n0) = 1.0;
+            return;
+        }
+        if (w == 0 && first < c->n)
+            far[c->far_t * fplane] = T;
+#pragma unroll
+        for (int q0 = 0; q0 < 2 * P; q0 += kRound) {
+#pragma unroll
+            for (int i = 0; i < kRound; ++i) {
+                const int q = q0 + i;
+                if (q < P)
+                    s_v[w][i][lane] = A[q];
+                else if (q < 2 * P)
+                    s_v[w][i][lane] = fma(O, A[q - P], B[q - P]);
+            }
+            __syncthreads();
+            for (int i = w; i < min(kRound, 2 * P - q0); i += SUB) {
+                double v = 0.0;
+#pragma unroll
+                for (int k = 0; k < SUB; ++k)
+                    v += s_v[k][i][lane];
+                if (first < c->n)
+                    far[(q0 + i) * fplane] = v;
+            }
+            __syncthreads();
+        }
+    }
+}
+
+// SUB = 1: one wavefront per tile, four tiles per workgroup; else one
+// workgroup of SUB wavefronts per tile.
+template <typename R, int SUB>
+__global__ __launch_bounds__(SUB == 1 ? kBlock : SUB * kWave) void k_far_pass(
+    char *__restrict__ ws, const ChanDev *__restrict__ chans, const HistTile *__restrict__ tiles,
+    int n_tiles, const int64_t *__restrict__ tcount, int trel, int span, int blk)
+{
+    const int i = SUB == 1 ? (int)blockIdx.x * (kBlock / kWave) +
+                                 __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave))
+                           : (int)blockIdx.x;
+    if (i >= n_tiles)
+        return;
+    const HistTile tl = tiles[i];
+    const ChanDev *c = chans + tl.ch;
+    if (!c->far)
+        return;
+    const int S = far_span(c, span);
+    if ((blk * kFarNearBlock) % S != 0)
+        return;  // inside a span of this channel
+    const int64_t t_s = *tcount + trel;
+    if (c->has_r)
+        far_tile<R, SUB, true>(ws, c, tl, t_s, S);
+    else
+        far_tile<R, SUB, false>(ws, c, tl, t_s, S);
+}
+
+// Near pass of a block of 32 steps from t0 = t_s + o (o a multiple of 32 below
+// the span S): the far sums carried to m + o, the entries pushed since the
+// span's start (ages 1 .. o), the newest entry (age 0, pushed here), and the
+// ages [H - S + o, H) at the window's end, MG of the block's steps per
+// wavefront.  MG = 32 for wide channels (four tiles of 64 nodes per
+// workgroup); MG = 8 where that leaves compute units idle: the four wavefronts
+// of a workgroup share a tile's rows, and its far sums through LDS.
+template <typename R, int MG>
+__device__ __forceinline__ void near_rows(R s, R r, int kf, const Decay<R> &dec, double &loc,
+                                          R (&pa)[MG][1], R (&pb)[MG][1])
+{
+#pragma clang fp contract(off)
+    const R rate = decay_rate<R>(dec, r);
+    loc += (double)s;
+    add_powers<R, MG, 1, false>(s * decay_pow(R(kf), rate), decay_pow(R(1), rate), (R)loc, pa,
+                                pb, 0);
+}
+
+template <typename P, typename R, int MG, bool HAS_R>
+__device__ __forceinline__ void near_tile(char *__restrict__ ws, const ChanDev *c, int n0,
+                                          int mg, int64_t t0, int S, int o,
+                                          const double *__restrict__ tab, double *s_mom)
+{
+    constexpr int T = kFarP<R>;
+    constexpr int G = sizeof(R) == 4 ? 8 : 4;
+    const int H = c->n_hist;
+    const size_t np = (size_t)c->np;
+    const int lane = (int)(threadIdx.x % kWave);
+    const int first = n0 + lane;
+    const int node = min(first, c->n - 1);
+    const bool own = first < c->n;
+    const uint32_t off = (uint32_t)node * (uint32_t)sizeof(R);
+    const int p = (int)(t0 % H);
+    const int m0 = mg * MG;  // this wavefront's steps m0 .. m0 + MG - 1 of the block
+    R *ring_s = reinterpret_cast<R *>(ws + c->off_ring_s);
+    R *ring_r = reinterpret_cast<R *>(ws + c->off_ring_r);
+    const Decay<R> dec(c);
+    const size_t fplane = (size_t)c->max_chunks * np;
+    const double *far = reinterpret_cast<const double *>(ws + c->off_far) + node;
+
+    // strain of the far entries
+    double Tf = 0.0;
+#pragma unroll 8
+    for (int k = 0; k < c->nchunks; ++k)
+        Tf += far[c->far_t * fplane + (size_t)k * np];
+
+    R pa[MG][1], pb[MG][1];
+#pragma unroll
+    for (int i = 0; i < MG; ++i)
+        pa[i][0] = pb[i][0] = R(0);
+    // newest entry
+    {
+        const P *vel = reinterpret_cast<const P *>(ws + c->off_vel);
+        const int y = node / c->lx, x = node - y * c->lx;
+        P kxx, kxy, kyx, kyy;
+        velocity_gradient<P>(vel, vel + np, c->lx, c->ly, x, y, kxx, kxy, kyx, kyy);
+        const R s = (R)kxy;
+        const R r = HAS_R ? (R)shear_rate<P>(kxx, kxy, kyx, kyy) : fabs(s);
+        if (mg == 0 && own) {
+            ring_s[(size_t)p * np + node] = s;
+            if (HAS_R)
+                ring_r[(size_t)p * np + node] = r;
+        }
+        tail_entry_newest<R, MG>(s, r, m0, dec, pa);
+    }
+    // entries pushed since the span's start
+    double loc = 0.0;
+    const auto sum_group = [&](const Pack<R, 1>(&sv)[G], const Pack<R, 1>(&rv)[G], int k) {
+#pragma unroll
+        for (int u = 0; u < G; ++u) {
+            const R s = sv[u].v[0];
+            near_rows<R, MG>(s, HAS_R ? rv[u].v[0] : fabs(s), k + u + m0, dec, loc, pa, pb);
+            if (MG == kFarNearBlock)
+                __builtin_amdgcn_sched_barrier(0);  // as in far_moments
+        }
+    };
+    const auto go_on = [] { return true; };
+    walk_rows<R, G, 128, HAS_R>(ring_s, ring_r, np, off, H, p, 1, 1 + o, sum_group, go_on);
+    const double D0 = loc;
+    loc += Tf;
+    // the window's end: whole-weight ages, then those that leave in the block
+    walk_rows<R, G, 128, HAS_R>(ring_s, ring_r, np, off, H, p, H - S + o, H - kFarNearBlock,
+                                sum_group, go_on);
+    walk_rows<R, G, 128, HAS_R>(ring_s, ring_r, np, off, H, p, H - kFarNearBlock, H,
+                           [&](const Pack<R, 1>(&sv)[G], const Pack<R, 1>(&rv)[G], int k) {
+#pragma unroll
+                               for (int u = 0; u < G; ++u) {
+                                   const R s = sv[u].v[0];
+                                   loc += (double)s;
+                                   R ta[MG], tb[MG];
+#pragma unroll
+                                   for (int i = 0; i < MG; ++i) {
+                                       ta[i] = pa[i][0];
+                                       tb[i] = pb[i][0];
+                                   }
+                                   tail_entry<R, MG>(s, HAS_R ? rv[u].v[0] : fabs(s), k + u + m0,
+                                                     H, (R)loc, dec, ta, tb);
+#pragma unroll
+                                   for (int i = 0; i < MG; ++i) {
+                                       pa[i][0] = ta[i];
+                                       pb[i][0] = tb[i];
+                                   }
+                                   if (MG == kFarNearBlock)
+                                       __builtin_amdgcn_sched_barrier(0);
+                               }
+                           },
+                           go_on);
+    // far sums of the chunks, newest first
+    double MA[T], MB[T];
+    if constexpr (MG == kFarNearBlock) {
+#pragma unroll
+        for (int q = 0; q < T; ++q)
+            MA[q] = MB[q] = 0.0;
+        double O = 0.0;
+        for (int k = 0; k < c->nchunks; ++k) {
+            const double *f = far + (size_t)k * np;
+#pragma unroll
+            for (int q = 0; q < T; ++q) {
+                const double a = f[q * fplane];
+                MA[q] += a;
+                MB[q] += fma(O, a, f[(T + q) * fplane]);
+            }
+            O += f[c->far_t * fplane];
+        }
+    } else {
+        // terms mg, mg + 4, .. by this wavefront, the others' through LDS
+        constexpr int kGroups = kFarNearBlock / MG;
+        constexpr int kPer = (T + kGroups - 1) / kGroups;
+        double a_[kPer], b_[kPer], O = 0.0;
+#pragma unroll
+        for (int i = 0; i < kPer; ++i)
+            a_[i] = b_[i] = 0.0;
+        constexpr int kAhead = 4;  // chunks loaded before any is used
+        for (int k0 = 0; k0 < c->nchunks; k0 += kAhead) {
+            double ta[kAhead][kPer], tb[kAhead][kPer], tt[kAhead];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                const double *f = far + (size_t)min(k0 + u, c->nchunks - 1) * np;
+#pragma unroll
+                for (int i = 0; i < kPer; ++i) {
+                    const int q = min(mg + i * kGroups, T - 1);
+                    ta[u][i] = f[q * fplane];
+                    tb[u][i] = f[(T + q) * fplane];
+                }
+                tt[u] = f[c->far_t * fplane];
+            }
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u)
+                if (k0 + u < c->nchunks) {
+#pragma unroll
+                    for (int i = 0; i < kPer; ++i) {
+                        a_[i] += ta[u][i];
+                        b_[i] += fma(O, ta[u][i], tb[u][i]);
+                    }
+                    O += tt[u];
+                }
+        }
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const int q = mg + i * kGroups;
+            if (q < T) {
+                s_mom[q * kWave + lane] = a_[i];
+                s_mom[(T + q) * kWave + lane] = b_[i];
+            }
+        }
+        __syncthreads();
+    }
+    if (!own)
+        return;
+    // the far sums at m + o
+    const FarRates<R> fr(c, far_center<R>(ws, c, node, t0 - o), S);
+    const double rate0 = c->inv_tau + fr.rho0;
+    const double mbar = 0.5 * (S - 1);
+    double F = exp(-((double)(o + m0) - mbar) * rate0);
+    const double Fq = exp(-rate0);
+    P *sig = reinterpret_cast<P *>(ws + c->off_sig);
+    double *blk = reinterpret_cast<double *>(ws + c->off_blk);
+#pragma unroll
+    for (int i = 0; i < MG; ++i) {
+        const int m = m0 + i;
+        const double *d = tab + (size_t)(o + m) * T;
+        double a = 0.0, b = 0.0;
+#pragma unroll
+        for (int q = T - 1; q >= 0; --q) {
+            if constexpr (MG == kFarNearBlock) {
+                a = fma(d[q], MA[q], a);
+                b = fma(d[q], MB[q], b);
+            } else {
+                a = fma(d[q], s_mom[q * kWave + lane], a);
+                b = fma(d[q], s_mom[(T + q) * kWave + lane], b);
+            }
+        }
+        if (sizeof(R) == 8 && i > 0)
+            F = exp(-((double)(o + m) - mbar) * rate0);
+        a *= F;
+        b = fma(D0, a, b * F);
+        if (sizeof(R) == 4)
+            F *= Fq;
+        const double Am = a + (double)pa[i][0];
+        // summed with gamma for 2 gamma: doubling is exact
+        const double Bm = 2.0 * (b + (double)pb[i][0]);
+        if (m == 0) {
+            sig[node] = (P)(c->g_inf * Am);
+            sig[np + node] = (P)(c->g_inf * Bm);
+        } else {
+            blk[m * np + node] = Am;
+            blk[(kPlaneB + m) * np + node] = Bm;
+        }
+    }
+}
+
+template <typename P, typename R, int MG>
+__global__ __launch_bounds__(kBlock, (sizeof(R) == 4 ? 3 : 1)) void k_near_pass(
+    char *__restrict__ ws, const ChanDev *__restrict__ chans, const NodeTile *__restrict__ tiles,
+    const int64_t *__restrict__ tcount, int trel, int span, int blk,
+    const double *__restrict__ tabs)
+{
+    constexpr int kTerms = MG == kFarNearBlock ? 1 : 2 * kFarP<R> * kWave;
+    __shared__ double s_mom[kTerms];
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    // node tile of 256 nodes and, with MG = 8, which quarter of it
+    constexpr int kPerTile = MG == kFarNearBlock ? 1 : kBlock / kWave;
+    const int b = MG == kFarNearBlock ? xcd_tile((int)blockIdx.x, (int)gridDim.x)
+                                      : (int)blockIdx.x;
+    const NodeTile tl = tiles[b / kPerTile];
+    const ChanDev *c = chans + tl.ch;
+    const int n0 = tl.n0 + kWave * (MG == kFarNearBlock ? wave : b % kPerTile);
+    const int mg = MG == kFarNearBlock ? 0 : wave;
+    if (c->law != 0 || c->finger || c->qb != 0 || n0 >= c->n)
+        return;
+    if (far_holds(ws, c, n0)) {
+        const int64_t t0 = *tcount + trel;
+        const int S = far_span(c, span), o = (blk * kFarNearBlock) % S;
+        const double *tab = tabs + (size_t)far_class(S) * kFarMaxSteps * kFarP<R>;
+        if (c->has_r)
+            near_tile<P, R, MG, true>(ws, c, n0, mg, t0, S, o, tab, s_mom);
+        else
+            near_tile<P, R, MG, false>(ws, c, n0, mg, t0, S, o, tab, s_mom);
+        return;
+    }
+    const int n = n0 + (int)(threadIdx.x % kWave);
+    if (c->nchunks > 1 && n < c->n)
+        for (int m = mg * MG; m < mg * MG + MG; ++m)
+            combine_node<P>(ws, c, n, m);
+}
+
 // One launch per (lane width V, block length M): the tiles of the channels
 // whose lane width is V, one wavefront per tile (64 V nodes), so channels
 // narrower than a workgroup leave no wavefront idle.  Plain form: the four
@@ -1074,7 +1683,7 @@ __global__ __launch_bounds__(kBlock, (pass_waves_per_simd<R, M>())) void k_hist_
                                                       const HistTile *__restrict__ tiles,
                                                       int n_tiles,
                                                       const int64_t *__restrict__ tcount,
-                                                      int trel)
+                                                      int trel, int far)
 {
     // wave-uniform, so the tile and channel fields stay in scalar registers
     const int i = (int)blockIdx.x * (kBlock / kWave) +
@@ -1083,6 +1692,8 @@ __global__ __launch_bounds__(kBlock, (pass_waves_per_simd<R, M>())) void k_hist_
         return;  // the last workgroup's spare wavefronts
     const HistTile tl = tiles[i];
     const ChanDev *c = chans + tl.ch;
+    if (M == kFarNearBlock && far && far_holds(ws, c, tl.n0))
+        return;
     const int64_t t = *tcount + trel;
     if (c->has_r)
         pass_tile<P, R, V, M, U, F, true>(ws, c, tl, t);
@@ -1098,7 +1709,7 @@ template <typename P, typename R, int V, int M, int U, int F>
 __global__ __launch_bounds__(kBlock, (pass_waves_per_simd<R, M>())) void k_hist_pass_persistent(
     char *__restrict__ ws, const ChanDev *__restrict__ chans,
     const HistTile *__restrict__ tiles, int n_tiles, const int64_t *__restrict__ tcount,
-    int trel, int *__restrict__ counter)
+    int trel, int *__restrict__ counter, int far)
 {
     const int64_t t = *tcount + trel;
     const bool leader = threadIdx.x % kWave == 0;
@@ -1111,6 +1722,8 @@ __global__ __launch_bounds__(kBlock, (pass_waves_per_simd<R, M>())) void k_hist_
             break;  // uniform across the wavefront
         const HistTile tl = tiles[i];
         const ChanDev *c = chans + tl.ch;
+        if (M == kFarNearBlock && far && far_holds(ws, c, tl.n0))
+            continue;
         if (c->has_r)
             pass_tile<P, R, V, M, U, F, true>(ws, c, tl, t);
         else
@@ -1786,16 +2399,8 @@ __global__ __launch_bounds__(kBlock) void k_inst_step(char *__restrict__ ws,
 // block sums for the following steps.
 // ---------------------------------------------------------------------------
 template <typename P>
-__global__ __launch_bounds__(kBlock) void k_combine(char *__restrict__ ws,
-                                                    const ChanDev *__restrict__ chans,
-                                                    const NodeTile *__restrict__ tiles)
+__device__ __forceinline__ void combine_node(char *__restrict__ ws, const ChanDev *c, int n, int m)
 {
-    const NodeTile tl = tiles[blockIdx.x];
-    const ChanDev *c = chans + tl.ch;
-    const int n = tl.n0 + threadIdx.x;
-    const int m = blockIdx.y;
-    if (c->nchunks == 1 || n >= c->n)
-        return;
     const size_t np = (size_t)c->np;
     const size_t pplane = (size_t)c->max_chunks * np;
     const double *part = reinterpret_cast<const double *>(ws + c->off_part);
@@ -1845,6 +2450,20 @@ __global__ __launch_bounds__(kBlock) void k_combine(char *__restrict__ ws,
         blk[m * np + n] = A;
         blk[(kPlaneB + m) * np + n] = B;
     }
+}
+
+// `far`: the near pass has combined the simple-shear channels.
+template <typename P>
+__global__ __launch_bounds__(kBlock) void k_combine(char *__restrict__ ws,
+                                                    const ChanDev *__restrict__ chans,
+                                                    const NodeTile *__restrict__ tiles, int far)
+{
+    const NodeTile tl = tiles[blockIdx.x];
+    const ChanDev *c = chans + tl.ch;
+    const int n = tl.n0 + threadIdx.x;
+    if (c->nchunks == 1 || n >= c->n || (far && !c->finger))
+        return;
+    combine_node<P>(ws, c, n, (int)blockIdx.y);
 }
 
 // ---------------------------------------------------------------------------
@@ -2624,10 +3243,12 @@ void launch_fill_zero(void *p, size_t bytes, hipStream_t st)
 }
 
 void launch_lb(int prec, char *ws, const ChanDev *chans, const NodeTile *tiles, int n_tiles,
-               const int64_t *tcount, int trel, int *tile_counters, hipStream_t st)
+               const int64_t *tcount, int trel, int *tile_counters, int span, int blk,
+               hipStream_t st)
 {
     LBMAX_BY_PREC(prec, hipLaunchKernelGGL((k_lb<P, S>), dim3(n_tiles), dim3(kBlock), 0, st, ws,
-                                           chans, tiles, tcount, trel, tile_counters));
+                                           chans, tiles, tcount, trel, tile_counters,
+                                           span, blk));
 }
 
 // Shapes of the history pass: (nodes per lane V, steps per pass M, rows
@@ -2667,7 +3288,7 @@ void launch_lb(int prec, char *ws, const ChanDev *chans, const NodeTile *tiles, 
 
 void launch_hist_pass(int prec, int vec, int block, char *ws, const ChanDev *chans,
                       const HistTile *tiles, int n_tiles, const int64_t *tcount, int trel,
-                      int persistent_grid, int *counter, hipStream_t st)
+                      int persistent_grid, int *counter, bool far, hipStream_t st)
 {
     if (n_tiles <= 0)
         return;
@@ -2679,16 +3300,101 @@ void launch_hist_pass(int prec, int vec, int block, char *ws, const ChanDev *cha
         if (persistent_grid > 0)                                                 \
             hipLaunchKernelGGL((k_hist_pass_persistent<P, H, V, M, U, F>), dim3(grid), \
                                dim3(kBlock), 0, st, ws, chans, tiles, n_tiles,   \
-                               tcount, trel, counter);                           \
+                               tcount, trel, counter, far ? 1 : 0);              \
         else                                                                     \
             hipLaunchKernelGGL((k_hist_pass<P, H, V, M, U, F>), dim3(grid),         \
                                dim3(kBlock), 0, st, ws, chans, tiles, n_tiles,   \
-                               tcount, trel);                                    \
+                               tcount, trel, far ? 1 : 0);                       \
     } while (0)
 #define LBMAX_PASS_SHAPES LBMAX_PASS_SHAPE_TABLE(block, vec, LBMAX_PASS)
     LBMAX_BY_PREC(prec, LBMAX_PASS_SHAPES);
 #undef LBMAX_PASS_SHAPES
 #undef LBMAX_PASS
+}
+
+#define LBMAX_BY_HIST(prec, BODY)                                                \
+    do {                                                                         \
+        if ((prec) == 0) {                                                       \
+            typedef double H;                                                    \
+            BODY;                                                                \
+        } else {                                                                 \
+            typedef float H;                                                     \
+            BODY;                                                                \
+        }                                                                        \
+    } while (0)
+
+void launch_far_pass(int prec, int sub, char *ws, const ChanDev *chans, const HistTile *tiles,
+                     int n_tiles, const int64_t *tcount, int trel, int span, int blk,
+                     hipStream_t st)
+{
+    if (n_tiles <= 0)
+        return;
+    const int per_group = kBlock / kWave;
+#define LBMAX_FAR(SUB)                                                                          \
+    LBMAX_BY_HIST(prec, hipLaunchKernelGGL((k_far_pass<H, SUB>),                                \
+                                           dim3(SUB == 1 ? (n_tiles + per_group - 1) / per_group \
+                                                         : n_tiles),                            \
+                                           dim3(SUB == 1 ? kBlock : SUB * kWave), 0, st, ws,    \
+                                           chans, tiles, n_tiles, tcount, trel, span, blk))
+    if (sub >= 8)
+        LBMAX_FAR(8);
+    else if (sub >= 4)
+        LBMAX_FAR(4);
+    else
+        LBMAX_FAR(1);
+#undef LBMAX_FAR
+}
+
+void launch_near_pass(int prec, bool split, char *ws, const ChanDev *chans,
+                      const NodeTile *tiles, int n_tiles, const int64_t *tcount, int trel,
+                      int span, int blk, const double *tabs, hipStream_t st)
+{
+    if (n_tiles <= 0)
+        return;
+    if (split)
+        LBMAX_BY_PREC(prec, hipLaunchKernelGGL((k_near_pass<P, H, 8>),
+                                               dim3(n_tiles * (kBlock / kWave)), dim3(kBlock), 0,
+                                               st, ws, chans, tiles, tcount, trel, span, blk, tabs));
+    else
+        LBMAX_BY_PREC(prec, hipLaunchKernelGGL((k_near_pass<P, H, kFarNearBlock>), dim3(n_tiles),
+                                               dim3(kBlock), 0, st, ws, chans, tiles, tcount,
+                                               trel, span, blk, tabs));
+}
+
+// d_p(v): the Chebyshev interpolation of exp(-z u v) in u at P nodes, in powers
+// of u (in long double: the powers' coefficients are small differences).
+void fill_far_table(int prec, int span, double *out)
+{
+    typedef long double L;
+    const int P = far_terms(prec);
+    const L z = (L)kFarZ, pi = acosl((L)-1), mbar = (L)(span - 1) / 2;
+    // T[q][i]: coefficient of u^i in the Chebyshev polynomial T_q
+    L T[kFarMaxTerms][kFarMaxTerms] = {};
+    T[0][0] = 1;
+    T[1][1] = 1;
+    for (int q = 2; q < P; ++q)
+        for (int i = 0; i < P; ++i)
+            T[q][i] = (i > 0 ? 2 * T[q - 1][i - 1] : (L)0) - T[q - 2][i];
+    L cq[kFarMaxTerms][kFarMaxTerms];  // cos(q theta_j)
+    for (int q = 0; q < P; ++q)
+        for (int j = 0; j < P; ++j)
+            cq[q][j] = cosl(q * (pi * ((L)j + (L)0.5) / P));
+    for (int m = 0; m < span; ++m) {
+        const L v = ((L)m - mbar) / mbar;
+        L f[kFarMaxTerms], d[kFarMaxTerms] = {};
+        for (int j = 0; j < P; ++j)
+            f[j] = expl(-z * cq[1][j] * v);
+        for (int q = 0; q < P; ++q) {
+            L a = 0;
+            for (int j = 0; j < P; ++j)
+                a += f[j] * cq[q][j];
+            a *= (q == 0 ? (L)1 : (L)2) / P;
+            for (int i = 0; i < P; ++i)
+                d[i] += a * T[q][i];
+        }
+        for (int i = 0; i < P; ++i)
+            out[m * P + i] = (double)d[i];
+    }
 }
 
 // Workgroups of the persistent pass that are resident on one compute unit.
@@ -2801,12 +3507,12 @@ void launch_inst_step(int prec, char *ws, const ChanDev *chans, const NodeTile *
 }
 
 void launch_combine(int prec, int block, char *ws, const ChanDev *chans, const NodeTile *tiles,
-                    int n_tiles, hipStream_t st)
+                    int n_tiles, bool far, hipStream_t st)
 {
     if (n_tiles <= 0 || block <= 0)
         return;
     LBMAX_BY_PREC(prec, hipLaunchKernelGGL(k_combine<P>, dim3(n_tiles, block), dim3(kBlock), 0,
-                                           st, ws, chans, tiles));
+                                           st, ws, chans, tiles, far ? 1 : 0));
 }
 
 void launch_fused_steps(int prec, bool lds, char *ws, const ChanDev *chans, int n_ch,

@@ -171,8 +171,11 @@ std::string check_desc(const lb_channel_desc *ch, int32_t n_ch, lb_precision pre
 struct Plan {
     size_t total = 0;
     size_t off_tcount = 0, off_chans = 0, off_node_tiles = 0, off_hist_tiles = 0,
-           off_stage = 0, stage_bytes = 0;
+           off_far_tiles = 0, off_far_tab = 0, off_stage = 0, stage_bytes = 0;
     int n_node_tiles = 0, n_hist_tiles_max = 0;
+    // longest and shortest span of far sums over the channels that take them
+    // (far_span = 0: none does)
+    int far_span = 0, far_span_min = kFarMaxSteps;
     std::vector<ChanDev> chans;
 };
 
@@ -189,6 +192,26 @@ size_t lattice_bytes(lb_precision) { return 8; }
 size_t pop_bytes(lb_precision prec) { return prec == LB_F32 ? 4 : 8; }
 size_t history_bytes(lb_precision prec) { return prec == LB_F64 ? 8 : 4; }
 int prec_code(lb_precision prec) { return prec == LB_F64 ? 0 : (prec == LB_F32 ? 1 : 2); }
+
+// Most steps one far pass serves on a channel: 128, 64, 32, or 0 where the
+// general pass is the one to take.  The window has to be a few spans long,
+// since the ages that leave it during a span are summed block by block.  And
+// the rates have to stay within the expansion: their spread over the window is
+// taken as the wall rate 4 u / ly of a channel flow whose peak speed u is two
+// fifths of the Mach guard's.  (A longer span only reads the window less often;
+// six FP64 channels of 32 nodes in a transient, 50-step calls: 0.90 ms a call
+// with 64-step spans, 1.06 ms with 128-step ones, which some tiles leave for
+// the general pass.)
+int far_span_for(const ChanDev &c)
+{
+    if (c.qb > 0 || c.law != 0 || c.finger || c.n_hist > (1 << 22))
+        return 0;
+    const double spread = 4.0 * 0.04 / c.ly * c.inv_gc;
+    for (int S = kFarMaxSteps; S >= kFarNearBlock; S /= 2)
+        if (c.n_hist >= kFarMinWindow * S && spread <= kFarZ / (0.5 * (S - 1)))
+            return S;
+    return 0;
+}
 
 Plan make_plan(const lb_channel_desc *ch, int32_t n_ch, lb_precision prec)
 {
@@ -227,6 +250,11 @@ Plan make_plan(const lb_channel_desc *ch, int32_t n_ch, lb_precision prec)
         c.l2_gc = M_LOG2E * c.inv_gc;
         c.gx = d.gx;
         c.gy = d.gy;
+        const int span = far_span_for(c);
+        c.far = span;
+        P.far_span = std::max(P.far_span, span);
+        if (span > 0)
+            P.far_span_min = std::min(P.far_span_min, span);
         const int blocks = (c.n + kBlock - 1) / kBlock;
         P.n_node_tiles += blocks;
         // history tiles: at most one per wavefront of nodes and age chunk
@@ -238,6 +266,15 @@ Plan make_plan(const lb_channel_desc *ch, int32_t n_ch, lb_precision prec)
     off = align_up(off + (size_t)P.n_node_tiles * sizeof(NodeTile), 256);
     P.off_hist_tiles = off;
     off = align_up(off + (size_t)P.n_hist_tiles_max * sizeof(HistTile), 256);
+    P.off_far_tiles = off;
+    P.off_far_tab = off;
+    if (P.far_span > 0) {
+        off = align_up(off + (size_t)P.n_hist_tiles_max * sizeof(HistTile), 256);
+        P.off_far_tab = off;
+        off = align_up(off + (size_t)kFarClasses * kFarMaxSteps * far_terms(prec_code(prec)) *
+                                 sizeof(double),
+                       256);
+    }
     P.off_stage = off;
     P.stage_bytes = align_up(stage * sizeof(double), 256);
     off += P.stage_bytes;
@@ -266,10 +303,18 @@ Plan make_plan(const lb_channel_desc *ch, int32_t n_ch, lb_precision prec)
         if (c.has_r && !c.finger)
             off = align_up(off + (size_t)c.n_hist * hplane, 256);
         c.off_part = (int64_t)off;
-        if (c.max_chunks > 1)
-            off = align_up(off + (size_t)(c.finger ? kFingerPartPlanes : kPartPlanes) *
-                                     c.max_chunks * c.np * sizeof(double),
-                           256);
+        const size_t part_planes =
+            c.max_chunks == 1 ? 0 : (c.finger ? kFingerPartPlanes : kPartPlanes);
+        // far sums: in the planes of the chunk partials (a tile takes the one
+        // or the other), or their own where the window has a single chunk;
+        // then their strain and the markers that tell which
+        const size_t far_planes =
+            c.far ? std::max(part_planes, 2 * (size_t)far_terms(prec_code(prec))) + 2 : 0;
+        c.off_far = c.off_part;
+        c.far_t = c.far ? (int)far_planes - 2 : 0;
+        off = align_up(off + std::max(part_planes, far_planes) * c.max_chunks * c.np *
+                                 sizeof(double),
+                       256);
         c.off_blk = (int64_t)off;
         off = align_up(off + (size_t)blk_planes(c) * c.np * sizeof(double), 256);
         const size_t grows = (size_t)c.qb * c.qc;  // 0 without a grid
@@ -312,8 +357,14 @@ struct lb_handle {
     ChanDev *d_chans = nullptr;
     NodeTile *d_node_tiles = nullptr;
     HistTile *d_hist_tiles = nullptr;
+    HistTile *d_far_tiles = nullptr;    // the simple-shear channels' tiles of 64 nodes
+    const double *d_far_tab = nullptr;  // expansion coefficients, one table per span
     double *d_stage = nullptr;
     int n_node_tiles = 0, n_hist_tiles = 0;
+    int n_far_tiles = 0;
+    int far_sub = 1;           // wavefronts per far tile
+    bool near_split = false;   // near pass with four wavefronts per 64 nodes
+    bool adjoint_kind = false; // every channel is of the kind the adjoint covers
     // history tile groups: lane width 1, 2, 4 (simple-shear pass), full tensor,
     // accumulated-strain damping
     int hist_group_begin[5] = {0, 0, 0, 0, 0}, hist_group_count[5] = {0, 0, 0, 0, 0};
@@ -327,10 +378,11 @@ struct lb_handle {
     int fuse_mode = 1;         // lb_set_fused
     // host mirrors kept alive for asynchronous uploads
     std::vector<NodeTile> node_tiles;
-    std::vector<HistTile> hist_tiles;
+    std::vector<HistTile> hist_tiles, far_tiles;
     std::vector<char> upload;
     // graph replay
-    int graph_steps = 0;
+    int graph_steps = 0;       // lb_set_graph
+    int graph_unit = 0;        // steps of the captured graph
     bool graph_dirty = true;
     hipStream_t cap_stream = nullptr;
     hipGraph_t graph = nullptr;
@@ -419,12 +471,17 @@ void build_tiles(lb_handle *h)
 {
     h->node_tiles.clear();
     h->hist_tiles.clear();
+    h->far_tiles.clear();
     h->any_chunked = false;
+    h->adjoint_kind = true;
+    int wide_tiles = 0, far_waves = 0, far_rows = 0;
     h->any_grid = h->any_window = h->any_inst = false;
     for (int ci = 0; ci < h->n_ch; ++ci) {
         const ChanDev &c = h->plan.chans[ci];
         for (int n0 = 0; n0 < c.n; n0 += kBlock)
             h->node_tiles.push_back({ci, n0});
+        if (c.lx != 1 || c.has_r || c.law || c.finger || c.coupling || c.qb > 0)
+            h->adjoint_kind = false;
         if (c.qb > 0) {
             h->any_grid = true;  // stepped by k_grid_step, no history tiles
             continue;
@@ -442,6 +499,15 @@ void build_tiles(lb_handle *h)
             const int k1 = (int)((int64_t)c.n_hist * (k + 1) / c.nchunks);
             for (int n0 = 0; n0 < c.n; n0 += span)
                 h->hist_tiles.push_back({ci, n0, k0, k1, k, 0});
+            if (h->plan.far_span > 0 && c.law == 0 && !c.finger)
+                for (int n0 = 0; n0 < c.n; n0 += kWave) {
+                    h->far_tiles.push_back({ci, n0, k0, k1, k, 0});
+                    if (c.far) {
+                        far_waves += 1;
+                        far_rows = std::max(far_rows, k1 - k0);
+                        wide_tiles += k == 0 ? 1 : 0;
+                    }
+                }
         }
     }
     // Group by lane width (one launch each), longest age range first inside
@@ -460,6 +526,18 @@ void build_tiles(lb_handle *h)
                              return group(a) < group(b);
                          return (a.k1 - a.k0) > (b.k1 - b.k0);
                      });
+    std::stable_sort(h->far_tiles.begin(), h->far_tiles.end(),
+                     [](const HistTile &a, const HistTile &b) {
+                         return (a.k1 - a.k0) > (b.k1 - b.k0);
+                     });
+    h->n_far_tiles = (int)h->far_tiles.size();
+    // Far tiles are split while the launch stays within 16 wavefronts per
+    // compute unit (4096) and a part keeps at least 32 rows.
+    h->far_sub = 1;
+    for (int sub : {4, 8})
+        if (far_waves * sub <= 4096 && far_rows >= 32 * sub)
+            h->far_sub = sub;
+    h->near_split = wide_tiles <= 1024;
     for (int g = 0; g < 5; ++g)
         h->hist_group_count[g] = 0;
     for (const HistTile &tl : h->hist_tiles)
@@ -508,6 +586,7 @@ void default_tiling(lb_handle *h)
 lb_status upload_tables(lb_handle *h)
 {
     if ((int)h->hist_tiles.size() > h->plan.n_hist_tiles_max ||
+        (int)h->far_tiles.size() > h->plan.n_hist_tiles_max ||
         (int)h->node_tiles.size() > h->plan.n_node_tiles)
         return fail(LB_EINVAL, "internal: tile lists exceed their workspace area");
     HIP_TRY(h, hipMemcpyAsync(h->d_chans, h->plan.chans.data(),
@@ -519,6 +598,10 @@ lb_status upload_tables(lb_handle *h)
     HIP_TRY(h, hipMemcpyAsync(h->d_hist_tiles, h->hist_tiles.data(),
                               h->hist_tiles.size() * sizeof(HistTile),
                               hipMemcpyHostToDevice, h->stream));
+    if (!h->far_tiles.empty())
+        HIP_TRY(h, hipMemcpyAsync(h->d_far_tiles, h->far_tiles.data(),
+                                  h->far_tiles.size() * sizeof(HistTile),
+                                  hipMemcpyHostToDevice, h->stream));
     // The host vectors are reused only after this synchronisation.
     HIP_TRY(h, hipStreamSynchronize(h->stream));
     h->graph_dirty = true;
@@ -553,10 +636,77 @@ lb_status resolve_timing(lb_handle *h)
     return LB_OK;
 }
 
-// One step's launches, step t = *tcount + trel, position m in its block (0:
-// the history pass).  With `timed`, HIP event pairs bracket the lattice launch
-// (slot 1) and the history work (slot 0 for a pass, slot 2 for a block step).
-lb_status enqueue_step(lb_handle *h, hipStream_t st, int trel, int m, bool timed)
+// Far sums in effect for a block: the span's steps and the block's place in it.
+struct FarBlock {
+    int span = 0;   // 0: the block takes the general pass alone
+    int index = 0;  // block of the span
+};
+
+// The expansion coefficients of every span (constants of the library), by
+// history type.
+const std::vector<double> &far_tables(int pc)
+{
+    const auto make = [](int code) {
+        const size_t table = (size_t)kFarMaxSteps * far_terms(code);
+        std::vector<double> v(kFarClasses * table, 0.0);
+        for (int S = kFarNearBlock; S <= kFarMaxSteps; S *= 2)
+            fill_far_table(code, S, v.data() + far_class(S) * table);
+        return v;
+    };
+    if (pc == 0) {
+        static const std::vector<double> f64 = make(0);
+        return f64;
+    }
+    static const std::vector<double> f32 = make(1);
+    return f32;
+}
+
+// The history pass of a block of `block` steps from step *tcount + trel.
+void enqueue_pass(lb_handle *h, hipStream_t st, int trel, int block, FarBlock far)
+{
+    static const int kVec[3] = {1, 2, 4};
+    if (far.span > 0) {
+        if ((far.index * kFarNearBlock) % std::min(far.span, h->plan.far_span_min) == 0)
+            launch_far_pass(h->pc, h->far_sub, h->ws, h->d_chans, h->d_far_tiles,
+                            h->n_far_tiles, h->d_tcount, trel, far.span, far.index, st);
+        const int pgrid =
+            h->persistent ? h->num_cus * hist_pass_blocks_per_cu(h->pc, 1, block) : 0;
+        launch_hist_pass(h->pc, 1, block, h->ws, h->d_chans, h->d_far_tiles, h->n_far_tiles,
+                         h->d_tcount, trel, pgrid, h->d_tile_counters, true, st);
+    } else {
+        for (int g = 0; g < 3; ++g) {
+            const int pgrid =
+                h->persistent ? h->num_cus * hist_pass_blocks_per_cu(h->pc, kVec[g], block) : 0;
+            launch_hist_pass(h->pc, kVec[g], block, h->ws, h->d_chans,
+                             h->d_hist_tiles + h->hist_group_begin[g], h->hist_group_count[g],
+                             h->d_tcount, trel, pgrid, h->d_tile_counters + g, false, st);
+        }
+    }
+    if (h->any_wm)
+        launch_wm_pass(h->pc, block, h->ws, h->d_chans, h->d_hist_tiles + h->hist_group_begin[4],
+                       h->hist_group_count[4], h->d_tcount, trel, st);
+    if (h->any_finger) {
+        const int pgrid =
+            h->persistent ? h->num_cus * finger_pass_blocks_per_cu(h->pc, block) : 0;
+        launch_finger_pass(h->pc, block, h->ws, h->d_chans,
+                           h->d_hist_tiles + h->hist_group_begin[3], h->hist_group_count[3],
+                           h->d_tcount, trel, pgrid, h->d_tile_counters + 3, st);
+    }
+    if (far.span > 0)
+        launch_near_pass(h->pc, h->near_split, h->ws, h->d_chans, h->d_node_tiles,
+                         h->n_node_tiles, h->d_tcount, trel, far.span, far.index, h->d_far_tab,
+                         st);
+    if (h->any_chunked && (far.span == 0 || h->any_finger))
+        launch_combine(h->pc, block, h->ws, h->d_chans, h->d_node_tiles, h->n_node_tiles,
+                       far.span > 0, st);
+}
+
+// One step's launches, step t = *tcount + trel, position m in its block of
+// `block` steps (0: the history pass).  With `timed`, HIP event pairs bracket
+// the lattice launch (slot 1) and the history work (slot 0 for a pass, slot 2
+// for a block step).
+lb_status enqueue_step(lb_handle *h, hipStream_t st, int trel, int m, int block, FarBlock far,
+                       bool timed)
 {
     hipEvent_t e[4] = {nullptr, nullptr, nullptr, nullptr};
     if (timed) {
@@ -568,45 +718,23 @@ lb_status enqueue_step(lb_handle *h, hipStream_t st, int trel, int m, bool timed
         HIP_TRY(h, hipEventRecord(e[0], st));
     }
     launch_lb(h->pc, h->ws, h->d_chans, h->d_node_tiles, h->n_node_tiles,
-              h->d_tcount, trel, h->d_tile_counters, st);
+              h->d_tcount, trel, h->d_tile_counters,
+              m == 0 ? far.span : 0, far.index, st);
     if (timed) {
         HIP_TRY(h, hipEventRecord(e[1], st));
         HIP_TRY(h, hipEventRecord(e[2], st));
     }
     if (h->any_grid)
-        launch_grid_step(h->pc, h->block, m, h->ws, h->d_chans, h->d_node_tiles,
+        launch_grid_step(h->pc, block, m, h->ws, h->d_chans, h->d_node_tiles,
                          h->n_node_tiles, h->d_tcount, trel, st);
     if (h->any_inst)
         launch_inst_step(h->pc, h->ws, h->d_chans, h->d_node_tiles, h->n_node_tiles,
                          h->d_tcount, trel, st);
-    if (m == 0) {
-        static const int kVec[3] = {1, 2, 4};
-        for (int g = 0; g < 3; ++g) {
-            const int pgrid =
-                h->persistent ? h->num_cus * hist_pass_blocks_per_cu(h->pc, kVec[g], h->block)
-                              : 0;
-            launch_hist_pass(h->pc, kVec[g], h->block, h->ws, h->d_chans,
-                             h->d_hist_tiles + h->hist_group_begin[g], h->hist_group_count[g],
-                             h->d_tcount, trel, pgrid, h->d_tile_counters + g, st);
-        }
-        if (h->any_wm)
-            launch_wm_pass(h->pc, h->block, h->ws, h->d_chans,
-                           h->d_hist_tiles + h->hist_group_begin[4], h->hist_group_count[4],
-                           h->d_tcount, trel, st);
-        if (h->any_finger) {
-            const int pgrid =
-                h->persistent ? h->num_cus * finger_pass_blocks_per_cu(h->pc, h->block) : 0;
-            launch_finger_pass(h->pc, h->block, h->ws, h->d_chans,
-                               h->d_hist_tiles + h->hist_group_begin[3], h->hist_group_count[3],
-                               h->d_tcount, trel, pgrid, h->d_tile_counters + 3, st);
-        }
-        if (h->any_chunked)
-            launch_combine(h->pc, h->block, h->ws, h->d_chans, h->d_node_tiles,
-                           h->n_node_tiles, st);
-    } else if (h->any_window) {
+    if (m == 0)
+        enqueue_pass(h, st, trel, block, far);
+    else if (h->any_window)
         launch_hist_step(h->pc, m, h->ws, h->d_chans, h->d_node_tiles, h->n_node_tiles,
                          h->d_tcount, trel, st);
-    }
     if (timed) {
         HIP_TRY(h, hipEventRecord(e[3], st));
         h->pending[1].push_back({e[0], e[1]});
@@ -618,23 +746,23 @@ lb_status enqueue_step(lb_handle *h, hipStream_t st, int trel, int m, bool timed
 // The in-block steps run fused: mode 2 whenever the channels fit a
 // workgroup; mode 1 (the default) in the LDS form where it applies, else in
 // the global-memory form only up to kFuseGlobalMaxNodes nodes per channel.
-bool fused_in_effect(const lb_handle *h)
+bool fused_in_effect(const lb_handle *h, int block)
 {
-    if (!h->fuse_ok || h->fuse_mode == 0 || h->block <= 1)
+    if (!h->fuse_ok || h->fuse_mode == 0 || block <= 1)
         return false;
     if (h->fuse_mode == 2)
         return true;
     return (h->fuse_lds_ok && h->fuse_lds_ready) || h->fuse_global_ok;
 }
 
-// Enqueue up to `left` steps starting at block position m: a fused launch
-// for the rest of the block when the handle allows it and m > 0, else one
-// step.  Sets *done to the steps enqueued.
-lb_status enqueue_span(lb_handle *h, hipStream_t st, int trel, int m, int64_t left, bool timed,
-                       int *done)
+// Enqueue up to `left` steps starting at position m of a block of `block`
+// steps: a fused launch for the rest of the block when the handle allows it
+// and m > 0, else one step.  Sets *done to the steps enqueued.
+lb_status enqueue_span(lb_handle *h, hipStream_t st, int trel, int m, int block, FarBlock far,
+                       int64_t left, bool timed, int *done)
 {
-    if (fused_in_effect(h) && m > 0) {
-        const int k = (int)std::min<int64_t>(left, h->block - m);
+    if (fused_in_effect(h, block) && m > 0) {
+        const int k = (int)std::min<int64_t>(left, block - m);
         hipEvent_t e[2] = {nullptr, nullptr};
         if (timed) {
             for (int i = 0; i < 2; ++i) {
@@ -654,7 +782,56 @@ lb_status enqueue_span(lb_handle *h, hipStream_t st, int trel, int m, int64_t le
         return check_launch(h, "fused steps launch");
     }
     *done = 1;
-    return enqueue_step(h, st, trel, m, timed);
+    return enqueue_step(h, st, trel, m, block, far, timed);
+}
+
+// Steps the next span of far sums covers, from a block's start with `left`
+// steps to go in this call (0: none).  Spans lie inside one lb_step call, so
+// nothing but the block sums outlives it.  Handles set to 32 steps per pass
+// take them as they are; shorter blocks run as blocks of 32 steps inside a
+// span while at least 32 steps are left.  Unblocked handles do so from 8
+// steps on (a far, a general and a near launch against one pass per step),
+// and their last block ends with the call; channels of the kind the adjoint
+// covers stay unblocked, so that a gradient does not depend on how the run is
+// cut into calls.
+int64_t far_steps(const lb_handle *h, int64_t left, int *span)
+{
+    *span = 0;
+    if (h->plan.far_span == 0)
+        return 0;
+    if (h->block != kFarNearBlock) {
+        if (h->any_grid || h->any_finger || (h->block == 1 && h->adjoint_kind) ||
+            left < (h->block == 1 ? 8 : kFarNearBlock))
+            return 0;
+    }
+    int S = kFarNearBlock;
+    while (S < h->plan.far_span && S < left)
+        S *= 2;
+    *span = S;
+    const int64_t n = std::min<int64_t>(S, left);
+    return h->block == 1 || h->block == kFarNearBlock ? n : n / kFarNearBlock * kFarNearBlock;
+}
+
+// Enqueue the n steps of a span (n <= span), the first at *tcount + trel.
+lb_status enqueue_far_span(lb_handle *h, hipStream_t st, int trel, int span, int n, bool timed)
+{
+    for (int i = 0, k = 0; i < n; i += k) {
+        const FarBlock far{span, i / kFarNearBlock};
+        lb_status s = enqueue_span(h, st, trel + i, i % kFarNearBlock, kFarNearBlock, far, n - i,
+                                   timed, &k);
+        if (s != LB_OK)
+            return s;
+    }
+    return LB_OK;
+}
+
+// Steps of one graph: the setting, or the span where far sums are in effect
+// from graph start to graph start.
+int graph_unit(const lb_handle *h)
+{
+    int span = 0;
+    const int64_t n = far_steps(h, kFarMaxSteps, &span);
+    return n > 0 ? (int)n : h->graph_steps;
 }
 
 lb_status capture_graph(lb_handle *h)
@@ -669,19 +846,24 @@ lb_status capture_graph(lb_handle *h)
     }
     if (!h->cap_stream)
         HIP_TRY(h, hipStreamCreateWithFlags(&h->cap_stream, hipStreamNonBlocking));
+    h->graph_unit = graph_unit(h);
     HIP_TRY(h, hipStreamBeginCapture(h->cap_stream, hipStreamCaptureModeThreadLocal));
-    for (int i = 0, k = 0; i < h->graph_steps; i += k) {
-        lb_status s = enqueue_span(h, h->cap_stream, i, i % h->block, h->graph_steps - i, false,
-                                   &k);
-        if (s != LB_OK) {
-            hipGraph_t g = nullptr;
-            (void)hipStreamEndCapture(h->cap_stream, &g);
-            if (g)
-                (void)hipGraphDestroy(g);
-            return s;
-        }
+    int span = 0;
+    lb_status s = LB_OK;
+    if (far_steps(h, h->graph_unit, &span) > 0)
+        s = enqueue_far_span(h, h->cap_stream, 0, span, h->graph_unit, false);
+    else
+        for (int i = 0, k = 0; s == LB_OK && i < h->graph_unit; i += k)
+            s = enqueue_span(h, h->cap_stream, i, i % h->block, h->block, FarBlock{},
+                             h->graph_unit - i, false, &k);
+    if (s != LB_OK) {
+        hipGraph_t g = nullptr;
+        (void)hipStreamEndCapture(h->cap_stream, &g);
+        if (g)
+            (void)hipGraphDestroy(g);
+        return s;
     }
-    launch_tick(h->d_tcount, h->graph_steps, h->cap_stream);
+    launch_tick(h->d_tcount, h->graph_unit, h->cap_stream);
     HIP_TRY(h, hipStreamEndCapture(h->cap_stream, &h->graph));
     HIP_TRY(h, hipGraphInstantiate(&h->graph_exec, h->graph, nullptr, nullptr, 0));
     h->graph_dirty = false;
@@ -1034,6 +1216,8 @@ lb_status lb_init(const lb_channel_desc *ch, int32_t n_ch, lb_precision prec, vo
     h->d_chans = reinterpret_cast<ChanDev *>(h->ws + h->plan.off_chans);
     h->d_node_tiles = reinterpret_cast<NodeTile *>(h->ws + h->plan.off_node_tiles);
     h->d_hist_tiles = reinterpret_cast<HistTile *>(h->ws + h->plan.off_hist_tiles);
+    h->d_far_tiles = reinterpret_cast<HistTile *>(h->ws + h->plan.off_far_tiles);
+    h->d_far_tab = reinterpret_cast<const double *>(h->ws + h->plan.off_far_tab);
     h->d_stage = reinterpret_cast<double *>(h->ws + h->plan.off_stage);
     for (int i = 0; i < n_ch; ++i) {
         h->lx.push_back(ch[i].lx);
@@ -1071,7 +1255,14 @@ lb_status lb_init(const lb_channel_desc *ch, int32_t n_ch, lb_precision prec, vo
     lb_status s = check_launch(h, "zero fill");
     if (s != LB_OK)
         return bail(s);
-    s = upload_tables(h);
+    if (h->plan.far_span > 0) {
+        const std::vector<double> &tab = far_tables(h->pc);
+        if (hipMemcpyAsync(const_cast<double *>(h->d_far_tab), tab.data(),
+                           tab.size() * sizeof(double), hipMemcpyHostToDevice,
+                           h->stream) != hipSuccess)
+            return bail(fail(LB_EDEVICE, "far table upload failed"));
+    }
+    s = upload_tables(h);  // and waits for the stream
     if (s != LB_OK)
         return bail(s);
     for (int i = 0; i < n_ch; ++i) {
@@ -1129,18 +1320,31 @@ lb_status lb_step(lb_handle *h, int64_t n_steps)
     auto eager = [&](int64_t count) -> lb_status {
         while (count > 0) {
             const int batch = (int)std::min(count, kMaxStepsPerBatch);
-            for (int i = 0, k = 0; i < batch; i += k) {
-                lb_status e = enqueue_span(h, h->stream, i, h->block_pos, batch - i, h->profile,
-                                           &k);
+            int i = 0;
+            for (int k = 0; i < batch; i += k) {
+                int span = 0;
+                const int64_t far = h->block_pos == 0 ? far_steps(h, count - i, &span) : 0;
+                if (far > 0 && far <= batch - i) {
+                    k = (int)far;
+                    lb_status e = enqueue_far_span(h, h->stream, i, span, k, h->profile);
+                    if (e != LB_OK)
+                        return e;
+                    h->block_pos = h->block == kFarNearBlock ? k % kFarNearBlock : 0;
+                    continue;
+                }
+                if (far > 0 && i > 0)
+                    break;  // the span starts the next batch
+                lb_status e = enqueue_span(h, h->stream, i, h->block_pos, h->block, FarBlock{},
+                                           batch - i, h->profile, &k);
                 if (e != LB_OK)
                     return e;
                 h->block_pos = (h->block_pos + k) % h->block;
             }
-            launch_tick(h->d_tcount, batch, h->stream);
+            launch_tick(h->d_tcount, i, h->stream);
             lb_status e = check_launch(h, "tick");
             if (e != LB_OK)
                 return e;
-            count -= batch;
+            count -= i;
         }
         return LB_OK;
     };
@@ -1151,15 +1355,16 @@ lb_status lb_step(lb_handle *h, int64_t n_steps)
         if (s != LB_OK)
             return s;
         left -= head;
-        if (left >= h->graph_steps) {
+        const int unit = graph_unit(h);
+        if (left >= unit) {
             if (h->graph_dirty) {
                 s = capture_graph(h);
                 if (s != LB_OK)
                     return s;
             }
-            while (left >= h->graph_steps) {
+            while (left >= unit) {
                 HIP_TRY(h, hipGraphLaunch(h->graph_exec, h->stream));
-                left -= h->graph_steps;
+                left -= unit;
             }
         }
     }
@@ -1443,7 +1648,7 @@ int32_t lb_get_adjoint_block(const lb_handle *h)
 
 int32_t lb_get_fused(const lb_handle *h)
 {
-    if (!h || !fused_in_effect(h))
+    if (!h || !fused_in_effect(h, h->block))
         return 0;
     return (h->fuse_mode == 1 && h->fuse_lds_ok && h->fuse_lds_ready) ? 2 : 1;
 }
