@@ -159,9 +159,16 @@ void launch_finger_pass(int prec, int block, char *ws, const ChanDev *chans,
                         const HistTile *tiles, int n_tiles, const int64_t *tcount, int trel,
                         int persistent_grid, int *counter, hipStream_t st);
 int finger_pass_blocks_per_cu(int prec, int block);
-// Accumulated-strain damping: one pass per block, O(1) work per entry.
+// Accumulated-strain damping: one pass per block, O(1) work per entry; with
+// `far`, of the channels that take no far sums.
 void launch_wm_pass(int prec, int block, char *ws, const ChanDev *chans, const HistTile *tiles,
-                    int n_tiles, const int64_t *tcount, int trel, hipStream_t st);
+                    int n_tiles, const int64_t *tcount, int trel, bool far, hipStream_t st);
+// Block blk of a span (as launch_far_pass and launch_near_pass) for these
+// channels: the far pass where `far` (some channel's span starts here), and
+// the near pass.
+void launch_wm_span(int prec, bool split, char *ws, const ChanDev *chans, const NodeTile *tiles,
+                    int n_tiles, const int64_t *tcount, int trel, int span, int blk, bool far,
+                    hipStream_t st);
 // Instantaneous law (Eq. inlM), every step, node-local (other channels return).
 void launch_inst_step(int prec, char *ws, const ChanDev *chans, const NodeTile *tiles,
                       int n_tiles, const int64_t *tcount, int trel, hipStream_t st);

@@ -570,7 +570,7 @@ __global__ __launch_bounds__(kBlock, 5) void k_lb(char *__restrict__ ws,
     if (n >= c->n)
         return;
     // first step of a far span of this channel (span = 0: not a span's step)
-    if (span && c->far && threadIdx.x % kWave == 0 &&
+    if (span && c->far && c->law == 0 && threadIdx.x % kWave == 0 &&
         (blk * kFarNearBlock) % far_span(c, span) == 0)
         *far_marker(ws, c, n) = 0.0;
     lb_node<P, S>(ws, c, n, *tcount + trel);
@@ -1160,8 +1160,9 @@ __device__ __forceinline__ R far_center(const char *__restrict__ ws, const ChanD
 }
 
 // Rows of slots slot, slot - 1, .., of which the first `count` are wanted (at
-// most G); the others come as zero entries.
-template <typename R, int G, bool HAS_R>
+// most G); the others come as entries of shear rate zero, |gamma_dot| zero
+// (ZERO_R) or that of the first.
+template <typename R, int G, bool HAS_R, bool ZERO_R>
 __device__ __forceinline__ void load_rows_masked(const R *__restrict__ ring_s,
                                                  const R *__restrict__ ring_r, size_t np,
                                                  uint32_t off, int slot, int count,
@@ -1178,7 +1179,7 @@ __device__ __forceinline__ void load_rows_masked(const R *__restrict__ ring_s,
     for (int u = 1; u < G; ++u) {
         sv[u].v[0] = u < count ? sv[u].v[0] : R(0);
         if (HAS_R)
-            rv[u].v[0] = u < count ? rv[u].v[0] : rv[0].v[0];
+            rv[u].v[0] = u < count ? rv[u].v[0] : (ZERO_R ? R(0) : rv[0].v[0]);
     }
 }
 
@@ -1187,7 +1188,7 @@ __device__ __forceinline__ void load_rows_masked(const R *__restrict__ ring_s,
 // The last rows of a run (before the ring wraps, or of the range) come in
 // groups filled up with zero entries.  block() is called every F rows at
 // most, and ends the walk when it returns false.
-template <typename R, int G, int F, bool HAS_R, typename Fn, typename Block>
+template <typename R, int G, int F, bool HAS_R, bool ZERO_R, typename Fn, typename Block>
 __device__ __forceinline__ bool walk_rows(const R *__restrict__ ring_s,
                                           const R *__restrict__ ring_r, size_t np,
                                           uint32_t off, int H, int p, int k, int kend, Fn &&fn,
@@ -1218,8 +1219,8 @@ __device__ __forceinline__ bool walk_rows(const R *__restrict__ ring_s,
         }
         if (j < run) {
             for (; j < run; j += G) {
-                load_rows_masked<R, G, HAS_R>(ring_s, ring_r, np, off, slot - j, run - j, as,
-                                              ar);
+                load_rows_masked<R, G, HAS_R, ZERO_R>(ring_s, ring_r, np, off, slot - j, run - j,
+                                                      as, ar);
                 fn(as, ar, k + j);
             }
             if (!block())
@@ -1253,7 +1254,7 @@ __device__ __forceinline__ bool far_moments(const R *__restrict__ ring_s,
     for (int q = 0; q < P; ++q)
         pa[q] = pb[q] = R(0);
     bool bad = false;
-    return walk_rows<R, G, F, HAS_R>(
+    return walk_rows<R, G, F, HAS_R, false>(
         ring_s, ring_r, np, off, H, p, ka, kb,
         [&](const Pack<R, 1>(&sv)[G], const Pack<R, 1>(&rv)[G], int k) {
 #pragma clang fp contract(off)
@@ -1496,13 +1497,13 @@ __device__ __forceinline__ void near_tile(char *__restrict__ ws, const ChanDev *
         }
     };
     const auto go_on = [] { return true; };
-    walk_rows<R, G, 128, HAS_R>(ring_s, ring_r, np, off, H, p, 1, 1 + o, sum_group, go_on);
+    walk_rows<R, G, 128, HAS_R, false>(ring_s, ring_r, np, off, H, p, 1, 1 + o, sum_group, go_on);
     const double D0 = loc;
     loc += Tf;
     // the window's end: whole-weight ages, then those that leave in the block
-    walk_rows<R, G, 128, HAS_R>(ring_s, ring_r, np, off, H, p, H - S + o, H - kFarNearBlock,
+    walk_rows<R, G, 128, HAS_R, false>(ring_s, ring_r, np, off, H, p, H - S + o, H - kFarNearBlock,
                                 sum_group, go_on);
-    walk_rows<R, G, 128, HAS_R>(ring_s, ring_r, np, off, H, p, H - kFarNearBlock, H,
+    walk_rows<R, G, 128, HAS_R, false>(ring_s, ring_r, np, off, H, p, H - kFarNearBlock, H,
                            [&](const Pack<R, 1>(&sv)[G], const Pack<R, 1>(&rv)[G], int k) {
 #pragma unroll
                                for (int u = 0; u < G; ++u) {
@@ -2294,13 +2295,234 @@ template <typename P, typename R, int M>
 __global__ __launch_bounds__(kBlock) void k_wm_pass(char *__restrict__ ws,
                                                     const ChanDev *__restrict__ chans,
                                                     const HistTile *__restrict__ tiles,
-                                                    const int64_t *__restrict__ tcount, int trel)
+                                                    const int64_t *__restrict__ tcount, int trel,
+                                                    int far)
 {
     const HistTile tl = tiles[blockIdx.x];
     const ChanDev *c = chans + tl.ch;
-    if (tl.n0 + (int)(threadIdx.x & ~63u) >= c->n)
+    if (tl.n0 + (int)(threadIdx.x & ~63u) >= c->n || (far && c->far))
         return;
     wm_tile<P, R, M>(ws, c, tl, *tcount + trel);
+}
+
+// Far sums of an accumulated-strain channel.  The damping factorises over time
+// exactly, so the window's interior (ages 1 .. H - S - 1 at the first step of a
+// span of S steps) needs two sums for every step of the span, A and B with the
+// factors of the span's start, beside its strain T and accumulated rate R:
+// planes A, B, T, R of off_far.  The near pass of each block of 32 steps
+// carries them to the block's start and adds the entries pushed since and the
+// window's end.  The far pass is bound by the window's bytes (1024 x 512
+// nodes, 4096 entries: one reading per 128 steps in place of one per 32, each
+// 3.2 ms, 5.3 TB/s); where whole channels are few wavefronts (SUB = 4), the
+// ages of 64 nodes are split over the four wavefronts of a workgroup.
+struct WmSums {
+    double A = 0.0, B = 0.0, T = 0.0, R = 0.0;
+
+    // Append the sums of the ages behind these (formed from T = R = 0 on).
+    __device__ __forceinline__ void append(const WmSums &o, double inv_gc)
+    {
+        const double f = exp(-inv_gc * R);
+        const double a = f * o.A;
+        A += a;
+        B += fma(2.0 * T, a, f * o.B);
+        T += o.T;
+        R += o.R;
+    }
+};
+
+// Ages [ka, kb), each with weight 1, into `w` (which holds the newer ages'
+// strain and rate).
+template <typename R, bool HAS_R>
+__device__ __forceinline__ void wm_walk(const R *__restrict__ ring_s,
+                                        const R *__restrict__ ring_r, size_t np, uint32_t off,
+                                        int H, int p, int ka, int kb, const Decay<R> &dec,
+                                        WmSums &w)
+{
+    constexpr int G = 8;
+    R pa = R(0), pb = R(0);
+    walk_rows<R, G, 16, HAS_R, true>(
+        ring_s, ring_r, np, off, H, p, ka, kb,
+        [&](const Pack<R, 1>(&sv)[G], const Pack<R, 1>(&rv)[G], int k) {
+#pragma clang fp contract(off)
+#pragma unroll
+            for (int u = 0; u < G; ++u) {
+                const R s = sv[u].v[0];
+                w.T += (double)s;
+                w.R += (double)(HAS_R ? rv[u].v[0] : fabs(s));
+                const R x = s * wm_damping<R>(dec, R(k + u), w.R);
+                pa = pa + x;
+                pb = fused(x, R(2) * (R)w.T, pb);
+            }
+        },
+        [&]() {
+            w.A += (double)pa;
+            w.B += (double)pb;
+            pa = pb = R(0);
+            return true;
+        });
+}
+
+template <typename R, int SUB>
+__global__ __launch_bounds__(kBlock) void k_wm_far(char *__restrict__ ws,
+                                                   const ChanDev *__restrict__ chans,
+                                                   const NodeTile *__restrict__ tiles,
+                                                   const int64_t *__restrict__ tcount, int trel,
+                                                   int span, int blk)
+{
+    static_assert(SUB == 1 || SUB * kWave == kBlock, "one workgroup per split tile");
+    const NodeTile tl = tiles[SUB == 1 ? blockIdx.x : blockIdx.x / SUB];
+    const ChanDev *c = chans + tl.ch;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    const int lane = (int)(threadIdx.x % kWave);
+    const int n0 = tl.n0 + kWave * (SUB == 1 ? wave : (int)(blockIdx.x % SUB));
+    if (c->law != 1 || !c->far || n0 >= c->n)
+        return;
+    const int S = far_span(c, span);
+    if ((blk * kFarNearBlock) % S != 0)
+        return;
+    const int H = c->n_hist;
+    const size_t np = (size_t)c->np;
+    const int first = n0 + lane, node = min(first, c->n - 1);
+    const int p = (int)((*tcount + trel) % H);
+    const R *ring_s = reinterpret_cast<const R *>(ws + c->off_ring_s);
+    const R *ring_r = reinterpret_cast<const R *>(ws + c->off_ring_r);
+    const Decay<R> dec(c);
+    int ka = 1, kb = H - S;
+    if (SUB > 1) {
+        const int len = (kb - ka + 16 * SUB - 1) / (16 * SUB) * 16;
+        ka += wave * len;
+        kb = min(kb, ka + len);
+    }
+    const uint32_t off = (uint32_t)node * (uint32_t)sizeof(R);
+    WmSums w;
+    if (c->has_r)
+        wm_walk<R, true>(ring_s, ring_r, np, off, H, p, ka, kb, dec, w);
+    else
+        wm_walk<R, false>(ring_s, ring_r, np, off, H, p, ka, kb, dec, w);
+    if constexpr (SUB > 1) {
+        __shared__ double s_w[SUB][4][kWave];
+        s_w[wave][0][lane] = w.A;
+        s_w[wave][1][lane] = w.B;
+        s_w[wave][2][lane] = w.T;
+        s_w[wave][3][lane] = w.R;
+        __syncthreads();
+        if (wave != 0)
+            return;
+#pragma unroll
+        for (int i = 1; i < SUB; ++i)
+            w.append({s_w[i][0][lane], s_w[i][1][lane], s_w[i][2][lane], s_w[i][3][lane]},
+                     c->inv_gc);
+    }
+    if (first >= c->n)
+        return;
+    double *far = reinterpret_cast<double *>(ws + c->off_far) + node;
+    far[0] = w.A;
+    far[np] = w.B;
+    far[2 * np] = w.T;
+    far[3 * np] = w.R;
+}
+
+template <typename P, typename R, bool HAS_R>
+__device__ __forceinline__ void wm_near_node(char *__restrict__ ws, const ChanDev *c, int first,
+                                             int64_t t0, int S, int o)
+{
+#pragma clang fp contract(off)
+    constexpr int M = kFarNearBlock, G = 8;
+    const int H = c->n_hist;
+    const size_t np = (size_t)c->np;
+    const int node = min(first, c->n - 1);
+    const uint32_t off = (uint32_t)node * (uint32_t)sizeof(R);
+    const int p = (int)(t0 % H);
+    R *ring_s = reinterpret_cast<R *>(ws + c->off_ring_s);
+    R *ring_r = reinterpret_cast<R *>(ws + c->off_ring_r);
+    const Decay<R> dec(c);
+    // newest entry: gradient, push, age 0
+    R s0;
+    {
+        const P *vel = reinterpret_cast<const P *>(ws + c->off_vel);
+        const int y = node / c->lx, x = node - y * c->lx;
+        P kxx, kxy, kyx, kyy;
+        velocity_gradient<P>(vel, vel + np, c->lx, c->ly, x, y, kxx, kxy, kyx, kyy);
+        s0 = (R)kxy;
+        if (first < c->n) {
+            ring_s[(size_t)p * np + node] = s0;
+            if (HAS_R)
+                ring_r[(size_t)p * np + node] = (R)shear_rate<P>(kxx, kxy, kyx, kyy);
+        }
+    }
+    // entries pushed since the span's start, the far ages carried to this
+    // step, and the ages at the window's end that stay through the block
+    WmSums w;
+    wm_walk<R, HAS_R>(ring_s, ring_r, np, off, H, p, 1, 1 + o, dec, w);
+    {
+        const double *far = reinterpret_cast<const double *>(ws + c->off_far) + node;
+        const double d = exp(-c->inv_tau * (double)o);
+        WmSums f;
+        f.A = d * far[0];
+        f.B = d * far[np];
+        f.T = far[2 * np];
+        f.R = far[3 * np];
+        w.append(f, c->inv_gc);
+    }
+    wm_walk<R, HAS_R>(ring_s, ring_r, np, off, H, p, H - S + o, H - M, dec, w);
+    // per-step sums of the newest entry and of the ages that leave in the block
+    R A[M], B[M];
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+        A[m] = (m == 0 ? R(0.5) : R(1)) * s0;
+        B[m] = R(0);
+    }
+    walk_rows<R, G, 16, HAS_R, true>(
+        ring_s, ring_r, np, off, H, p, H - M, H,
+        [&](const Pack<R, 1>(&sv)[G], const Pack<R, 1>(&rv)[G], int k) {
+#pragma unroll
+            for (int u = 0; u < G; ++u) {
+                const R s = sv[u].v[0];
+                w.T += (double)s;
+                w.R += (double)(HAS_R ? rv[u].v[0] : fabs(s));
+                const R e = wm_damping<R>(dec, R(k + u), w.R);
+#pragma unroll
+                for (int m = 0; m < M; ++m) {
+                    const int a = k + u + m;
+                    if (a <= H - 1) {
+                        const R x = (a == H - 1 ? R(0.5) : R(1)) * s * e;
+                        A[m] = A[m] + x;
+                        B[m] = B[m] + x * R(2) * (R)w.T;
+                    }
+                }
+            }
+        },
+        [] { return true; });
+    if (first >= c->n)
+        return;
+    P *sig = reinterpret_cast<P *>(ws + c->off_sig);
+    double *blk = reinterpret_cast<double *>(ws + c->off_blk);
+    sig[node] = (P)(c->g_inf * (w.A + (double)A[0]));
+    sig[np + node] = (P)(c->g_inf * (w.B + (double)B[0]));
+#pragma unroll
+    for (int m = 1; m < M; ++m) {
+        blk[m * np + node] = w.A + (double)A[m];
+        blk[(kPlaneB + m) * np + node] = w.B + (double)B[m];
+    }
+}
+
+template <typename P, typename R>
+__global__ __launch_bounds__(kBlock) void k_wm_near(char *__restrict__ ws,
+                                                    const ChanDev *__restrict__ chans,
+                                                    const NodeTile *__restrict__ tiles,
+                                                    const int64_t *__restrict__ tcount, int trel,
+                                                    int span, int blk)
+{
+    const NodeTile tl = tiles[xcd_tile((int)blockIdx.x, (int)gridDim.x)];
+    const ChanDev *c = chans + tl.ch;
+    if (c->law != 1 || !c->far || tl.n0 + (int)(threadIdx.x & ~63u) >= c->n)
+        return;
+    const int S = far_span(c, span), o = (blk * kFarNearBlock) % S;
+    const int first = tl.n0 + (int)threadIdx.x;
+    if (c->has_r)
+        wm_near_node<P, R, true>(ws, c, first, *tcount + trel, S, o);
+    else
+        wm_near_node<P, R, false>(ws, c, first, *tcount + trel, S, o);
 }
 
 // In-block step m of an accumulated-strain channel (called from k_hist_step).
@@ -3473,12 +3695,12 @@ int finger_pass_blocks_per_cu(int prec, int block)
 }
 
 void launch_wm_pass(int prec, int block, char *ws, const ChanDev *chans, const HistTile *tiles,
-                    int n_tiles, const int64_t *tcount, int trel, hipStream_t st)
+                    int n_tiles, const int64_t *tcount, int trel, bool far, hipStream_t st)
 {
     if (n_tiles <= 0)
         return;
 #define LBMAX_WM(MM) hipLaunchKernelGGL((k_wm_pass<P, H, MM>), dim3(n_tiles), dim3(kBlock), 0, \
-                                        st, ws, chans, tiles, tcount, trel)
+                                        st, ws, chans, tiles, tcount, trel, far ? 1 : 0)
 #define LBMAX_WM_SHAPES                                                          \
     do {                                                                         \
         if (block == 1)                                                          \
@@ -3497,6 +3719,22 @@ void launch_wm_pass(int prec, int block, char *ws, const ChanDev *chans, const H
     LBMAX_BY_PREC(prec, LBMAX_WM_SHAPES);
 #undef LBMAX_WM_SHAPES
 #undef LBMAX_WM
+}
+
+void launch_wm_span(int prec, bool split, char *ws, const ChanDev *chans, const NodeTile *tiles,
+                    int n_tiles, const int64_t *tcount, int trel, int span, int blk, bool far,
+                    hipStream_t st)
+{
+    constexpr int kSub = kBlock / kWave;
+    if (far && split)
+        LBMAX_BY_HIST(prec, hipLaunchKernelGGL((k_wm_far<H, kSub>), dim3(n_tiles * kSub),
+                                               dim3(kBlock), 0, st, ws, chans, tiles, tcount,
+                                               trel, span, blk));
+    else if (far)
+        LBMAX_BY_HIST(prec, hipLaunchKernelGGL((k_wm_far<H, 1>), dim3(n_tiles), dim3(kBlock), 0,
+                                               st, ws, chans, tiles, tcount, trel, span, blk));
+    LBMAX_BY_PREC(prec, hipLaunchKernelGGL((k_wm_near<P, H>), dim3(n_tiles), dim3(kBlock), 0, st,
+                                           ws, chans, tiles, tcount, trel, span, blk));
 }
 
 void launch_inst_step(int prec, char *ws, const ChanDev *chans, const NodeTile *tiles,

@@ -204,9 +204,10 @@ int prec_code(lb_precision prec) { return prec == LB_F64 ? 0 : (prec == LB_F32 ?
 // the general pass.)
 int far_span_for(const ChanDev &c)
 {
-    if (c.qb > 0 || c.law != 0 || c.finger || c.n_hist > (1 << 22))
+    if (c.qb > 0 || c.law == 2 || c.finger || c.n_hist > (1 << 22))
         return 0;
-    const double spread = 4.0 * 0.04 / c.ly * c.inv_gc;
+    // accumulated-strain damping factorises over time: no rates to bound
+    const double spread = c.law == 1 ? 0.0 : 4.0 * 0.04 / c.ly * c.inv_gc;
     for (int S = kFarMaxSteps; S >= kFarNearBlock; S /= 2)
         if (c.n_hist >= kFarMinWindow * S && spread <= kFarZ / (0.5 * (S - 1)))
             return S;
@@ -309,7 +310,9 @@ Plan make_plan(const lb_channel_desc *ch, int32_t n_ch, lb_precision prec)
         // or the other), or their own where the window has a single chunk;
         // then their strain and the markers that tell which
         const size_t far_planes =
-            c.far ? std::max(part_planes, 2 * (size_t)far_terms(prec_code(prec))) + 2 : 0;
+            !c.far ? 0
+                   : (c.law == 1 ? 4  // A, B, strain, accumulated rate
+                                 : std::max(part_planes, 2 * (size_t)far_terms(prec_code(prec))) + 2);
         c.off_far = c.off_part;
         c.far_t = c.far ? (int)far_planes - 2 : 0;
         off = align_up(off + std::max(part_planes, far_planes) * c.max_chunks * c.np *
@@ -369,6 +372,7 @@ struct lb_handle {
     // accumulated-strain damping
     int hist_group_begin[5] = {0, 0, 0, 0, 0}, hist_group_count[5] = {0, 0, 0, 0, 0};
     bool any_finger = false, any_wm = false, any_inst = false;
+    bool any_wm_short = false;  // an accumulated-strain channel without far sums
     bool any_chunked = false;
     bool any_grid = false, any_window = false;  // channels on the grid / the uniform window
     bool fuse_ok = false;      // every channel fits the fused in-block steps
@@ -475,7 +479,7 @@ void build_tiles(lb_handle *h)
     h->any_chunked = false;
     h->adjoint_kind = true;
     int wide_tiles = 0, far_waves = 0, far_rows = 0;
-    h->any_grid = h->any_window = h->any_inst = false;
+    h->any_grid = h->any_window = h->any_inst = h->any_wm_short = false;
     for (int ci = 0; ci < h->n_ch; ++ci) {
         const ChanDev &c = h->plan.chans[ci];
         for (int n0 = 0; n0 < c.n; n0 += kBlock)
@@ -491,6 +495,10 @@ void build_tiles(lb_handle *h)
             continue;
         }
         h->any_window = true;
+        if (c.law == 1 && !c.far)
+            h->any_wm_short = true;
+        if (c.far)
+            wide_tiles += (c.n + kWave - 1) / kWave;
         if (c.nchunks > 1)
             h->any_chunked = true;
         const int span = (c.finger || c.law) ? kBlock : kWave * effective_vec(c.vec, h->block);
@@ -505,7 +513,6 @@ void build_tiles(lb_handle *h)
                     if (c.far) {
                         far_waves += 1;
                         far_rows = std::max(far_rows, k1 - k0);
-                        wide_tiles += k == 0 ? 1 : 0;
                     }
                 }
         }
@@ -665,14 +672,21 @@ const std::vector<double> &far_tables(int pc)
 void enqueue_pass(lb_handle *h, hipStream_t st, int trel, int block, FarBlock far)
 {
     static const int kVec[3] = {1, 2, 4};
-    if (far.span > 0) {
-        if ((far.index * kFarNearBlock) % std::min(far.span, h->plan.far_span_min) == 0)
+    // some channel's far span starts at this block
+    const bool far_start = far.span > 0 && (far.index * kFarNearBlock) %
+                                                   std::min(far.span, h->plan.far_span_min) ==
+                                               0;
+    if (far.span > 0 && h->n_far_tiles > 0) {
+        if (far_start)
             launch_far_pass(h->pc, h->far_sub, h->ws, h->d_chans, h->d_far_tiles,
                             h->n_far_tiles, h->d_tcount, trel, far.span, far.index, st);
         const int pgrid =
             h->persistent ? h->num_cus * hist_pass_blocks_per_cu(h->pc, 1, block) : 0;
         launch_hist_pass(h->pc, 1, block, h->ws, h->d_chans, h->d_far_tiles, h->n_far_tiles,
                          h->d_tcount, trel, pgrid, h->d_tile_counters, true, st);
+        launch_near_pass(h->pc, h->near_split, h->ws, h->d_chans, h->d_node_tiles,
+                         h->n_node_tiles, h->d_tcount, trel, far.span, far.index, h->d_far_tab,
+                         st);
     } else {
         for (int g = 0; g < 3; ++g) {
             const int pgrid =
@@ -682,9 +696,12 @@ void enqueue_pass(lb_handle *h, hipStream_t st, int trel, int block, FarBlock fa
                              h->d_tcount, trel, pgrid, h->d_tile_counters + g, false, st);
         }
     }
-    if (h->any_wm)
+    if (h->any_wm && (far.span == 0 || h->any_wm_short))
         launch_wm_pass(h->pc, block, h->ws, h->d_chans, h->d_hist_tiles + h->hist_group_begin[4],
-                       h->hist_group_count[4], h->d_tcount, trel, st);
+                       h->hist_group_count[4], h->d_tcount, trel, far.span > 0, st);
+    if (h->any_wm && far.span > 0)
+        launch_wm_span(h->pc, h->near_split, h->ws, h->d_chans, h->d_node_tiles,
+                       h->n_node_tiles, h->d_tcount, trel, far.span, far.index, far_start, st);
     if (h->any_finger) {
         const int pgrid =
             h->persistent ? h->num_cus * finger_pass_blocks_per_cu(h->pc, block) : 0;
@@ -692,10 +709,6 @@ void enqueue_pass(lb_handle *h, hipStream_t st, int trel, int block, FarBlock fa
                            h->d_hist_tiles + h->hist_group_begin[3], h->hist_group_count[3],
                            h->d_tcount, trel, pgrid, h->d_tile_counters + 3, st);
     }
-    if (far.span > 0)
-        launch_near_pass(h->pc, h->near_split, h->ws, h->d_chans, h->d_node_tiles,
-                         h->n_node_tiles, h->d_tcount, trel, far.span, far.index, h->d_far_tab,
-                         st);
     if (h->any_chunked && (far.span == 0 || h->any_finger))
         launch_combine(h->pc, block, h->ws, h->d_chans, h->d_node_tiles, h->n_node_tiles,
                        far.span > 0, st);

@@ -138,3 +138,19 @@ def test_resume_inside_a_span_is_bitwise(Solver):
         got = s.fields(0) + s.stress(0)
     for a, b in zip(want, got):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("lx,ly,n_hist", [(1, 40, 127), (1, 64, 128), (5, 13, 300), (3, 43, 700),
+                                          (65, 16, 515)])
+def test_strain_damping_spans(Solver, lx, ly, n_hist):
+    """Accumulated-strain damping: calls of many steps against single steps in
+    FP64 (1e-12), and the FP32 forms against the FP64 run (its tolerances)."""
+    ch = (twod(lx, ly, n_hist) if lx > 1 else uni(ly, n_hist)).replace(law="strain_damping")
+    calls = [200, 150, 8, 7, 31, 32, 33, 64, 100, 129]
+    print(f"case strain damping spans {lx}x{ly}, window {n_hist}", flush=True)
+    one = advance(Solver, [ch], "f64", [1] * sum(calls))[0]
+    for prec, block, fused, bound in (("f64", 1, 1, 1e-12), ("f64", 32, 0, 1e-12),
+                                      ("f32", 32, 1, 1e-4), ("f32p64", 8, 0, 1e-4)):
+        got = advance(Solver, [ch], prec, calls, block=block, fused=fused)[0]
+        for k, a, b in zip(("ux", "sxy", "n1"), got, one):
+            assert nerr(a, b) < bound, (prec, block, k, nerr(a, b))
