@@ -1,7 +1,8 @@
-// lbmax_checks.h -- host-side checks of readout values (plain C++, no HIP):
-// the finite check behind LB_ENONFINITE and the lattice Mach guard behind
-// LB_WARN_MACH.  Used by lbmax_runtime.hip; also compiled alone by the CPU
-// tests.
+// lbmax_checks.h -- checks of readout values (plain C++, no HIP): the finite
+// check behind LB_ENONFINITE and the lattice Mach guard behind LB_WARN_MACH.
+// lbmax_runtime.hip applies the guard to the largest speed that the readout
+// kernel found; the scans here say over host arrays what that kernel forms
+// (a NaN speed there counts as infinite).  Also compiled alone by the CPU tests.
 #pragma once
 
 #include <cmath>

@@ -203,10 +203,16 @@ int prepare_fused_lds(int prec);
 void launch_tick(int64_t *tcount, int64_t add, hipStream_t st);
 void launch_set_force(ChanDev *chans, int ch, double gx, double gy,
                       hipStream_t st);
-// Readouts into FP64 staging (nodes of one channel): which = 0 fields
-// (rho, ux, uy), 1 stress (sxy, n1), 2 gradient (kxx, kxy, kyx, kyy).
-void launch_readout(int prec, int which, char *ws, const ChanDev *chans,
-                    int ch, int n_nodes, double *stage, hipStream_t st);
+// Check values of one workgroup (kBlock nodes) of a readout.
+struct ReadoutCheck {
+    double max_speed;
+    int64_t nonfinite;
+};
+// Readout of nodes [n_lo, n_hi) of a channel as FP64 component planes of
+// n_hi - n_lo values into pinned host memory, with a check per workgroup: which
+// = 0 fields (rho, ux, uy), 1 stress (sxy, n1), 2 gradient (kxx, kxy, kyx, kyy).
+void launch_readout(int prec, int which, char *ws, const ChanDev *chans, int ch, int n_lo,
+                    int n_hi, double *out, ReadoutCheck *check, hipStream_t st);
 
 }  // namespace lbmax
 

@@ -14,6 +14,8 @@
 #include <cstring>
 #include <mutex>
 #include <string>
+#include <system_error>
+#include <thread>
 #include <vector>
 
 using namespace lbmax;
@@ -167,7 +169,7 @@ std::string check_desc(const lb_channel_desc *ch, int32_t n_ch, lb_precision pre
 }
 
 // Workspace plan: header | channel table | node tiles | history tiles |
-// readout staging | per-channel planes.  Everything 256-byte aligned.
+// u0 staging | per-channel planes.  Everything 256-byte aligned.
 struct Plan {
     size_t total = 0;
     size_t off_tcount = 0, off_chans = 0, off_node_tiles = 0, off_hist_tiles = 0,
@@ -261,7 +263,7 @@ Plan make_plan(const lb_channel_desc *ch, int32_t n_ch, lb_precision prec)
         // history tiles: at most one per wavefront of nodes and age chunk
         if (c.qb == 0 && c.law != 2)
             P.n_hist_tiles_max += ((c.n + kWave - 1) / kWave) * c.max_chunks;
-        stage = std::max(stage, (size_t)4 * c.n);
+        stage = std::max(stage, (size_t)2 * c.n);  // u0 on its way in
     }
     P.off_node_tiles = off;
     off = align_up(off + (size_t)P.n_node_tiles * sizeof(NodeTile), 256);
@@ -360,11 +362,13 @@ struct lb_handle {
     ChanDev *d_chans = nullptr;
     NodeTile *d_node_tiles = nullptr;
     HistTile *d_hist_tiles = nullptr;
-    HistTile *d_far_tiles = nullptr;    // the simple-shear channels' tiles of 64 nodes
+    HistTile *d_far_tiles = nullptr;    // the simple-shear channels' tiles of 64 nodes,
+                                        // where they are not a group of d_hist_tiles
     const double *d_far_tab = nullptr;  // expansion coefficients, one table per span
     double *d_stage = nullptr;
     int n_node_tiles = 0, n_hist_tiles = 0;
     int n_far_tiles = 0;
+    int far_list = 0;          // where they start in d_hist_tiles (-1: d_far_tiles)
     int far_sub = 1;           // wavefronts per far tile
     bool near_split = false;   // near pass with four wavefronts per 64 nodes
     bool adjoint_kind = false; // every channel is of the kind the adjoint covers
@@ -380,6 +384,9 @@ struct lb_handle {
     bool fuse_global_ok = false;  // ... and is narrow enough for the global-memory form to pay
     bool fuse_lds_ready = false;  // its dynamic LDS size is allowed
     int fuse_mode = 1;         // lb_set_fused
+    char *pin = nullptr;       // pinned readout buffer
+    size_t pin_nodes = 0;      // nodes one part of it holds
+    hipEvent_t pin_ev[2] = {nullptr, nullptr};
     // host mirrors kept alive for asynchronous uploads
     std::vector<NodeTile> node_tiles;
     std::vector<HistTile> hist_tiles, far_tiles;
@@ -507,14 +514,10 @@ void build_tiles(lb_handle *h)
             const int k1 = (int)((int64_t)c.n_hist * (k + 1) / c.nchunks);
             for (int n0 = 0; n0 < c.n; n0 += span)
                 h->hist_tiles.push_back({ci, n0, k0, k1, k, 0});
-            if (h->plan.far_span > 0 && c.law == 0 && !c.finger)
-                for (int n0 = 0; n0 < c.n; n0 += kWave) {
-                    h->far_tiles.push_back({ci, n0, k0, k1, k, 0});
-                    if (c.far) {
-                        far_waves += 1;
-                        far_rows = std::max(far_rows, k1 - k0);
-                    }
-                }
+            if (c.far && c.law == 0) {
+                far_waves += (c.n + kWave - 1) / kWave;
+                far_rows = std::max(far_rows, k1 - k0);
+            }
         }
     }
     // Group by lane width (one launch each), longest age range first inside
@@ -533,11 +536,6 @@ void build_tiles(lb_handle *h)
                              return group(a) < group(b);
                          return (a.k1 - a.k0) > (b.k1 - b.k0);
                      });
-    std::stable_sort(h->far_tiles.begin(), h->far_tiles.end(),
-                     [](const HistTile &a, const HistTile &b) {
-                         return (a.k1 - a.k0) > (b.k1 - b.k0);
-                     });
-    h->n_far_tiles = (int)h->far_tiles.size();
     // Far tiles are split while the launch stays within 16 wavefronts per
     // compute unit (4096) and a part keeps at least 32 rows.
     h->far_sub = 1;
@@ -554,6 +552,25 @@ void build_tiles(lb_handle *h)
     h->hist_group_begin[2] = h->hist_group_count[0] + h->hist_group_count[1];
     h->hist_group_begin[3] = h->hist_group_begin[2] + h->hist_group_count[2];
     h->hist_group_begin[4] = h->hist_group_begin[3] + h->hist_group_count[3];
+    // Tiles of 64 nodes of the simple-shear channels: group 0, or a list of
+    // its own where some channel's lanes are wider.
+    h->far_list = h->hist_group_begin[0];
+    h->n_far_tiles = h->plan.far_span > 0 ? h->hist_group_count[0] : 0;
+    if (h->plan.far_span > 0 && h->hist_group_count[1] + h->hist_group_count[2] > 0) {
+        for (int g = 0; g < 3; ++g)
+            for (int i = 0; i < h->hist_group_count[g]; ++i) {
+                HistTile tl = h->hist_tiles[h->hist_group_begin[g] + i];
+                const int n1 = std::min(tl.n0 + (kWave << g), h->plan.chans[tl.ch].n);
+                for (; tl.n0 < n1; tl.n0 += kWave)
+                    h->far_tiles.push_back(tl);
+            }
+        std::stable_sort(h->far_tiles.begin(), h->far_tiles.end(),
+                         [](const HistTile &a, const HistTile &b) {
+                             return (a.k1 - a.k0) > (b.k1 - b.k0);
+                         });
+        h->far_list = -1;
+        h->n_far_tiles = (int)h->far_tiles.size();
+    }
     h->any_finger = h->hist_group_count[3] > 0;
     h->any_wm = h->hist_group_count[4] > 0;
     h->n_node_tiles = (int)h->node_tiles.size();
@@ -677,12 +694,13 @@ void enqueue_pass(lb_handle *h, hipStream_t st, int trel, int block, FarBlock fa
                                                    std::min(far.span, h->plan.far_span_min) ==
                                                0;
     if (far.span > 0 && h->n_far_tiles > 0) {
+        const HistTile *tiles = h->far_list < 0 ? h->d_far_tiles : h->d_hist_tiles + h->far_list;
         if (far_start)
-            launch_far_pass(h->pc, h->far_sub, h->ws, h->d_chans, h->d_far_tiles,
-                            h->n_far_tiles, h->d_tcount, trel, far.span, far.index, st);
+            launch_far_pass(h->pc, h->far_sub, h->ws, h->d_chans, tiles, h->n_far_tiles,
+                            h->d_tcount, trel, far.span, far.index, st);
         const int pgrid =
             h->persistent ? h->num_cus * hist_pass_blocks_per_cu(h->pc, 1, block) : 0;
-        launch_hist_pass(h->pc, 1, block, h->ws, h->d_chans, h->d_far_tiles, h->n_far_tiles,
+        launch_hist_pass(h->pc, 1, block, h->ws, h->d_chans, tiles, h->n_far_tiles,
                          h->d_tcount, trel, pgrid, h->d_tile_counters, true, st);
         launch_near_pass(h->pc, h->near_split, h->ws, h->d_chans, h->d_node_tiles,
                          h->n_node_tiles, h->d_tcount, trel, far.span, far.index, h->d_far_tab,
@@ -883,6 +901,83 @@ lb_status capture_graph(lb_handle *h)
     return LB_OK;
 }
 
+// Pinned readout buffer: parts of at most this many bytes, four values a node
+// and a check per workgroup.
+constexpr size_t kPinPartMax = size_t(8) << 20;
+
+size_t pin_part_bytes(size_t nodes)
+{
+    return align_up(4 * nodes * sizeof(double) +
+                        (nodes + kBlock - 1) / kBlock * sizeof(ReadoutCheck),
+                    256);
+}
+
+// Pinned buffer for the handle's widest channel: one part where it fits, else
+// two.
+lb_status pin_alloc(lb_handle *h)
+{
+    size_t nodes = 0;
+    for (const ChanDev &c : h->plan.chans)
+        nodes = std::max(nodes, (size_t)c.n);
+    size_t parts = 1;
+    if (pin_part_bytes(nodes) > kPinPartMax) {
+        nodes = kPinPartMax / (4 * sizeof(double) + 1) / kBlock * kBlock;
+        parts = 2;
+        for (hipEvent_t &e : h->pin_ev)
+            HIP_TRY(h, hipEventCreateWithFlags(&e, hipEventDisableTiming));
+    }
+    h->pin_nodes = nodes;
+    void *p = nullptr;
+    HIP_TRY(h, hipHostMalloc(&p, parts * pin_part_bytes(nodes), hipHostMallocDefault));
+    h->pin = static_cast<char *>(p);
+    return LB_OK;
+}
+
+void pin_free(lb_handle *h)
+{
+    if (h->pin)
+        (void)hipHostFree(h->pin);
+    h->pin = nullptr;
+    for (hipEvent_t &e : h->pin_ev) {
+        if (e)
+            (void)hipEventDestroy(e);
+        e = nullptr;
+    }
+}
+
+// The component planes of `cnt` values at src to their places (from node lo) in
+// the caller's arrays.  Fresh pages of those arrays are what a large copy waits
+// for (21 MB: 1.4 ms by one thread, 0.5 ms by four), so it is shared by up to
+// four threads.
+void copy_out(const double *src, int cnt, int comps, double **outs, int lo)
+{
+    const auto part = [=](int i, int of) {
+        const size_t a = (size_t)cnt * i / of, b = (size_t)cnt * (i + 1) / of;
+        for (int q = 0; q < comps; ++q)
+            if (outs[q])
+                std::memcpy(outs[q] + lo + a, src + (size_t)q * cnt + a, (b - a) * sizeof(double));
+    };
+    constexpr int kThreads = 4;
+    constexpr size_t kShare = size_t(1) << 20;  // bytes from which the copy is shared
+    if ((size_t)cnt * comps * sizeof(double) < kShare) {
+        part(0, 1);
+        return;
+    }
+    std::thread th[kThreads - 1];
+    int started = 0;
+    try {
+        for (; started < kThreads - 1; ++started)
+            th[started] = std::thread(part, started + 1, kThreads);
+    } catch (const std::system_error &) {
+        // no more threads to be had: the parts left are copied here
+    }
+    part(0, kThreads);
+    for (int i = started + 1; i < kThreads; ++i)
+        part(i, kThreads);
+    for (int i = 0; i < started; ++i)
+        th[i].join();
+}
+
 lb_status readout(lb_handle *h, int32_t ch, int which, int comps,
                   double **outs)
 {
@@ -893,29 +988,55 @@ lb_status readout(lb_handle *h, int32_t ch, int which, int comps,
         return fail(LB_EINVAL, "channel index out of range");
     if (!h->has_out)
         return fail(LB_ESTATE, "no completed step to read");
+    // Chunks of nodes through the handle's pinned buffer: the GPU writes one
+    // part of it while the host copies the other out.
     const int N = h->plan.chans[ch].n;
-    launch_readout(h->pc, which, h->ws, h->d_chans, ch, N, h->d_stage, h->stream);
-    s = check_launch(h, "readout");
-    if (s != LB_OK)
-        return s;
-    std::vector<double> host((size_t)comps * N);
-    HIP_TRY(h, hipMemcpyAsync(host.data(), h->d_stage, host.size() * sizeof(double),
-                              hipMemcpyDeviceToHost, h->stream));
-    HIP_TRY(h, hipStreamSynchronize(h->stream));
-    for (int k = 0; k < comps; ++k)
-        if (outs[k])
-            std::memcpy(outs[k], host.data() + (size_t)k * N, N * sizeof(double));
-    // velocity readout: the lattice Mach guard (both components, requested or not)
-    if (which == 0 && (h->checks & LB_CHECK_MACH) &&
-        mach_guard_trips(max_speed(host.data() + N, host.data() + 2 * (size_t)N, N)))
-        h->warnings |= LB_WARN_MACH;
-    if (h->checks & LB_CHECK_FINITE) {
-        const ValueScan v = scan_values(host.data(), host.size());
-        if (v.nonfinite)
-            return fail(LB_ENONFINITE, "readout of channel " + std::to_string(ch) + ": " +
-                                           std::to_string(v.nonfinite) +
-                                           " non-finite values (the run has diverged)");
+    const int step = (int)std::min<size_t>(N, h->pin_nodes);
+    const int parts = step < N ? 2 : 1;
+    double max_speed = 0.0;
+    int64_t nonfinite = 0;
+    const auto values = [&](int part) {
+        return reinterpret_cast<double *>(h->pin + (size_t)part * pin_part_bytes(h->pin_nodes));
+    };
+    const auto checks = [&](int part) {
+        return reinterpret_cast<ReadoutCheck *>(values(part) + 4 * h->pin_nodes);
+    };
+    const auto launch = [&](int lo, int part) -> lb_status {
+        launch_readout(h->pc, which, h->ws, h->d_chans, ch, lo, std::min(N, lo + step),
+                       values(part), checks(part), h->stream);
+        lb_status e = check_launch(h, "readout");
+        if (e == LB_OK && parts > 1)
+            HIP_TRY(h, hipEventRecord(h->pin_ev[part], h->stream));
+        return e;
+    };
+    s = launch(0, 0);
+    for (int lo = 0, part = 0; s == LB_OK && lo < N; lo += step, part ^= 1) {
+        if (lo + step < N)
+            s = launch(lo + step, part ^ 1);
+        if (s != LB_OK)
+            break;
+        if (parts > 1)
+            HIP_TRY(h, hipEventSynchronize(h->pin_ev[part]));
+        else
+            HIP_TRY(h, hipStreamSynchronize(h->stream));
+        const int cnt = std::min(N, lo + step) - lo;
+        copy_out(values(part), cnt, comps, outs, lo);
+        for (int b = 0; b < (cnt + kBlock - 1) / kBlock; ++b) {
+            max_speed = std::max(max_speed, checks(part)[b].max_speed);
+            nonfinite += checks(part)[b].nonfinite;
+        }
     }
+    if (s != LB_OK) {
+        (void)hipStreamSynchronize(h->stream);
+        return s;
+    }
+    // velocity readout: the lattice Mach guard (both components, requested or not)
+    if (which == 0 && (h->checks & LB_CHECK_MACH) && mach_guard_trips(max_speed))
+        h->warnings |= LB_WARN_MACH;
+    if ((h->checks & LB_CHECK_FINITE) && nonfinite)
+        return fail(LB_ENONFINITE, "readout of channel " + std::to_string(ch) + ": " +
+                                       std::to_string(nonfinite) +
+                                       " non-finite values (the run has diverged)");
     return LB_OK;
 }
 
@@ -1258,6 +1379,7 @@ lb_status lb_init(const lb_channel_desc *ch, int32_t n_ch, lb_precision prec, vo
     }
 
     auto bail = [&](lb_status s) {
+        pin_free(h);
         delete h;
         return s;
     };
@@ -1266,6 +1388,8 @@ lb_status lb_init(const lb_channel_desc *ch, int32_t n_ch, lb_precision prec, vo
     // the tables and initialise each channel.
     launch_fill_zero(h->ws, h->plan.total, h->stream);
     lb_status s = check_launch(h, "zero fill");
+    if (s == LB_OK)
+        s = pin_alloc(h);
     if (s != LB_OK)
         return bail(s);
     if (h->plan.far_span > 0) {
@@ -2017,6 +2141,7 @@ lb_status lb_destroy(lb_handle *h)
             (void)hipEventDestroy(h->adj_ev_sweep[b]);
     if (h->cap_stream)
         (void)hipStreamDestroy(h->cap_stream);
+    pin_free(h);
     for (int w = 0; w < 3; ++w)
         for (auto &pr : h->pending[w]) {
             h->free_events.push_back(pr.first);
