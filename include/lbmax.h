@@ -326,7 +326,8 @@ int32_t lb_get_block(const lb_handle *h);
  * the workgroup keeps the channel's populations (rebuilt in FP64 from the
  * split storage once per node and step), velocity and stress in LDS and the
  * history rows pushed since the pass in registers (the stencils then read no
- * global memory).  mode: 0
+ * global memory); handles with FP64 populations whose channels are of that
+ * kind and have at most 512 nodes run the same way in mode 1.  mode: 0
  * separate launches, 1 fused (the default: the LDS form where it applies,
  * else the global-memory form when every channel has at most 512 nodes;
  * wider, that form is slower than separate launches and the steps run
@@ -334,7 +335,7 @@ int32_t lb_get_block(const lb_handle *h);
  * Results are identical in every mode.
  * lb_get_fused returns 0 when the steps are not fused (mode 0, a channel
  * that does not qualify, or blocks of one step), 1 for the fused launch, 2
- * for its LDS form.  Takes effect at the next lb_step.  For lb_kernel_time a
+ * for the LDS form of LB_F32.  Takes effect at the next lb_step.  For lb_kernel_time a
  * fused launch counts as one in-block launch.
  */
 lb_status lb_set_fused(lb_handle *h, int32_t mode);

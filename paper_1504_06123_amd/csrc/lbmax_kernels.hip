@@ -317,11 +317,14 @@ __device__ __forceinline__ void lb_moments(const R (&d)[9], R &drho, R &jx, R &j
 // the half-force shift, BGK + forcing term.  Post-collision deviations in
 // `out`.
 template <typename R>
-__device__ __forceinline__ void lb_collide_body(const ChanDev *c, int n, const R (&d)[9],
-                                                const R *__restrict__ sg, size_t gs,
-                                                R (&out)[9], R &ux, R &uy, R &drho)
+__device__ __forceinline__ void lb_collide_body(const ChanDev *c, int lx, int n,
+                                                const R (&d)[9], const R *__restrict__ sg,
+                                                size_t gs, R (&out)[9], R &ux, R &uy, R &drho)
 {
-    const int lx = c->lx, ly = c->ly;
+    // Every fused product is written out: left to the compiler, the choice
+    // differs between the kernels that step the same node.
+#pragma clang fp contract(off)
+    const int ly = c->ly;
     const int y = n / lx, x = n - y * lx;
     const int xp = (x + 1 == lx) ? 0 : x + 1;
     const int xm = (x == 0) ? lx - 1 : x - 1;
@@ -335,19 +338,23 @@ __device__ __forceinline__ void lb_collide_body(const ChanDev *c, int n, const R
     // d/dy central with one-sided rows at the walls.
     const R *__restrict__ sxy = sg;
     const R *__restrict__ sxx = sg + gs;
+    // The stencil's nodes by selection, so that its loads go out together.
+    const bool first = y == 0, last = y == ly - 1;
+    const int i0 = first || last ? n : n + lx;
+    const int i1 = first ? n + lx : n - lx;
+    const int i2 = first ? n + 2 * lx : (last ? n - 2 * lx : n);
     auto ddy = [&](const R *__restrict__ f) {
-        if (y == 0)
-            return R(0.5) * (R(-3) * f[n] + R(4) * f[n + lx] - f[n + 2 * lx]);
-        if (y == ly - 1)
-            return R(0.5) * (R(3) * f[n] - R(4) * f[n - lx] + f[n - 2 * lx]);
-        return R(0.5) * (f[n + lx] - f[n - lx]);
+#pragma clang fp contract(off)
+        const R f0 = f[i0], f1 = f[i1], f2 = f[i2];
+        const R w = fma(R(-3), f0, R(4) * f1) - f2;
+        return R(0.5) * (first ? w : (last ? -w : f0 - f1));
     };
     R fx = R(0.5) * (sxx[row + xp] - sxx[row + xm]) + ddy(sxy);
     R fy = R(0.5) * (sxy[row + xp] - sxy[row + xm]);
     if (c->finger)
         fy += ddy(sg + 2 * gs);
-    fx += rho * (R)c->gx;
-    fy += rho * (R)c->gy;
+    fx = fma(rho, (R)c->gx, fx);
+    fy = fma(rho, (R)c->gy, fy);
 
     // Velocity with the half-force shift (Eq. hydrofields).
     ux = (jx + R(0.5) * fx) / rho;
@@ -358,16 +365,17 @@ __device__ __forceinline__ void lb_collide_body(const ChanDev *c, int n, const R
     // (the f^ex part of Eq. bodyforce), all in deviation form.
     const R om = (R)c->omega;
     const R pf = R(1) - R(0.5) * om;
-    const R uu = ux * ux + uy * uy;
-    const R uf = ux * fx + uy * fy;
+    const R uu = fma(ux, ux, uy * uy);
+    const R uf = fma(ux, fx, uy * fy);
 #pragma unroll
     for (int q = 0; q < 9; ++q) {
         const R cu = R(QX[q]) * ux + R(QY[q]) * uy;
         const R cf = R(QX[q]) * fx + R(QY[q]) * fy;
         const R w = qweight<R>(q);
-        const R deq = w * (drho + rho * (R(3) * cu + R(4.5) * cu * cu - R(1.5) * uu));
-        const R F = w * pf * (R(3) * (cf - uf) + R(9) * cu * cf);
-        out[q] = d[q] - om * (d[q] - deq) + F;
+        const R e = fma(R(-1.5), uu, fma(R(4.5) * cu, cu, R(3) * cu));
+        const R deq = w * fma(rho, e, drho);
+        const R F = fma(R(9) * cu, cf, R(3) * (cf - uf));
+        out[q] = fma(w * pf, F, fma(-om, d[q] - deq, d[q]));
     }
 }
 
@@ -498,7 +506,7 @@ __device__ __forceinline__ void lb_node(char *__restrict__ ws, const ChanDev *c,
         lb_moments<P>(d, drho0, jx, jy);
         lb_collide_paper<P>(ws, c, n, np, d, drho0, jx, jy, out, ux, uy, drho);
     } else {
-        lb_collide_body<P>(c, n, d, sig, np, out, ux, uy, drho);
+        lb_collide_body<P>(c, c->lx, n, d, sig, np, out, ux, uy, drho);
     }
     if constexpr (kSplit) {
         float r[9];
@@ -2807,47 +2815,6 @@ __global__ __launch_bounds__(kFuseThreads) void k_fused_steps(char *__restrict__
     }
 }
 
-// Steps m0 .. m0 + count - 1 of a block with the channel's lattice state in
-// the workgroup, for handles in split population storage whose channels all
-// take the simple-shear integral law with the body-force coupling on a
-// uniform window (and fit one workgroup).  LDS holds the post-collision
-// remainders, the moments (rho - 1, u) and the stress of the channel, so the
-// neighbours a stencil reads come from LDS; each thread keeps the history rows
-// of its node pushed since the pass in registers.  Every result still goes to
-// the workspace (remainders and moments of both parities, velocity, rho,
-// stress, ring rows) as the separate launches write it, and the arithmetic is
-// the same operations in the same order, so the results are identical.
-//
-// In-block history of one node at step t0 + m from the rows in registers
-// (entry j pushed at t0 + j, s_new this step's): the ring walk of
-// hist_step_node, ages a = 1..m in the same order.
-template <typename R, bool HAS_R>
-__device__ __forceinline__ void hist_regs(const ChanDev *c, const Decay<R> &dec, int m, R s_new,
-                                          const R (&hs)[kMaxBlock], const R (&hr)[kMaxBlock],
-                                          double &sxy_out, double &sxx_out, double &gam_out)
-{
-    const int H = c->n_hist;
-    double sxy = 0.5 * (double)s_new, sxx = 0.0, gam = 0.0;
-#pragma unroll
-    for (int j = kMaxBlock - 1; j >= 0; --j) {
-        if (j < m) {
-            const int a = m - j;
-            const R s = hs[j];
-            gam += (double)s;
-            if (a < m && a <= H - 1) {
-                const double w = (a == H - 1) ? 0.5 : 1.0;
-                const R r = HAS_R ? hr[j] : fabs(s);
-                const double se = w * (double)(s * decay_pow(R(a), decay_rate<R>(dec, r)));
-                sxy += se;
-                sxx += 2.0 * gam * se;
-            }
-        }
-    }
-    sxy_out = sxy;
-    sxx_out = sxx;
-    gam_out = gam;
-}
-
 // Remainders r_q = (float)(out_q - n^eq_q) of a collision, as
 // split_remainders forms them, and the populations a pull rebuilds from them,
 // n^eq_q + r_q (the same operations as pull_split_one, so bit for bit what a
@@ -2867,148 +2834,233 @@ __device__ __forceinline__ void split_and_rebuild(const P (&out)[9], P ux, P uy,
     }
 }
 
-// LDS of the span: the channel's pulled-from populations as FP64 deviations
-// rebuilt from split storage ([9][K]), its velocity ([2][K]) and stress
-// ([2][K]); pulls read them without arithmetic.
-template <typename P, typename R, bool HAS_R>
-__device__ __forceinline__ void fused_span_lds(char *__restrict__ ws, const ChanDev *c,
-                                               int64_t t0s, int m0, int count, P *s_full,
-                                               P *s_vel, P *s_sig)
+// Steps m0 .. m0 + count - 1 of a block with the channel's lattice state in
+// the workgroup, for handles whose channels are all unidirectional (lx = 1,
+// |gamma_dot| = |s|), take the simple-shear integral law with the body-force
+// coupling on a uniform window, and fit one workgroup of NT threads, a thread
+// per node.  LDS holds the post-collision deviations n*_q - a_q of the channel
+// (split storage: rebuilt once per node and step), its velocity and its stress,
+// so that stencils read no global memory; each thread keeps the history entries
+// of its node pushed since the pass in registers, the newest first, so that
+// every entry's age is a constant of the unrolled sums.  The workspace gets the
+// state of the span's last step and all ring rows at the end.  Same operations
+// in the same order as k_lb and k_hist_step: results are identical.
+//
+// One workgroup is one compute unit with a wavefront or a few per SIMD, so a
+// step is a chain of latencies: channel constants are read once, a stencil's
+// loads go out together, the block sums of a step are loaded a step ahead,
+// nothing is stored to memory inside the loop, and up to 512 nodes the
+// populations alternate between two LDS buffers, which saves a barrier.
+// Measured for 31 steps: 64 us at 1 x 256 nodes in split storage (86 us with
+// 1024 threads, a scalar load and a 64-bit division per step and branches
+// around the stencil's loads), 98 us at 32 nodes in FP64 (231 us by
+// k_fused_steps, whose stencils read global memory).
+
+// Pull-stream of node n of a 1 x ly channel from LDS planes of stride K.
+template <typename P>
+__device__ __forceinline__ void lb_pull_column(int ly, int n, const P *src, int K, P (&d)[9])
 {
-    constexpr int K = kFuseThreads;  // LDS plane stride
-    const int n = threadIdx.x;
-    const bool own = n < c->n;
-    const size_t np = (size_t)c->np;
-    const int H = c->n_hist;
-    const int64_t tb = t0s - m0;  // step of the block's pass
-    float *pop = reinterpret_cast<float *>(ws + c->off_pop);
-    P *mom = reinterpret_cast<P *>(ws + c->off_mom);
-    P *vel = reinterpret_cast<P *>(ws + c->off_vel);
-    P *rhop = reinterpret_cast<P *>(ws + c->off_rho);
-    P *sig = reinterpret_cast<P *>(ws + c->off_sig);
-    R *ring_s = reinterpret_cast<R *>(ws + c->off_ring_s);
-    R *ring_r = reinterpret_cast<R *>(ws + c->off_ring_r);
-    const double *blk = reinterpret_cast<const double *>(ws + c->off_blk);
-    const Decay<R> dec(c);
-    // state of step t0s - 1, and the rows pushed since the pass
-    R hs[kMaxBlock], hr[kMaxBlock];
-    if (own) {
-        const float *src = pop + ((t0s + 1) & 1) * 9 * np;
-        const P *msrc = mom + ((t0s + 1) & 1) * 3 * np;
-        P full[9];
-        own_split<P>(n, src, msrc, np, full);
+    const bool lo = n > 0, hi = n < ly - 1;
+    const int dn = lo ? n - 1 : n, up = hi ? n + 1 : n;
+    d[0] = src[n];
+    d[1] = src[K + n];
+    d[2] = src[2 * K + n];
+    d[3] = src[(lo ? 3 : 4) * K + dn];
+    d[4] = src[(hi ? 4 : 3) * K + up];
+    d[5] = src[(lo ? 5 : 6) * K + dn];
+    d[6] = src[(hi ? 6 : 5) * K + up];
+    d[7] = src[(hi ? 7 : 8) * K + up];
+    d[8] = src[(lo ? 8 : 7) * K + dn];
+}
+
+// Shear rate of node n of a 1 x ly channel (as velocity_gradient).
+template <typename P>
+__device__ __forceinline__ P column_shear(int ly, int n, const P *ux)
+{
+    const bool first = n == 0, last = n == ly - 1;
+    const P u0 = ux[first || last ? n : n + 1], u1 = ux[first ? n + 1 : n - 1];
+    if (first)
+        return u0 + u1 / P(3);
+    if (last)
+        return -u0 - u1 / P(3);
+    return P(0.5) * (u0 - u1);
+}
+
+// In-block history of one node at step t0 + m: the walk of hist_step_node over
+// the entries of ages 1 .. m, hs[a - 1] the one of age a < m, s_pass the one of
+// age m (its strain only).  Entries past age m - 1 are zero and add nothing.
+template <typename R>
+__device__ __forceinline__ void hist_regs(int H, const Decay<R> &dec, int m, R s_new, R s_pass,
+                                          const R (&hs)[kMaxBlock - 1], double &sxy_out,
+                                          double &sxx_out, double &gam_out)
+{
+    constexpr int kGroup = 4;  // entries per uniform branch
+    double sxy = 0.5 * (double)s_new, sxx = 0.0, gam = 0.0;
 #pragma unroll
-        for (int q = 0; q < 9; ++q)
-            s_full[q * K + n] = full[q];
-        s_sig[n] = sig[n];
-        s_sig[K + n] = sig[np + n];
+    for (int a0 = 1; a0 < kMaxBlock; a0 += kGroup) {
+        if (a0 < m) {
 #pragma unroll
-        for (int j = 0; j < kMaxBlock; ++j) {
-            hs[j] = hr[j] = R(0);
-            if (j < m0) {
-                const size_t o = (size_t)((tb + j) % H) * np + n;
-                hs[j] = ring_s[o];
-                if (HAS_R)
-                    hr[j] = ring_r[o];
+            for (int a = a0; a < a0 + kGroup && a < kMaxBlock; ++a) {
+                const R s = hs[a - 1];
+                gam += (double)s;
+                const double w = a < H - 1 ? 1.0 : (a == H - 1 ? 0.5 : 0.0);
+                const double se = w * (double)(s * decay_pow(R(a), decay_rate<R>(dec, fabs(s))));
+                sxy += se;
+                sxx += 2.0 * gam * se;
             }
         }
+    }
+    sxy_out = sxy;
+    sxx_out = sxx;
+    gam_out = gam + (double)s_pass;
+}
+
+template <int NT>
+constexpr int kFusePlanes = NT <= 512 ? 21 : 12;  // populations (two buffers), u_x, two stresses
+
+template <typename R, typename S, int NT>
+__global__ __launch_bounds__(NT) void k_fused_column(char *__restrict__ ws,
+                                                     const ChanDev *__restrict__ chans,
+                                                     const int64_t *__restrict__ tcount,
+                                                     int trel, int m0, int count)
+{
+    typedef double P;
+    constexpr bool kSplit = sizeof(S) < sizeof(P);
+    constexpr bool kTwo = NT <= 512;
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    P *s_pop = reinterpret_cast<P *>(lds_raw);
+    P *s_next = kTwo ? s_pop + 9 * NT : s_pop;
+    P *s_vel = s_pop + (kTwo ? 18 : 9) * NT;
+    P *s_sig = s_vel + NT;  // [2][NT]
+    const ChanDev c = chans[blockIdx.x];
+    const int64_t t0s = *tcount + trel;
+    const int n = threadIdx.x;
+    const int ly = c.ly, H = c.n_hist;
+    const bool own = n < ly;
+    const size_t np = (size_t)c.np;
+    S *pop = reinterpret_cast<S *>(ws + c.off_pop);
+    P *mom = reinterpret_cast<P *>(ws + c.off_mom);  // split storage only
+    P *sig = reinterpret_cast<P *>(ws + c.off_sig);
+    R *ring = reinterpret_cast<R *>(ws + c.off_ring_s);
+    const double *blk = reinterpret_cast<const double *>(ws + c.off_blk);
+    const Decay<R> dec(&c);
+    const int p0 = (int)((t0s - m0) % H);  // ring slot of the block's pass
+    const auto row = [&](int j) { return ring + (size_t)((p0 + j) % H) * np + n; };
+    // state of step t0s - 1, and the entries pushed since the pass
+    R hs[kMaxBlock - 1], s_pass = R(0);
+#pragma unroll
+    for (int a = 1; a < kMaxBlock; ++a)
+        hs[a - 1] = R(0);
+    double A1 = 0.0, B1 = 0.0;
+    if (own) {
+        const S *src = pop + ((t0s + 1) & 1) * 9 * np;
+        P d[9];
+        if constexpr (kSplit) {
+            own_split<P>(n, src, mom + ((t0s + 1) & 1) * 3 * np, np, d);
+        } else {
+#pragma unroll
+            for (int q = 0; q < 9; ++q)
+                d[q] = src[q * np + n];
+        }
+#pragma unroll
+        for (int q = 0; q < 9; ++q)
+            s_pop[q * NT + n] = d[q];
+        s_sig[n] = sig[n];
+        s_sig[NT + n] = sig[np + n];
+        // the step before the span's first sees ages 1 .. m0 - 1 after a shift
+        s_pass = *row(0);
+#pragma unroll
+        for (int a = 1; a < kMaxBlock; ++a)
+            if (a < m0)
+                hs[a - 1] = *row(m0 - a);
+        A1 = blk[m0 * np + n];
+        B1 = blk[(kPlaneB + m0) * np + n];
     }
     __syncthreads();
     for (int k = 0; k < count; ++k) {
         const int64_t t = t0s + k;
         const int m = m0 + k;
-        double A = 0.0, B = 0.0;
-        P full[9];
-        P ux = P(0), uy = P(0);
+        const double A = A1, B = B1;
+        P out[9], ux = P(0), uy = P(0), drho = P(0);
+        float r[9];
         if (own) {
-            A = blk[m * np + n];  // issued before the lattice phase
-            B = blk[(kPlaneB + m) * np + n];
-            if (c->rec) {
-                P *rec = reinterpret_cast<P *>(c->rec) + (size_t)(t - c->rec_t0) * 10 * np;
+            const int mn = min(m + 1, m0 + count - 1);
+            A1 = blk[mn * np + n];
+            B1 = blk[(kPlaneB + mn) * np + n];
+            if (c.rec) {
+                P *rec = reinterpret_cast<P *>(c.rec) + (size_t)(t - c.rec_t0) * 10 * np;
 #pragma unroll
                 for (int q = 0; q < 9; ++q)
-                    rec[q * np + n] = s_full[q * K + n];
+                    rec[q * np + n] = s_pop[q * NT + n];
                 rec[9 * np + n] = s_sig[n];
             }
-            P d[9], out[9], drho;
-            lb_pull<P>(c, n, s_full, K, d);
-            lb_collide_body<P>(c, n, d, s_sig, K, out, ux, uy, drho);
-            float r[9];
-            split_and_rebuild<P>(out, ux, uy, drho, r, full);
-            // The workspace state of the span's last step (nothing here is read
-            // in the span, and the next step reads only the last one); every
-            // step's while the lattice inputs are being recorded.
-            if (k == count - 1 || c->rec) {
-                float *dst = pop + (t & 1) * 9 * np;
-                P *mdst = mom + (t & 1) * 3 * np;
+            P d[9];
+            lb_pull_column<P>(ly, n, s_pop, NT, d);
+            lb_collide_body<P>(&c, 1, n, d, s_sig, NT, out, ux, uy, drho);
+        }
+        if (!kTwo)
+            __syncthreads();  // every stencil read of the old state is done
+        if (own) {
+            if constexpr (kSplit) {
+                P full[9];
+                split_and_rebuild<P>(out, ux, uy, drho, r, full);
 #pragma unroll
                 for (int q = 0; q < 9; ++q)
-                    dst[q * np + n] = r[q];
-                mdst[n] = drho;
-                mdst[np + n] = ux;
-                mdst[2 * np + n] = uy;
+                    s_next[q * NT + n] = full[q];
+            } else {
+#pragma unroll
+                for (int q = 0; q < 9; ++q)
+                    s_next[q * NT + n] = out[q];
+            }
+            s_vel[n] = ux;
+        }
+        __syncthreads();  // this step's velocities are in LDS, the old stress has been read
+        if (own) {
+            const R s_new = (R)column_shear<P>(ly, n, s_vel);
+            double sxy, sxx, gam;
+            hist_regs<R>(H, dec, m, s_new, s_pass, hs, sxy, sxx, gam);
+#pragma unroll
+            for (int a = kMaxBlock - 1; a > 1; --a)
+                hs[a - 1] = hs[a - 2];
+            hs[0] = s_new;
+            const P sxy_p = (P)(c.g_inf * (A + sxy));
+            const P sxx_p = (P)(c.g_inf * (B + 2.0 * gam * A + sxx));
+            s_sig[n] = sxy_p;
+            s_sig[NT + n] = sxx_p;
+            if (k == count - 1) {
+                // nothing here is read in the span
+                S *dst = pop + (t & 1) * 9 * np;
+#pragma unroll
+                for (int q = 0; q < 9; ++q)
+                    dst[q * np + n] = kSplit ? (S)r[q] : (S)out[q];
+                if constexpr (kSplit) {
+                    P *mdst = mom + (t & 1) * 3 * np;
+                    mdst[n] = drho;
+                    mdst[np + n] = ux;
+                    mdst[2 * np + n] = uy;
+                }
+                P *vel = reinterpret_cast<P *>(ws + c.off_vel);
                 vel[n] = ux;
                 vel[np + n] = uy;
-                rhop[n] = drho;
-            }
-        }
-        __syncthreads();  // every stencil read of the old state and stress is done
-        if (own) {
-#pragma unroll
-            for (int q = 0; q < 9; ++q)
-                s_full[q * K + n] = full[q];
-            s_vel[n] = ux;
-            s_vel[K + n] = uy;
-        }
-        __syncthreads();  // this step's velocities are in LDS
-        if (own) {
-            const int y = n / c->lx, x = n - y * c->lx;
-            P kxx, kxy, kyx, kyy;
-            velocity_gradient<P>(s_vel, s_vel + K, c->lx, c->ly, x, y, kxx, kxy, kyx, kyy);
-            const R s_new = (R)kxy;
-            const size_t o = (size_t)(t % H) * np + n;
-            ring_s[o] = s_new;
-            R r_new = R(0);
-            if (HAS_R) {
-                r_new = (R)shear_rate<P>(kxx, kxy, kyx, kyy);
-                ring_r[o] = r_new;
-            }
-            double sxy, sxx, gam;
-            hist_regs<R, HAS_R>(c, dec, m, s_new, hs, hr, sxy, sxx, gam);
-#pragma unroll
-            for (int j = 0; j < kMaxBlock; ++j)
-                if (j == m) {
-                    hs[j] = s_new;
-                    if (HAS_R)
-                        hr[j] = r_new;
-                }
-            const P sxy_p = (P)(c->g_inf * (A + sxy));
-            const P sxx_p = (P)(c->g_inf * (B + 2.0 * gam * A + sxx));
-            if (k == count - 1 || c->rec) {
+                reinterpret_cast<P *>(ws + c.off_rho)[n] = drho;
                 sig[n] = sxy_p;
                 sig[np + n] = sxx_p;
             }
-            s_sig[n] = sxy_p;
-            s_sig[K + n] = sxx_p;
         }
         __syncthreads();  // this step's stress is in LDS
+        if (kTwo) {
+            P *sw = s_pop;
+            s_pop = s_next;
+            s_next = sw;
+        }
     }
-}
-
-template <typename P, typename R>
-__global__ __launch_bounds__(kFuseThreads) void k_fused_steps_lds(
-    char *__restrict__ ws, const ChanDev *__restrict__ chans, const int64_t *__restrict__ tcount,
-    int trel, int m0, int count)
-{
-    extern __shared__ __align__(16) unsigned char lds_raw[];
-    P *s_full = reinterpret_cast<P *>(lds_raw);  // [9][kFuseThreads]
-    P *s_vel = s_full + 9 * kFuseThreads;        // [2][kFuseThreads]
-    P *s_sig = s_vel + 2 * kFuseThreads;         // [2][kFuseThreads]
-    const ChanDev *c = chans + blockIdx.x;
-    const int64_t t0s = *tcount + trel;
-    // unidirectional channels only (|gamma_dot| = |s|: one row per entry in
-    // registers); the host selects this form only then
-    fused_span_lds<P, R, false>(ws, c, t0s, m0, count, s_full, s_vel, s_sig);
+    // ring rows of the span's steps (a window shorter than the span: its last)
+    if (own) {
+#pragma unroll
+        for (int a = 1; a < kMaxBlock; ++a)
+            if (a <= count && a <= H)
+                *row(m0 + count - a) = hs[a - 1];
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -3793,36 +3845,47 @@ void launch_combine(int prec, int block, char *ws, const ChanDev *chans, const N
                                            st, ws, chans, tiles, far ? 1 : 0));
 }
 
-void launch_fused_steps(int prec, bool lds, char *ws, const ChanDev *chans, int n_ch,
-                        const int64_t *tcount, int trel, int m0, int count, hipStream_t st)
+void launch_fused_steps(int prec, bool column, int max_ly, char *ws, const ChanDev *chans,
+                        int n_ch, const int64_t *tcount, int trel, int m0, int count, hipStream_t st)
 {
     if (n_ch <= 0 || count <= 0)
         return;
-    if (!lds) {
+    if (!column) {
         LBMAX_BY_PREC(prec, hipLaunchKernelGGL((k_fused_steps<P, H, S>), dim3(n_ch),
                                                dim3(kFuseThreads), 0, st, ws, chans, tcount,
                                                trel, m0, count));
         return;
     }
-    if (prec == 1)
-        hipLaunchKernelGGL((k_fused_steps_lds<double, float>), dim3(n_ch), dim3(kFuseThreads),
-                           fused_lds_bytes(prec), st, ws, chans, tcount, trel, m0, count);
+#define LBMAX_COLUMN(NT)                                                                       \
+    LBMAX_BY_PREC(prec, hipLaunchKernelGGL((k_fused_column<H, S, NT>), dim3(n_ch), dim3(NT),   \
+                                           kFusePlanes<NT> * NT * sizeof(double), st, ws, chans, \
+                                           tcount, trel, m0, count))
+    if (max_ly <= 64)
+        LBMAX_COLUMN(64);
+    else if (max_ly <= 256)
+        LBMAX_COLUMN(256);
+    else if (max_ly <= 512)
+        LBMAX_COLUMN(512);
+    else if (prec == 1)
+        hipLaunchKernelGGL((k_fused_column<float, float, 1024>), dim3(n_ch), dim3(1024),
+                           kFusePlanes<1024> * 1024 * sizeof(double), st, ws, chans, tcount,
+                           trel, m0, count);
+#undef LBMAX_COLUMN
 }
 
-// Rebuilt populations, velocity and stress: 13 FP64 planes.
-size_t fused_lds_bytes(int prec)
+// Allow the column form's dynamic LDS (above the default 64 KiB).
+int prepare_fused_column(int prec)
 {
-    return prec == 1 ? (size_t)kFuseThreads * 13 * sizeof(double) : 0;
-}
-
-int prepare_fused_lds(int prec)
-{
-    // Split storage only: with FP64 populations the state would not fit
-    if (prec != 1)
-        return -1;
-    const hipError_t e =
-        hipFuncSetAttribute(reinterpret_cast<const void *>(&k_fused_steps_lds<double, float>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)fused_lds_bytes(prec));
+    hipError_t e = hipSuccess;
+    LBMAX_BY_PREC(prec, e = hipFuncSetAttribute(
+                            reinterpret_cast<const void *>(&k_fused_column<H, S, 512>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)(kFusePlanes<512> * 512 * sizeof(double))));
+    if (e == hipSuccess && prec == 1)
+        e = hipFuncSetAttribute(
+            reinterpret_cast<const void *>(&k_fused_column<float, float, 1024>),
+            hipFuncAttributeMaxDynamicSharedMemorySize,
+            (int)(kFusePlanes<1024> * 1024 * sizeof(double)));
     return e == hipSuccess ? 0 : -1;
 }
 

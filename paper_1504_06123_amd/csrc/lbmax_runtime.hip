@@ -380,9 +380,10 @@ struct lb_handle {
     bool any_chunked = false;
     bool any_grid = false, any_window = false;  // channels on the grid / the uniform window
     bool fuse_ok = false;      // every channel fits the fused in-block steps
-    bool fuse_lds_ok = false;  // ... and takes the LDS-resident form
+    bool fuse_column_ok = false;  // ... and takes the column form (state in LDS)
     bool fuse_global_ok = false;  // ... and is narrow enough for the global-memory form to pay
-    bool fuse_lds_ready = false;  // its dynamic LDS size is allowed
+    bool fuse_column_ready = false;  // its dynamic LDS size is allowed
+    int fuse_max_ly = 0;
     int fuse_mode = 1;         // lb_set_fused
     char *pin = nullptr;       // pinned readout buffer
     size_t pin_nodes = 0;      // nodes one part of it holds
@@ -576,18 +577,23 @@ void build_tiles(lb_handle *h)
     h->n_node_tiles = (int)h->node_tiles.size();
     h->n_hist_tiles = (int)h->hist_tiles.size();
     h->fuse_ok = !h->any_grid && !h->any_inst;
-    h->fuse_lds_ok = h->fuse_ok;
+    h->fuse_column_ok = h->fuse_ok;
     h->fuse_global_ok = h->fuse_ok;
+    h->fuse_max_ly = 0;
     for (const ChanDev &c : h->plan.chans) {
         if (c.n > kFuseMaxNodes)
-            h->fuse_ok = h->fuse_lds_ok = false;
+            h->fuse_ok = h->fuse_column_ok = false;
         if (c.n > kFuseGlobalMaxNodes)
             h->fuse_global_ok = false;
-        if (c.law != 0 || c.finger || c.coupling || c.has_r)
-            h->fuse_lds_ok = false;
+        // the column form: FP64 populations up to the width of the global-memory
+        // form, split storage up to a workgroup's
+        if (c.law != 0 || c.finger || c.coupling || c.has_r ||
+            (h->pc != 1 && c.n > kFuseGlobalMaxNodes))
+            h->fuse_column_ok = false;
+        h->fuse_max_ly = std::max(h->fuse_max_ly, c.ly);
     }
-    if (h->fuse_lds_ok && !h->fuse_lds_ready)
-        h->fuse_lds_ready = prepare_fused_lds(h->pc) == 0;
+    if (h->fuse_column_ok && !h->fuse_column_ready)
+        h->fuse_column_ready = prepare_fused_column(h->pc) == 0;
 }
 
 // Default launch shape: wide lanes for large channels, and enough age chunks
@@ -775,7 +781,7 @@ lb_status enqueue_step(lb_handle *h, hipStream_t st, int trel, int m, int block,
 }
 
 // The in-block steps run fused: mode 2 whenever the channels fit a
-// workgroup; mode 1 (the default) in the LDS form where it applies, else in
+// workgroup; mode 1 (the default) in the column form where it applies, else in
 // the global-memory form only up to kFuseGlobalMaxNodes nodes per channel.
 bool fused_in_effect(const lb_handle *h, int block)
 {
@@ -783,7 +789,7 @@ bool fused_in_effect(const lb_handle *h, int block)
         return false;
     if (h->fuse_mode == 2)
         return true;
-    return (h->fuse_lds_ok && h->fuse_lds_ready) || h->fuse_global_ok;
+    return (h->fuse_column_ok && h->fuse_column_ready) || h->fuse_global_ok;
 }
 
 // Enqueue up to `left` steps starting at position m of a block of `block`
@@ -803,8 +809,9 @@ lb_status enqueue_span(lb_handle *h, hipStream_t st, int trel, int m, int block,
             }
             HIP_TRY(h, hipEventRecord(e[0], st));
         }
-        const bool lds = h->fuse_mode == 1 && h->fuse_lds_ok && h->fuse_lds_ready;
-        launch_fused_steps(h->pc, lds, h->ws, h->d_chans, h->n_ch, h->d_tcount, trel, m, k, st);
+        const bool column = h->fuse_mode == 1 && h->fuse_column_ok && h->fuse_column_ready;
+        launch_fused_steps(h->pc, column, h->fuse_max_ly, h->ws, h->d_chans, h->n_ch,
+                           h->d_tcount, trel, m, k, st);
         if (timed) {
             HIP_TRY(h, hipEventRecord(e[1], st));
             h->pending[2].push_back({e[0], e[1]});
@@ -1787,7 +1794,8 @@ int32_t lb_get_fused(const lb_handle *h)
 {
     if (!h || !fused_in_effect(h, h->block))
         return 0;
-    return (h->fuse_mode == 1 && h->fuse_lds_ok && h->fuse_lds_ready) ? 2 : 1;
+    return (h->pc == 1 && h->fuse_mode == 1 && h->fuse_column_ok && h->fuse_column_ready) ? 2
+                                                                                         : 1;
 }
 
 lb_status lb_set_persistent(lb_handle *h, int32_t enable)
