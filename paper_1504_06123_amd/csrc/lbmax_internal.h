@@ -91,8 +91,8 @@ struct alignas(256) ChanDev {
     int64_t rec_t0;
     int64_t off_far;                // [2 terms][max_chunks][np] doubles: far sums
     int32_t far;                    // most steps of a far span (0: takes no far sums)
-    int32_t far_t;                  // plane of off_far with the far entries' strain;
-                                    // the next one holds the tiles' markers
+    int32_t far_mark;               // plane of off_far with the tiles' markers; before it
+                                    // the far entries' strain (full tensor: deformation)
 };
 static_assert(sizeof(ChanDev) == 256, "ChanDev layout");
 
@@ -121,11 +121,11 @@ void launch_init(int prec, char *ws, const ChanDev *chans, int ch,
                  hipStream_t st);
 void launch_fill_zero(void *p, size_t bytes, hipStream_t st);
 // The lattice kernel also zeroes the persistent-pass tile counters and, at the
-// first step of a channel's far span (block blk of a span of `span` steps; 0:
+// first step of a channel's far span (`at` steps into a span of `span` steps; 0:
 // none), its far tiles' markers.
 void launch_lb(int prec, char *ws, const ChanDev *chans, const NodeTile *tiles,
                int n_tiles, const int64_t *tcount, int trel, int *tile_counters,
-               int span, int blk, hipStream_t st);
+               int span, int at, hipStream_t st);
 // History pass (first step of a block of `block` steps) for the tiles of the
 // channels whose lane width is `vec`.  persistent_grid > 0 launches that many
 // persistent workgroups claiming tiles from *counter.  With `far` (32 steps
@@ -136,13 +136,13 @@ void launch_hist_pass(int prec, int vec, int block, char *ws, const ChanDev *cha
 int hist_pass_blocks_per_cu(int prec, int vec, int block);
 // Far sums.  A call-level span of `span` steps (32, 64 or 128) is cut into
 // blocks of 32 and, per channel, into spans of min(ChanDev::far, span) steps;
-// at block blk of it (first step *tcount + trel) the far pass runs for the
+// `at` steps into it (step *tcount + trel) the far pass runs for the
 // channels whose span starts there, each tile split over `sub` wavefronts (1, 4
 // or 8).
 void launch_far_pass(int prec, int sub, char *ws, const ChanDev *chans, const HistTile *tiles,
-                     int n_tiles, const int64_t *tcount, int trel, int span, int blk,
+                     int n_tiles, const int64_t *tcount, int trel, int span, int at,
                      hipStream_t st);
-// Near pass of block blk: sigma of the block's first step and the block sums
+// Near pass of the block that starts there: sigma of the block's first step and the block sums
 // of the rest, from the far sums, the entries pushed since the channel's span
 // began and the window's end.  Tiles whose far sums do not hold (and channels
 // without) are combined from the chunk partials of launch_hist_pass.  `tabs`:
@@ -150,32 +150,39 @@ void launch_far_pass(int prec, int sub, char *ws, const ChanDev *chans, const Hi
 // (fill_far_table).
 void launch_near_pass(int prec, bool split, char *ws, const ChanDev *chans,
                       const NodeTile *tiles, int n_tiles, const int64_t *tcount, int trel,
-                      int span, int blk, const double *tabs, hipStream_t st);
+                      int span, int at, const double *tabs, hipStream_t st);
 inline constexpr int far_class(int span) { return span >= 128 ? 2 : (span >= 64 ? 1 : 0); }
 // Coefficients d_p(m), m < span, p < far_terms(prec).
 void fill_far_table(int prec, int span, double *out);
 // Full-tensor pass for the tiles of the full-tensor channels (block <= 16).
 void launch_finger_pass(int prec, int block, char *ws, const ChanDev *chans,
                         const HistTile *tiles, int n_tiles, const int64_t *tcount, int trel,
-                        int persistent_grid, int *counter, hipStream_t st);
+                        int persistent_grid, int *counter, bool far, hipStream_t st);
+// Far and near passes of full-tensor channels (blocks of 16 steps); tiles whose
+// far sums do not hold take launch_finger_pass with `far` (16 steps per pass).
+void launch_finger_far(int prec, char *ws, const ChanDev *chans, const HistTile *tiles,
+                       int n_tiles, const int64_t *tcount, int trel, int span, int at,
+                       hipStream_t st);
+void launch_finger_near(int prec, char *ws, const ChanDev *chans, const NodeTile *tiles,
+                        int n_tiles, const int64_t *tcount, int trel, int span, int at,
+                        const double *tabs, hipStream_t st);
 int finger_pass_blocks_per_cu(int prec, int block);
 // Accumulated-strain damping: one pass per block, O(1) work per entry; with
 // `far`, of the channels that take no far sums.
 void launch_wm_pass(int prec, int block, char *ws, const ChanDev *chans, const HistTile *tiles,
                     int n_tiles, const int64_t *tcount, int trel, bool far, hipStream_t st);
-// Block blk of a span (as launch_far_pass and launch_near_pass) for these
+// A block of a span (as launch_far_pass and launch_near_pass) for these
 // channels: the far pass where `far` (some channel's span starts here), and
 // the near pass.
 void launch_wm_span(int prec, bool split, char *ws, const ChanDev *chans, const NodeTile *tiles,
-                    int n_tiles, const int64_t *tcount, int trel, int span, int blk, bool far,
+                    int n_tiles, const int64_t *tcount, int trel, int span, int at, bool far,
                     hipStream_t st);
 // Instantaneous law (Eq. inlM), every step, node-local (other channels return).
 void launch_inst_step(int prec, char *ws, const ChanDev *chans, const NodeTile *tiles,
                       int n_tiles, const int64_t *tcount, int trel, hipStream_t st);
-// FP64 combine of chunk partials into sigma and the block sums (far: of the
-// full-tensor channels; the near pass takes the others).
+// FP64 combine of chunk partials into sigma and the block sums.
 void launch_combine(int prec, int block, char *ws, const ChanDev *chans,
-                    const NodeTile *tiles, int n_tiles, bool far, hipStream_t st);
+                    const NodeTile *tiles, int n_tiles, hipStream_t st);
 // Step m (1 <= m < block) of a block: gradient, push, sigma from the block sums.
 void launch_hist_step(int prec, int m, char *ws, const ChanDev *chans,
                       const NodeTile *tiles, int n_tiles, const int64_t *tcount,

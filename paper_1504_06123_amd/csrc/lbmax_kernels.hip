@@ -373,9 +373,9 @@ __device__ __forceinline__ void lb_collide_body(const ChanDev *c, int lx, int n,
         const R cf = R(QX[q]) * fx + R(QY[q]) * fy;
         const R w = qweight<R>(q);
         const R e = fma(R(-1.5), uu, fma(R(4.5) * cu, cu, R(3) * cu));
-        const R deq = w * fma(rho, e, drho);
+        const R neq = fma(-w, fma(rho, e, drho), d[q]);  // d - d^eq
         const R F = fma(R(9) * cu, cf, R(3) * (cf - uf));
-        out[q] = fma(w * pf, F, fma(-om, d[q] - deq, d[q]));
+        out[q] = fma(w * pf, F, fma(-om, neq, d[q]));
     }
 }
 
@@ -549,7 +549,7 @@ __device__ __forceinline__ int xcd_tile(int b, int n)
 __device__ __forceinline__ double *far_marker(char *ws, const ChanDev *c, int n0)
 {
     return reinterpret_cast<double *>(ws + c->off_far) +
-           (size_t)(c->far_t + 1) * c->max_chunks * c->np + n0;
+           (size_t)c->far_mark * c->max_chunks * c->np + n0;
 }
 
 // Steps of channel c's spans inside a call-level span of `span` steps.
@@ -566,7 +566,7 @@ __global__ __launch_bounds__(kBlock, 5) void k_lb(char *__restrict__ ws,
                                                const NodeTile *__restrict__ tiles,
                                                const int64_t *__restrict__ tcount,
                                                int trel, int *__restrict__ tile_counters,
-                                               int span, int blk)
+                                               int span, int at)
 {
     const NodeTile tl = tiles[xcd_tile((int)blockIdx.x, (int)gridDim.x)];
     const ChanDev *c = chans + tl.ch;
@@ -579,7 +579,7 @@ __global__ __launch_bounds__(kBlock, 5) void k_lb(char *__restrict__ ws,
         return;
     // first step of a far span of this channel (span = 0: not a span's step)
     if (span && c->far && c->law == 0 && threadIdx.x % kWave == 0 &&
-        (blk * kFarNearBlock) % far_span(c, span) == 0)
+        at % far_span(c, span) == 0)
         *far_marker(ws, c, n) = 0.0;
     lb_node<P, S>(ws, c, n, *tcount + trel);
 }
@@ -1343,7 +1343,7 @@ __device__ __forceinline__ void far_tile(char *__restrict__ ws, const ChanDev *c
                 *far_marker(ws, c, tl.n0) = 1.0;
             return;
         }
-        far[c->far_t * fplane] = loc;
+        far[(c->far_mark - 1) * fplane] = loc;
 #pragma unroll
         for (int q = 0; q < P; ++q) {
             far[q * fplane] = A[q];
@@ -1377,7 +1377,7 @@ __device__ __forceinline__ void far_tile(char *__restrict__ ws, const ChanDev *c
             return;
         }
         if (w == 0 && first < c->n)
-            far[c->far_t * fplane] = T;
+            far[(c->far_mark - 1) * fplane] = T;
 #pragma unroll
         for (int q0 = 0; q0 < 2 * P; q0 += kRound) {
 #pragma unroll
@@ -1407,7 +1407,7 @@ __device__ __forceinline__ void far_tile(char *__restrict__ ws, const ChanDev *c
 template <typename R, int SUB>
 __global__ __launch_bounds__(SUB == 1 ? kBlock : SUB * kWave) void k_far_pass(
     char *__restrict__ ws, const ChanDev *__restrict__ chans, const HistTile *__restrict__ tiles,
-    int n_tiles, const int64_t *__restrict__ tcount, int trel, int span, int blk)
+    int n_tiles, const int64_t *__restrict__ tcount, int trel, int span, int at)
 {
     const int i = SUB == 1 ? (int)blockIdx.x * (kBlock / kWave) +
                                  __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave))
@@ -1419,7 +1419,7 @@ __global__ __launch_bounds__(SUB == 1 ? kBlock : SUB * kWave) void k_far_pass(
     if (!c->far)
         return;
     const int S = far_span(c, span);
-    if ((blk * kFarNearBlock) % S != 0)
+    if (at % S != 0)
         return;  // inside a span of this channel
     const int64_t t_s = *tcount + trel;
     if (c->has_r)
@@ -1472,7 +1472,7 @@ __device__ __forceinline__ void near_tile(char *__restrict__ ws, const ChanDev *
     double Tf = 0.0;
 #pragma unroll 8
     for (int k = 0; k < c->nchunks; ++k)
-        Tf += far[c->far_t * fplane + (size_t)k * np];
+        Tf += far[(c->far_mark - 1) * fplane + (size_t)k * np];
 
     R pa[MG][1], pb[MG][1];
 #pragma unroll
@@ -1550,7 +1550,7 @@ __device__ __forceinline__ void near_tile(char *__restrict__ ws, const ChanDev *
                 MA[q] += a;
                 MB[q] += fma(O, a, f[(T + q) * fplane]);
             }
-            O += f[c->far_t * fplane];
+            O += f[(c->far_mark - 1) * fplane];
         }
     } else {
         // terms mg, mg + 4, .. by this wavefront, the others' through LDS
@@ -1572,7 +1572,7 @@ __device__ __forceinline__ void near_tile(char *__restrict__ ws, const ChanDev *
                     ta[u][i] = f[q * fplane];
                     tb[u][i] = f[(T + q) * fplane];
                 }
-                tt[u] = f[c->far_t * fplane];
+                tt[u] = f[(c->far_mark - 1) * fplane];
             }
 #pragma unroll
             for (int u = 0; u < kAhead; ++u)
@@ -1642,7 +1642,7 @@ __device__ __forceinline__ void near_tile(char *__restrict__ ws, const ChanDev *
 template <typename P, typename R, int MG>
 __global__ __launch_bounds__(kBlock, (sizeof(R) == 4 ? 3 : 1)) void k_near_pass(
     char *__restrict__ ws, const ChanDev *__restrict__ chans, const NodeTile *__restrict__ tiles,
-    const int64_t *__restrict__ tcount, int trel, int span, int blk,
+    const int64_t *__restrict__ tcount, int trel, int span, int at,
     const double *__restrict__ tabs)
 {
     constexpr int kTerms = MG == kFarNearBlock ? 1 : 2 * kFarP<R> * kWave;
@@ -1660,7 +1660,7 @@ __global__ __launch_bounds__(kBlock, (sizeof(R) == 4 ? 3 : 1)) void k_near_pass(
         return;
     if (far_holds(ws, c, n0)) {
         const int64_t t0 = *tcount + trel;
-        const int S = far_span(c, span), o = (blk * kFarNearBlock) % S;
+        const int S = far_span(c, span), o = at % S;
         const double *tab = tabs + (size_t)far_class(S) * kFarMaxSteps * kFarP<R>;
         if (c->has_r)
             near_tile<P, R, MG, true>(ws, c, n0, mg, t0, S, o, tab, s_mom);
@@ -2087,11 +2087,12 @@ __global__ __launch_bounds__(kBlock) void k_finger_pass(char *__restrict__ ws,
                                                         const ChanDev *__restrict__ chans,
                                                         const HistTile *__restrict__ tiles,
                                                         const int64_t *__restrict__ tcount,
-                                                        int trel)
+                                                        int trel, int far)
 {
     const HistTile tl = tiles[blockIdx.x];
     const ChanDev *c = chans + tl.ch;
-    if (tl.n0 + (int)(threadIdx.x & ~63u) >= c->n)
+    const int n0 = tl.n0 + (int)(threadIdx.x & ~63u);
+    if (n0 >= c->n || (M == kMaxFingerBlock && far && far_holds(ws, c, n0)))
         return;
     finger_tile<P, R, M, U, F>(ws, c, tl, *tcount + trel);
 }
@@ -2100,7 +2101,7 @@ template <typename P, typename R, int M, int U, int F>
 __global__ __launch_bounds__(kBlock) void k_finger_pass_persistent(
     char *__restrict__ ws, const ChanDev *__restrict__ chans,
     const HistTile *__restrict__ tiles, int n_tiles, const int64_t *__restrict__ tcount,
-    int trel, int *__restrict__ counter)
+    int trel, int *__restrict__ counter, int far)
 {
     __shared__ int claimed;
     const int64_t t = *tcount + trel;
@@ -2114,8 +2115,327 @@ __global__ __launch_bounds__(kBlock) void k_finger_pass_persistent(
             break;
         const HistTile tl = tiles[i];
         const ChanDev *c = chans + tl.ch;
-        if (tl.n0 + (int)(threadIdx.x & ~63u) < c->n)
+        const int n0 = tl.n0 + (int)(threadIdx.x & ~63u);
+        if (n0 < c->n && !(M == kMaxFingerBlock && far && far_holds(ws, c, n0)))
             finger_tile<P, R, M, U, F>(ws, c, tl, t);
+    }
+}
+
+// Far sums of a full-tensor channel: the expansion of the simple-shear far
+// sums in the entries' rates, three sums (xx, xy, yy) per term, of the ages 1 ..
+// H - S - 1 with the deformations E(t_s, .) of the span's start, beside the
+// total deformation of those ages (four planes before the marker).  A step
+// after the span's start conjugates them with the deformation since, as the
+// in-block steps do.  Bound by the ring's bytes (8 planes: 500 x 251 nodes,
+// 2048 entries, 8.2 GB a reading, 1.5 ms by the general pass, every 16 steps),
+// which a span of 128 steps reads once, and a sixteenth of them per near pass.
+template <typename R>
+__device__ __forceinline__ FarRates<R> finger_far_rates(const char *__restrict__ ws,
+                                                        const ChanDev *c, int node, int64_t t_s,
+                                                        int S)
+{
+    const int H = c->n_hist;
+    const size_t np = (size_t)c->np, hplane = (size_t)H * np;
+    const int p = (int)(t_s % H);
+    const R *k = reinterpret_cast<const R *>(ws + c->off_ring_s) +
+                 (size_t)(p == 0 ? H - 1 : p - 1) * np + node;
+    return FarRates<R>(c, finger_rate<R>(k[0], k[hplane], k[2 * hplane], k[3 * hplane]), S);
+}
+
+template <typename R>
+__global__ __launch_bounds__(kBlock, (sizeof(R) == 4 ? 2 : 1)) void k_finger_far(
+    char *__restrict__ ws, const ChanDev *__restrict__ chans, const HistTile *__restrict__ tiles,
+    const int64_t *__restrict__ tcount, int trel, int span, int at)
+{
+#pragma clang fp contract(off)
+    constexpr int T = kFarP<R>, U = 4, F = 16;
+    const HistTile tl = tiles[blockIdx.x];
+    const ChanDev *c = chans + tl.ch;
+    const int n0 = tl.n0 + (int)(threadIdx.x & ~63u);
+    if (!c->far || n0 >= c->n)
+        return;
+    const int S = far_span(c, span);
+    if (at % S != 0)
+        return;
+    const int H = c->n_hist;
+    const int64_t t_s = *tcount + trel;
+    const size_t np = (size_t)c->np, hplane = (size_t)H * np;
+    const int first = tl.n0 + (int)threadIdx.x;
+    const int node = min(first, c->n - 1);  // shadow lanes past the end
+    const int p = (int)(t_s % H);
+    const R *ring = reinterpret_cast<const R *>(ws + c->off_ring_s);
+    const FarRates<R> fr = finger_far_rates<R>(ws, c, node, t_s, S);
+    double X[T] = {}, Y[T] = {}, Z[T] = {};
+    R px[T], py[T], pz[T];
+#pragma unroll
+    for (int q = 0; q < T; ++q)
+        px[q] = py[q] = pz[q] = R(0);
+    Mat2 E = {1.0, 0.0, 0.0, 1.0};
+    bool bad = false;
+    const auto sum_row = [&](const R (&v)[8], int k) {
+#pragma clang fp contract(off)
+        E = step_deformation(E, (double)v[4], (double)v[5], (double)v[6], (double)v[7]);
+        double pxx, pxy, pyy;
+        finger_term(E, (double)v[0], (double)v[1], (double)v[2], (double)v[3], pxx, pxy, pyy);
+        const R r = finger_rate<R>(v[0], v[1], v[2], v[3]);
+        const R u = fused(fr.cu, r, -fr.c0);
+        bad |= !(fabs(u) <= R(1));
+        R x = decay_pow(R(2 * k + S - 1), fused(fr.b, r, fr.a));
+        const R fx = (R)pxx, fy = (R)pxy, fz = (R)pyy;
+        // the leading sums, whose rounding every step of the span shares, in FP64
+        X[0] += (double)(x * fx);
+        Y[0] += (double)(x * fy);
+        Z[0] += (double)(x * fz);
+        x = x * u;
+#pragma unroll
+        for (int q = 1; q < T; ++q) {
+            px[q] = fused(x, fx, px[q]);
+            py[q] = fused(x, fy, py[q]);
+            pz[q] = fused(x, fz, pz[q]);
+            if (q + 1 < T)
+                x = x * u;
+        }
+    };
+    const auto flush_rows = [&]() {
+#pragma unroll
+        for (int q = 1; q < T; ++q) {
+            X[q] += (double)px[q];
+            Y[q] += (double)py[q];
+            Z[q] += (double)pz[q];
+            px[q] = py[q] = pz[q] = R(0);
+        }
+    };
+    int k = max(tl.k0, 1);
+    const int kend = min(tl.k1, H - S);
+    while (k < kend && !__any(bad)) {
+        int slot = p - k;
+        if (slot < 0)
+            slot += H;
+        const int run = min(kend - k, slot + 1);
+        int j = 0;
+        while (j + U <= run && !__any(bad)) {
+            const int end = min(j + F, run);
+            for (; j + U <= end; j += U) {
+                R v[U][8];
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int q = 0; q < 8; ++q)
+                        v[u][q] = ring[q * hplane + (size_t)(slot - j - u) * np + node];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    sum_row(v[u], k + j + u);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            flush_rows();
+        }
+        for (; j < run && !__any(bad); ++j) {
+            R v[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+                v[q] = ring[q * hplane + (size_t)(slot - j) * np + node];
+            sum_row(v, k + j);
+        }
+        flush_rows();
+        k += run;
+    }
+    if (__any(bad)) {
+        if (threadIdx.x % kWave == 0)
+            *far_marker(ws, c, n0) = 1.0;
+        return;
+    }
+    if (first >= c->n)
+        return;
+    double *far = reinterpret_cast<double *>(ws + c->off_far) + (size_t)tl.chunk * np + node;
+    const size_t fplane = (size_t)c->max_chunks * np;
+#pragma unroll
+    for (int q = 0; q < T; ++q) {
+        far[q * fplane] = X[q];
+        far[(T + q) * fplane] = Y[q];
+        far[(2 * T + q) * fplane] = Z[q];
+    }
+    double *def = far + (c->far_mark - 4) * fplane;
+    def[0] = E.a;
+    def[fplane] = E.b;
+    def[2 * fplane] = E.c;
+    def[3 * fplane] = E.d;
+}
+
+// Near pass of a block of 16 steps from t0 = t_s + o: as k_near_pass, with the
+// deformation carried through the entries pushed since the span's start, the
+// far ages and the window's end in place of the strain.
+template <typename P, typename R>
+__device__ __forceinline__ void finger_near_node(char *__restrict__ ws, const ChanDev *c,
+                                                 int first, int64_t t0, int S, int o,
+                                                 const double *__restrict__ tab)
+{
+#pragma clang fp contract(off)
+    constexpr int T = kFarP<R>, M = kMaxFingerBlock;
+    const int H = c->n_hist;
+    const size_t np = (size_t)c->np, hplane = (size_t)H * np;
+    const int node = min(first, c->n - 1);
+    const int p = (int)(t0 % H);
+    const R *ring = reinterpret_cast<const R *>(ws + c->off_ring_s);
+    const Decay<R> dec(c);
+    R px[M], py[M], pz[M];
+    Mat2 E = {1.0, 0.0, 0.0, 1.0};
+    {
+        // newest entry: age 0, E = I, P = kappa + kappa^T
+        P kxx = P(0), kxy = P(0), kyx = P(0), kyy = P(0);
+        if (first < c->n)
+            finger_push<P, R>(ws, c, node, p, kxx, kxy, kyx, kyy);
+        const R rate = decay_rate<R>(dec, finger_rate<R>((R)kxx, (R)kxy, (R)kyx, (R)kyy));
+        const R fx = R(2) * (R)kxx, fy = (R)((double)(R)kxy + (double)(R)kyx),
+                fz = R(2) * (R)kyy;
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
+            const R x = (m == 0 ? R(0.5) : R(1)) * decay_pow(R(m), rate);
+            px[m] = x * fx;
+            py[m] = x * fy;
+            pz[m] = x * fz;
+        }
+    }
+    // ages [k, kend); those that leave the window in the block with their
+    // weight of each step; partial sums of 16 rows (as the general pass's) into
+    // the totals
+    double sx[M] = {}, sy[M] = {}, sz[M] = {};
+    const auto flush_rows = [&]() {
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
+            sx[m] += (double)px[m];
+            sy[m] += (double)py[m];
+            sz[m] += (double)pz[m];
+            px[m] = py[m] = pz[m] = R(0);
+        }
+    };
+    const auto walk = [&](int k, int kend) {
+#pragma clang fp contract(off)
+        constexpr int U = 2;
+        for (int rows = 0; k < kend; k += U) {
+            if ((rows += U) > 16) {
+                flush_rows();
+                rows = U;
+            }
+            R v[U][8];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                int slot = p - min(k + u, kend - 1);
+                if (slot < 0)
+                    slot += H;
+#pragma unroll
+                for (int q = 0; q < 8; ++q)
+                    v[u][q] = ring[q * hplane + (size_t)slot * np + node];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int a0 = k + u;
+                if (a0 >= kend)
+                    break;
+                E = step_deformation(E, (double)v[u][4], (double)v[u][5], (double)v[u][6],
+                                     (double)v[u][7]);
+                double pxx, pxy, pyy;
+                finger_term(E, (double)v[u][0], (double)v[u][1], (double)v[u][2],
+                            (double)v[u][3], pxx, pxy, pyy);
+                const R rate = decay_rate<R>(
+                    dec, finger_rate<R>(v[u][0], v[u][1], v[u][2], v[u][3]));
+                R x = decay_pow(R(a0), rate);
+                const R q = decay_pow(R(1), rate);
+                const R fx = (R)pxx, fy = (R)pxy, fz = (R)pyy;
+#pragma unroll
+                for (int m = 0; m < M; ++m) {
+                    const int a = a0 + m;
+                    const R w = a < H - 1 ? x : (a == H - 1 ? R(0.5) * x : R(0));
+                    px[m] = fused(w, fx, px[m]);
+                    py[m] = fused(w, fy, py[m]);
+                    pz[m] = fused(w, fz, pz[m]);
+                    if (m + 1 < M)
+                        x = x * q;
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        flush_rows();
+    };
+    walk(1, 1 + o);
+    // the far ages: the chunks' deformations in turn
+    const Mat2 E0 = E;
+    const size_t fplane = (size_t)c->max_chunks * np;
+    const double *far = reinterpret_cast<const double *>(ws + c->off_far) + node;
+    for (int k = 0; k < c->nchunks; ++k) {
+        const double *d = far + (size_t)(c->far_mark - 4) * fplane + (size_t)k * np;
+        E = mat_mul(E, {d[0], d[fplane], d[2 * fplane], d[3 * fplane]});
+    }
+    walk(H - S + o, H);
+    if (first >= c->n)
+        return;
+    double X[T], Y[T], Z[T];
+#pragma unroll
+    for (int q = 0; q < T; ++q)
+        X[q] = Y[q] = Z[q] = 0.0;
+    Mat2 O = E0;
+    for (int k = 0; k < c->nchunks; ++k) {
+        const double *f = far + (size_t)k * np;
+#pragma unroll
+        for (int q = 0; q < T; ++q) {
+            double x = f[q * fplane], y = f[(T + q) * fplane], z = f[(2 * T + q) * fplane];
+            congruence(O, x, y, z);  // takes xx, xy, yy
+            X[q] += x;
+            Y[q] += y;
+            Z[q] += z;
+        }
+        const double *d = f + (size_t)(c->far_mark - 4) * fplane;
+        O = mat_mul(O, {d[0], d[fplane], d[2 * fplane], d[3 * fplane]});
+    }
+    const FarRates<R> fr = finger_far_rates<R>(ws, c, node, t0 - o, S);
+    const double rate0 = c->inv_tau + fr.rho0, mbar = 0.5 * (S - 1);
+    P *sig = reinterpret_cast<P *>(ws + c->off_sig);
+    double *blk = reinterpret_cast<double *>(ws + c->off_blk);
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+        const double *d = tab + (size_t)(o + m) * T;
+        double x = 0.0, y = 0.0, z = 0.0;
+#pragma unroll
+        for (int q = T - 1; q >= 0; --q) {
+            x = fma(d[q], X[q], x);
+            y = fma(d[q], Y[q], y);
+            z = fma(d[q], Z[q], z);
+        }
+        const double Fm = exp(-((double)(o + m) - mbar) * rate0);
+        x = fma(Fm, x, sx[m]);
+        y = fma(Fm, y, sy[m]);
+        z = fma(Fm, z, sz[m]);
+        if (m == 0) {
+            sig[node] = (P)(c->g_inf * y);
+            sig[np + node] = (P)(c->g_inf * x);
+            sig[2 * np + node] = (P)(c->g_inf * z);
+        } else {
+            blk[m * np + node] = x;
+            blk[(kMaxBlock + m) * np + node] = y;
+            blk[(2 * kMaxBlock + m) * np + node] = z;
+        }
+    }
+}
+
+template <typename P, typename R>
+__global__ __launch_bounds__(kBlock, (sizeof(R) == 4 ? 2 : 1)) void k_finger_near(
+    char *__restrict__ ws, const ChanDev *__restrict__ chans, const NodeTile *__restrict__ tiles,
+    const int64_t *__restrict__ tcount, int trel, int span, int at,
+    const double *__restrict__ tabs)
+{
+    const NodeTile tl = tiles[xcd_tile((int)blockIdx.x, (int)gridDim.x)];
+    const ChanDev *c = chans + tl.ch;
+    const int n0 = tl.n0 + (int)(threadIdx.x & ~63u);
+    const int first = tl.n0 + (int)threadIdx.x;
+    if (!c->finger || n0 >= c->n)
+        return;
+    if (far_holds(ws, c, n0)) {
+        const int S = far_span(c, span);
+        finger_near_node<P, R>(ws, c, first, *tcount + trel, S, at % S,
+                               tabs + (size_t)far_class(S) * kFarMaxSteps * kFarP<R>);
+    } else if (c->nchunks > 1 && first < c->n) {
+        for (int m = 0; m < kMaxFingerBlock; ++m)
+            combine_node<P>(ws, c, first, m);
     }
 }
 
@@ -2375,7 +2695,7 @@ __global__ __launch_bounds__(kBlock) void k_wm_far(char *__restrict__ ws,
                                                    const ChanDev *__restrict__ chans,
                                                    const NodeTile *__restrict__ tiles,
                                                    const int64_t *__restrict__ tcount, int trel,
-                                                   int span, int blk)
+                                                   int span, int at)
 {
     static_assert(SUB == 1 || SUB * kWave == kBlock, "one workgroup per split tile");
     const NodeTile tl = tiles[SUB == 1 ? blockIdx.x : blockIdx.x / SUB];
@@ -2386,7 +2706,7 @@ __global__ __launch_bounds__(kBlock) void k_wm_far(char *__restrict__ ws,
     if (c->law != 1 || !c->far || n0 >= c->n)
         return;
     const int S = far_span(c, span);
-    if ((blk * kFarNearBlock) % S != 0)
+    if (at % S != 0)
         return;
     const int H = c->n_hist;
     const size_t np = (size_t)c->np;
@@ -2519,13 +2839,13 @@ __global__ __launch_bounds__(kBlock) void k_wm_near(char *__restrict__ ws,
                                                     const ChanDev *__restrict__ chans,
                                                     const NodeTile *__restrict__ tiles,
                                                     const int64_t *__restrict__ tcount, int trel,
-                                                    int span, int blk)
+                                                    int span, int at)
 {
     const NodeTile tl = tiles[xcd_tile((int)blockIdx.x, (int)gridDim.x)];
     const ChanDev *c = chans + tl.ch;
     if (c->law != 1 || !c->far || tl.n0 + (int)(threadIdx.x & ~63u) >= c->n)
         return;
-    const int S = far_span(c, span), o = (blk * kFarNearBlock) % S;
+    const int S = far_span(c, span), o = at % S;
     const int first = tl.n0 + (int)threadIdx.x;
     if (c->has_r)
         wm_near_node<P, R, true>(ws, c, first, *tcount + trel, S, o);
@@ -2682,16 +3002,15 @@ __device__ __forceinline__ void combine_node(char *__restrict__ ws, const ChanDe
     }
 }
 
-// `far`: the near pass has combined the simple-shear channels.
 template <typename P>
 __global__ __launch_bounds__(kBlock) void k_combine(char *__restrict__ ws,
                                                     const ChanDev *__restrict__ chans,
-                                                    const NodeTile *__restrict__ tiles, int far)
+                                                    const NodeTile *__restrict__ tiles)
 {
     const NodeTile tl = tiles[blockIdx.x];
     const ChanDev *c = chans + tl.ch;
     const int n = tl.n0 + threadIdx.x;
-    if (c->nchunks == 1 || n >= c->n || (far && !c->finger))
+    if (c->nchunks == 1 || n >= c->n)
         return;
     combine_node<P>(ws, c, n, (int)blockIdx.y);
 }
@@ -3557,12 +3876,12 @@ void launch_fill_zero(void *p, size_t bytes, hipStream_t st)
 }
 
 void launch_lb(int prec, char *ws, const ChanDev *chans, const NodeTile *tiles, int n_tiles,
-               const int64_t *tcount, int trel, int *tile_counters, int span, int blk,
+               const int64_t *tcount, int trel, int *tile_counters, int span, int at,
                hipStream_t st)
 {
     LBMAX_BY_PREC(prec, hipLaunchKernelGGL((k_lb<P, S>), dim3(n_tiles), dim3(kBlock), 0, st, ws,
                                            chans, tiles, tcount, trel, tile_counters,
-                                           span, blk));
+                                           span, at));
 }
 
 // Shapes of the history pass: (nodes per lane V, steps per pass M, rows
@@ -3638,7 +3957,7 @@ void launch_hist_pass(int prec, int vec, int block, char *ws, const ChanDev *cha
     } while (0)
 
 void launch_far_pass(int prec, int sub, char *ws, const ChanDev *chans, const HistTile *tiles,
-                     int n_tiles, const int64_t *tcount, int trel, int span, int blk,
+                     int n_tiles, const int64_t *tcount, int trel, int span, int at,
                      hipStream_t st)
 {
     if (n_tiles <= 0)
@@ -3649,7 +3968,7 @@ void launch_far_pass(int prec, int sub, char *ws, const ChanDev *chans, const Hi
                                            dim3(SUB == 1 ? (n_tiles + per_group - 1) / per_group \
                                                          : n_tiles),                            \
                                            dim3(SUB == 1 ? kBlock : SUB * kWave), 0, st, ws,    \
-                                           chans, tiles, n_tiles, tcount, trel, span, blk))
+                                           chans, tiles, n_tiles, tcount, trel, span, at))
     if (sub >= 8)
         LBMAX_FAR(8);
     else if (sub >= 4)
@@ -3661,18 +3980,18 @@ void launch_far_pass(int prec, int sub, char *ws, const ChanDev *chans, const Hi
 
 void launch_near_pass(int prec, bool split, char *ws, const ChanDev *chans,
                       const NodeTile *tiles, int n_tiles, const int64_t *tcount, int trel,
-                      int span, int blk, const double *tabs, hipStream_t st)
+                      int span, int at, const double *tabs, hipStream_t st)
 {
     if (n_tiles <= 0)
         return;
     if (split)
         LBMAX_BY_PREC(prec, hipLaunchKernelGGL((k_near_pass<P, H, 8>),
                                                dim3(n_tiles * (kBlock / kWave)), dim3(kBlock), 0,
-                                               st, ws, chans, tiles, tcount, trel, span, blk, tabs));
+                                               st, ws, chans, tiles, tcount, trel, span, at, tabs));
     else
         LBMAX_BY_PREC(prec, hipLaunchKernelGGL((k_near_pass<P, H, kFarNearBlock>), dim3(n_tiles),
                                                dim3(kBlock), 0, st, ws, chans, tiles, tcount,
-                                               trel, span, blk, tabs));
+                                               trel, span, at, tabs));
 }
 
 // d_p(v): the Chebyshev interpolation of exp(-z u v) in u at P nodes, in powers
@@ -3747,7 +4066,7 @@ int hist_pass_blocks_per_cu(int prec, int vec, int block)
 
 void launch_finger_pass(int prec, int block, char *ws, const ChanDev *chans,
                         const HistTile *tiles, int n_tiles, const int64_t *tcount, int trel,
-                        int persistent_grid, int *counter, hipStream_t st)
+                        int persistent_grid, int *counter, bool far, hipStream_t st)
 {
     if (n_tiles <= 0)
         return;
@@ -3757,16 +4076,34 @@ void launch_finger_pass(int prec, int block, char *ws, const ChanDev *chans,
         if (persistent_grid > 0)                                                 \
             hipLaunchKernelGGL((k_finger_pass_persistent<P, H, M, U, F>), dim3(grid), \
                                dim3(kBlock), 0, st, ws, chans, tiles, n_tiles,   \
-                               tcount, trel, counter);                           \
+                               tcount, trel, counter, far ? 1 : 0);              \
         else                                                                     \
             hipLaunchKernelGGL((k_finger_pass<P, H, M, U, F>), dim3(grid),       \
                                dim3(kBlock), 0, st, ws, chans, tiles, tcount,    \
-                               trel);                                            \
+                               trel, far ? 1 : 0);                               \
     } while (0)
 #define LBMAX_FPASS_SHAPES LBMAX_FINGER_SHAPE_TABLE(block, LBMAX_FPASS)
     LBMAX_BY_PREC(prec, LBMAX_FPASS_SHAPES);
 #undef LBMAX_FPASS_SHAPES
 #undef LBMAX_FPASS
+}
+
+void launch_finger_far(int prec, char *ws, const ChanDev *chans, const HistTile *tiles,
+                       int n_tiles, const int64_t *tcount, int trel, int span, int at,
+                       hipStream_t st)
+{
+    if (n_tiles <= 0)
+        return;
+    LBMAX_BY_HIST(prec, hipLaunchKernelGGL((k_finger_far<H>), dim3(n_tiles), dim3(kBlock), 0, st,
+                                           ws, chans, tiles, tcount, trel, span, at));
+}
+
+void launch_finger_near(int prec, char *ws, const ChanDev *chans, const NodeTile *tiles,
+                        int n_tiles, const int64_t *tcount, int trel, int span, int at,
+                        const double *tabs, hipStream_t st)
+{
+    LBMAX_BY_PREC(prec, hipLaunchKernelGGL((k_finger_near<P, H>), dim3(n_tiles), dim3(kBlock), 0,
+                                           st, ws, chans, tiles, tcount, trel, span, at, tabs));
 }
 
 int finger_pass_blocks_per_cu(int prec, int block)
@@ -3814,19 +4151,19 @@ void launch_wm_pass(int prec, int block, char *ws, const ChanDev *chans, const H
 }
 
 void launch_wm_span(int prec, bool split, char *ws, const ChanDev *chans, const NodeTile *tiles,
-                    int n_tiles, const int64_t *tcount, int trel, int span, int blk, bool far,
+                    int n_tiles, const int64_t *tcount, int trel, int span, int at, bool far,
                     hipStream_t st)
 {
     constexpr int kSub = kBlock / kWave;
     if (far && split)
         LBMAX_BY_HIST(prec, hipLaunchKernelGGL((k_wm_far<H, kSub>), dim3(n_tiles * kSub),
                                                dim3(kBlock), 0, st, ws, chans, tiles, tcount,
-                                               trel, span, blk));
+                                               trel, span, at));
     else if (far)
         LBMAX_BY_HIST(prec, hipLaunchKernelGGL((k_wm_far<H, 1>), dim3(n_tiles), dim3(kBlock), 0,
-                                               st, ws, chans, tiles, tcount, trel, span, blk));
+                                               st, ws, chans, tiles, tcount, trel, span, at));
     LBMAX_BY_PREC(prec, hipLaunchKernelGGL((k_wm_near<P, H>), dim3(n_tiles), dim3(kBlock), 0, st,
-                                           ws, chans, tiles, tcount, trel, span, blk));
+                                           ws, chans, tiles, tcount, trel, span, at));
 }
 
 void launch_inst_step(int prec, char *ws, const ChanDev *chans, const NodeTile *tiles,
@@ -3837,12 +4174,12 @@ void launch_inst_step(int prec, char *ws, const ChanDev *chans, const NodeTile *
 }
 
 void launch_combine(int prec, int block, char *ws, const ChanDev *chans, const NodeTile *tiles,
-                    int n_tiles, bool far, hipStream_t st)
+                    int n_tiles, hipStream_t st)
 {
     if (n_tiles <= 0 || block <= 0)
         return;
     LBMAX_BY_PREC(prec, hipLaunchKernelGGL(k_combine<P>, dim3(n_tiles, block), dim3(kBlock), 0,
-                                           st, ws, chans, tiles, far ? 1 : 0));
+                                           st, ws, chans, tiles));
 }
 
 void launch_fused_steps(int prec, bool column, int max_ly, char *ws, const ChanDev *chans,

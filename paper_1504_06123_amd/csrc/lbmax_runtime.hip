@@ -206,7 +206,7 @@ int prec_code(lb_precision prec) { return prec == LB_F64 ? 0 : (prec == LB_F32 ?
 // the general pass.)
 int far_span_for(const ChanDev &c)
 {
-    if (c.qb > 0 || c.law == 2 || c.finger || c.n_hist > (1 << 22))
+    if (c.qb > 0 || c.law == 2 || c.n_hist > (1 << 22))
         return 0;
     // accumulated-strain damping factorises over time: no rates to bound
     const double spread = c.law == 1 ? 0.0 : 4.0 * 0.04 / c.ly * c.inv_gc;
@@ -310,13 +310,15 @@ Plan make_plan(const lb_channel_desc *ch, int32_t n_ch, lb_precision prec)
             c.max_chunks == 1 ? 0 : (c.finger ? kFingerPartPlanes : kPartPlanes);
         // far sums: in the planes of the chunk partials (a tile takes the one
         // or the other), or their own where the window has a single chunk;
-        // then their strain and the markers that tell which
-        const size_t far_planes =
-            !c.far ? 0
-                   : (c.law == 1 ? 4  // A, B, strain, accumulated rate
-                                 : std::max(part_planes, 2 * (size_t)far_terms(prec_code(prec))) + 2);
+        // then their strain (deformation) and the markers that tell which
+        const size_t terms = (size_t)far_terms(prec_code(prec));
+        size_t far_planes = 0;
+        if (c.far && c.law == 1)
+            far_planes = 4;  // A, B, strain, accumulated rate
+        else if (c.far)
+            far_planes = std::max(part_planes, (c.finger ? 3 : 2) * terms) + (c.finger ? 5 : 2);
         c.off_far = c.off_part;
-        c.far_t = c.far ? (int)far_planes - 2 : 0;
+        c.far_mark = c.far ? (int)far_planes - 1 : 0;
         off = align_up(off + std::max(part_planes, far_planes) * c.max_chunks * c.np *
                                  sizeof(double),
                        256);
@@ -669,7 +671,7 @@ lb_status resolve_timing(lb_handle *h)
 // Far sums in effect for a block: the span's steps and the block's place in it.
 struct FarBlock {
     int span = 0;   // 0: the block takes the general pass alone
-    int index = 0;  // block of the span
+    int at = 0;     // steps into the span
 };
 
 // The expansion coefficients of every span (constants of the library), by
@@ -696,20 +698,19 @@ void enqueue_pass(lb_handle *h, hipStream_t st, int trel, int block, FarBlock fa
 {
     static const int kVec[3] = {1, 2, 4};
     // some channel's far span starts at this block
-    const bool far_start = far.span > 0 && (far.index * kFarNearBlock) %
-                                                   std::min(far.span, h->plan.far_span_min) ==
-                                               0;
+    const bool far_start =
+        far.span > 0 && far.at % std::min(far.span, h->plan.far_span_min) == 0;
     if (far.span > 0 && h->n_far_tiles > 0) {
         const HistTile *tiles = h->far_list < 0 ? h->d_far_tiles : h->d_hist_tiles + h->far_list;
         if (far_start)
             launch_far_pass(h->pc, h->far_sub, h->ws, h->d_chans, tiles, h->n_far_tiles,
-                            h->d_tcount, trel, far.span, far.index, st);
+                            h->d_tcount, trel, far.span, far.at, st);
         const int pgrid =
             h->persistent ? h->num_cus * hist_pass_blocks_per_cu(h->pc, 1, block) : 0;
         launch_hist_pass(h->pc, 1, block, h->ws, h->d_chans, tiles, h->n_far_tiles,
                          h->d_tcount, trel, pgrid, h->d_tile_counters, true, st);
         launch_near_pass(h->pc, h->near_split, h->ws, h->d_chans, h->d_node_tiles,
-                         h->n_node_tiles, h->d_tcount, trel, far.span, far.index, h->d_far_tab,
+                         h->n_node_tiles, h->d_tcount, trel, far.span, far.at, h->d_far_tab,
                          st);
     } else {
         for (int g = 0; g < 3; ++g) {
@@ -725,17 +726,22 @@ void enqueue_pass(lb_handle *h, hipStream_t st, int trel, int block, FarBlock fa
                        h->hist_group_count[4], h->d_tcount, trel, far.span > 0, st);
     if (h->any_wm && far.span > 0)
         launch_wm_span(h->pc, h->near_split, h->ws, h->d_chans, h->d_node_tiles,
-                       h->n_node_tiles, h->d_tcount, trel, far.span, far.index, far_start, st);
+                       h->n_node_tiles, h->d_tcount, trel, far.span, far.at, far_start, st);
     if (h->any_finger) {
+        const HistTile *tiles = h->d_hist_tiles + h->hist_group_begin[3];
+        if (far_start)
+            launch_finger_far(h->pc, h->ws, h->d_chans, tiles, h->hist_group_count[3],
+                              h->d_tcount, trel, far.span, far.at, st);
         const int pgrid =
             h->persistent ? h->num_cus * finger_pass_blocks_per_cu(h->pc, block) : 0;
-        launch_finger_pass(h->pc, block, h->ws, h->d_chans,
-                           h->d_hist_tiles + h->hist_group_begin[3], h->hist_group_count[3],
-                           h->d_tcount, trel, pgrid, h->d_tile_counters + 3, st);
+        launch_finger_pass(h->pc, block, h->ws, h->d_chans, tiles, h->hist_group_count[3],
+                           h->d_tcount, trel, pgrid, h->d_tile_counters + 3, far.span > 0, st);
+        if (far.span > 0)
+            launch_finger_near(h->pc, h->ws, h->d_chans, h->d_node_tiles, h->n_node_tiles,
+                               h->d_tcount, trel, far.span, far.at, h->d_far_tab, st);
     }
-    if (h->any_chunked && (far.span == 0 || h->any_finger))
-        launch_combine(h->pc, block, h->ws, h->d_chans, h->d_node_tiles, h->n_node_tiles,
-                       far.span > 0, st);
+    if (h->any_chunked && far.span == 0)  // else the near passes combine
+        launch_combine(h->pc, block, h->ws, h->d_chans, h->d_node_tiles, h->n_node_tiles, st);
 }
 
 // One step's launches, step t = *tcount + trel, position m in its block of
@@ -756,7 +762,7 @@ lb_status enqueue_step(lb_handle *h, hipStream_t st, int trel, int m, int block,
     }
     launch_lb(h->pc, h->ws, h->d_chans, h->d_node_tiles, h->n_node_tiles,
               h->d_tcount, trel, h->d_tile_counters,
-              m == 0 ? far.span : 0, far.index, st);
+              m == 0 ? far.span : 0, far.at, st);
     if (timed) {
         HIP_TRY(h, hipEventRecord(e[1], st));
         HIP_TRY(h, hipEventRecord(e[2], st));
@@ -832,31 +838,36 @@ lb_status enqueue_span(lb_handle *h, hipStream_t st, int trel, int m, int block,
 // and their last block ends with the call; channels of the kind the adjoint
 // covers stay unblocked, so that a gradient does not depend on how the run is
 // cut into calls.
+// Full-tensor handles do the same in blocks of 16 steps; a handle that mixes
+// such channels with other window channels takes no spans.
+int far_block(const lb_handle *h) { return h->any_finger ? kMaxFingerBlock : kFarNearBlock; }
+
 int64_t far_steps(const lb_handle *h, int64_t left, int *span)
 {
     *span = 0;
-    if (h->plan.far_span == 0)
+    if (h->plan.far_span == 0 ||
+        (h->any_finger && h->hist_group_count[3] != (int)h->hist_tiles.size()))
         return 0;
-    if (h->block != kFarNearBlock) {
-        if (h->any_grid || h->any_finger || (h->block == 1 && h->adjoint_kind) ||
-            left < (h->block == 1 ? 8 : kFarNearBlock))
-            return 0;
-    }
+    const int nb = far_block(h);
+    if (h->block != nb &&
+        (h->any_grid || (h->block == 1 && h->adjoint_kind) || h->block > nb ||
+         left < (h->block == 1 ? 8 : nb)))
+        return 0;
     int S = kFarNearBlock;
     while (S < h->plan.far_span && S < left)
         S *= 2;
     *span = S;
     const int64_t n = std::min<int64_t>(S, left);
-    return h->block == 1 || h->block == kFarNearBlock ? n : n / kFarNearBlock * kFarNearBlock;
+    return h->block == 1 || h->block == nb ? n : n / nb * nb;
 }
 
 // Enqueue the n steps of a span (n <= span), the first at *tcount + trel.
 lb_status enqueue_far_span(lb_handle *h, hipStream_t st, int trel, int span, int n, bool timed)
 {
+    const int nb = far_block(h);
     for (int i = 0, k = 0; i < n; i += k) {
-        const FarBlock far{span, i / kFarNearBlock};
-        lb_status s = enqueue_span(h, st, trel + i, i % kFarNearBlock, kFarNearBlock, far, n - i,
-                                   timed, &k);
+        const FarBlock far{span, i / nb * nb};
+        lb_status s = enqueue_span(h, st, trel + i, i % nb, nb, far, n - i, timed, &k);
         if (s != LB_OK)
             return s;
     }
@@ -1473,7 +1484,7 @@ lb_status lb_step(lb_handle *h, int64_t n_steps)
                     lb_status e = enqueue_far_span(h, h->stream, i, span, k, h->profile);
                     if (e != LB_OK)
                         return e;
-                    h->block_pos = h->block == kFarNearBlock ? k % kFarNearBlock : 0;
+                    h->block_pos = h->block == far_block(h) ? k % h->block : 0;
                     continue;
                 }
                 if (far > 0 && i > 0)

@@ -154,3 +154,37 @@ def test_strain_damping_spans(Solver, lx, ly, n_hist):
         got = advance(Solver, [ch], prec, calls, block=block, fused=fused)[0]
         for k, a, b in zip(("ux", "sxy", "n1"), got, one):
             assert nerr(a, b) < bound, (prec, block, k, nerr(a, b))
+
+
+@pytest.mark.parametrize("lx,ly,n_hist,chunks", [
+    (5, 13, 127, [1]), (4, 16, 128, [1]), (1, 40, 257, [2]), (8, 32, 300, [2]), (65, 16, 530, [3]),
+])
+def test_full_tensor_spans(Solver, lx, ly, n_hist, chunks):
+    """The full tensor: calls of many steps against single steps in FP64
+    (1e-12), the FP32 forms against the FP64 run (the FP32 tolerances), and a
+    jet whose rates leave the expansion."""
+    ch = twod(lx, ly, n_hist, finger=True) if lx > 1 else uni(ly, n_hist, finger=True)
+    calls = [150, 8, 7, 15, 16, 17, 33, 100]
+    print(f"case full-tensor spans {lx}x{ly}, window {n_hist}", flush=True)
+    one = advance(Solver, [ch], "f64", [1] * sum(calls), chunks=chunks)[0]
+    for prec, block, fused, pers, bound in (
+            ("f64", 1, 1, False, 1e-12), ("f64", 16, 0, True, 1e-12), ("f64", 4, 0, False, 1e-12),
+            ("f32", 16, 1, True, 1e-4), ("f32p64", 8, 0, False, 1e-4)):
+        got = advance(Solver, [ch], prec, calls, block=block, chunks=chunks, persistent=pers,
+                      fused=fused)[0]
+        for k, a, b in zip(("ux", "sxy", "n1"), got, one):
+            assert nerr(a, b) < bound, (prec, block, k, nerr(a, b))
+
+
+@pytest.mark.parametrize("chunks", [[1], [3]])
+def test_full_tensor_rates_beyond_the_expansion(Solver, chunks):
+    ly, lx = 64, 8
+    u0 = np.zeros((2, ly, lx))
+    u0[0, 20:24] = 0.08
+    ch = twod(lx, ly, 600, u0=u0, gx=0.0, gamma_c=0.1, finger=True)
+    calls = [64, 150, 100]
+    print(f"case full tensor, rates beyond the expansion, chunks {chunks}", flush=True)
+    one = advance(Solver, [ch], "f64", [1] * sum(calls), chunks=chunks)[0]
+    got = advance(Solver, [ch], "f64", calls, chunks=chunks)[0]
+    for k, a, b in zip(("ux", "sxy", "n1"), got, one):
+        assert nerr(a, b) < 1e-12, (k, nerr(a, b))
