@@ -1431,10 +1431,8 @@ __global__ __launch_bounds__(SUB == 1 ? kBlock : SUB * kWave) void k_far_pass(
 // Near pass of a block of 32 steps from t0 = t_s + o (o a multiple of 32 below
 // the span S): the far sums carried to m + o, the entries pushed since the
 // span's start (ages 1 .. o), the newest entry (age 0, pushed here), and the
-// ages [H - S + o, H) at the window's end, MG of the block's steps per
-// wavefront.  MG = 32 for wide channels (four tiles of 64 nodes per
-// workgroup); MG = 8 where that leaves compute units idle: the four wavefronts
-// of a workgroup share a tile's rows, and its far sums through LDS.
+// ages [H - S + o, H) at the window's end.  On wide channels a wavefront takes
+// 64 nodes and all of the block's steps (k_near_pass), else k_near_split runs.
 template <typename R, int MG>
 __device__ __forceinline__ void near_rows(R s, R r, int kf, const Decay<R> &dec, double &loc,
                                           R (&pa)[MG][1], R (&pb)[MG][1])
@@ -1446,12 +1444,12 @@ __device__ __forceinline__ void near_rows(R s, R r, int kf, const Decay<R> &dec,
                                 pb, 0);
 }
 
-template <typename P, typename R, int MG, bool HAS_R>
+template <typename P, typename R, bool HAS_R>
 __device__ __forceinline__ void near_tile(char *__restrict__ ws, const ChanDev *c, int n0,
-                                          int mg, int64_t t0, int S, int o,
-                                          const double *__restrict__ tab, double *s_mom)
+                                          int64_t t0, int S, int o,
+                                          const double *__restrict__ tab)
 {
-    constexpr int T = kFarP<R>;
+    constexpr int T = kFarP<R>, MG = kFarNearBlock, m0 = 0;
     constexpr int G = sizeof(R) == 4 ? 8 : 4;
     const int H = c->n_hist;
     const size_t np = (size_t)c->np;
@@ -1461,7 +1459,6 @@ __device__ __forceinline__ void near_tile(char *__restrict__ ws, const ChanDev *
     const bool own = first < c->n;
     const uint32_t off = (uint32_t)node * (uint32_t)sizeof(R);
     const int p = (int)(t0 % H);
-    const int m0 = mg * MG;  // this wavefront's steps m0 .. m0 + MG - 1 of the block
     R *ring_s = reinterpret_cast<R *>(ws + c->off_ring_s);
     R *ring_r = reinterpret_cast<R *>(ws + c->off_ring_r);
     const Decay<R> dec(c);
@@ -1486,7 +1483,7 @@ __device__ __forceinline__ void near_tile(char *__restrict__ ws, const ChanDev *
         velocity_gradient<P>(vel, vel + np, c->lx, c->ly, x, y, kxx, kxy, kyx, kyy);
         const R s = (R)kxy;
         const R r = HAS_R ? (R)shear_rate<P>(kxx, kxy, kyx, kyy) : fabs(s);
-        if (mg == 0 && own) {
+        if (own) {
             ring_s[(size_t)p * np + node] = s;
             if (HAS_R)
                 ring_r[(size_t)p * np + node] = r;
@@ -1500,8 +1497,7 @@ __device__ __forceinline__ void near_tile(char *__restrict__ ws, const ChanDev *
         for (int u = 0; u < G; ++u) {
             const R s = sv[u].v[0];
             near_rows<R, MG>(s, HAS_R ? rv[u].v[0] : fabs(s), k + u + m0, dec, loc, pa, pb);
-            if (MG == kFarNearBlock)
-                __builtin_amdgcn_sched_barrier(0);  // as in far_moments
+            __builtin_amdgcn_sched_barrier(0);  // as in far_moments
         }
     };
     const auto go_on = [] { return true; };
@@ -1530,70 +1526,25 @@ __device__ __forceinline__ void near_tile(char *__restrict__ ws, const ChanDev *
                                        pa[i][0] = ta[i];
                                        pb[i][0] = tb[i];
                                    }
-                                   if (MG == kFarNearBlock)
-                                       __builtin_amdgcn_sched_barrier(0);
+                                   __builtin_amdgcn_sched_barrier(0);
                                }
                            },
                            go_on);
     // far sums of the chunks, newest first
     double MA[T], MB[T];
-    if constexpr (MG == kFarNearBlock) {
 #pragma unroll
-        for (int q = 0; q < T; ++q)
-            MA[q] = MB[q] = 0.0;
-        double O = 0.0;
-        for (int k = 0; k < c->nchunks; ++k) {
-            const double *f = far + (size_t)k * np;
+    for (int q = 0; q < T; ++q)
+        MA[q] = MB[q] = 0.0;
+    double O = 0.0;
+    for (int k = 0; k < c->nchunks; ++k) {
+        const double *f = far + (size_t)k * np;
 #pragma unroll
-            for (int q = 0; q < T; ++q) {
-                const double a = f[q * fplane];
-                MA[q] += a;
-                MB[q] += fma(O, a, f[(T + q) * fplane]);
-            }
-            O += f[(c->far_mark - 1) * fplane];
+        for (int q = 0; q < T; ++q) {
+            const double a = f[q * fplane];
+            MA[q] += a;
+            MB[q] += fma(O, a, f[(T + q) * fplane]);
         }
-    } else {
-        // terms mg, mg + 4, .. by this wavefront, the others' through LDS
-        constexpr int kGroups = kFarNearBlock / MG;
-        constexpr int kPer = (T + kGroups - 1) / kGroups;
-        double a_[kPer], b_[kPer], O = 0.0;
-#pragma unroll
-        for (int i = 0; i < kPer; ++i)
-            a_[i] = b_[i] = 0.0;
-        constexpr int kAhead = 4;  // chunks loaded before any is used
-        for (int k0 = 0; k0 < c->nchunks; k0 += kAhead) {
-            double ta[kAhead][kPer], tb[kAhead][kPer], tt[kAhead];
-#pragma unroll
-            for (int u = 0; u < kAhead; ++u) {
-                const double *f = far + (size_t)min(k0 + u, c->nchunks - 1) * np;
-#pragma unroll
-                for (int i = 0; i < kPer; ++i) {
-                    const int q = min(mg + i * kGroups, T - 1);
-                    ta[u][i] = f[q * fplane];
-                    tb[u][i] = f[(T + q) * fplane];
-                }
-                tt[u] = f[(c->far_mark - 1) * fplane];
-            }
-#pragma unroll
-            for (int u = 0; u < kAhead; ++u)
-                if (k0 + u < c->nchunks) {
-#pragma unroll
-                    for (int i = 0; i < kPer; ++i) {
-                        a_[i] += ta[u][i];
-                        b_[i] += fma(O, ta[u][i], tb[u][i]);
-                    }
-                    O += tt[u];
-                }
-        }
-#pragma unroll
-        for (int i = 0; i < kPer; ++i) {
-            const int q = mg + i * kGroups;
-            if (q < T) {
-                s_mom[q * kWave + lane] = a_[i];
-                s_mom[(T + q) * kWave + lane] = b_[i];
-            }
-        }
-        __syncthreads();
+        O += f[(c->far_mark - 1) * fplane];
     }
     if (!own)
         return;
@@ -1612,13 +1563,8 @@ __device__ __forceinline__ void near_tile(char *__restrict__ ws, const ChanDev *
         double a = 0.0, b = 0.0;
 #pragma unroll
         for (int q = T - 1; q >= 0; --q) {
-            if constexpr (MG == kFarNearBlock) {
-                a = fma(d[q], MA[q], a);
-                b = fma(d[q], MB[q], b);
-            } else {
-                a = fma(d[q], s_mom[q * kWave + lane], a);
-                b = fma(d[q], s_mom[(T + q) * kWave + lane], b);
-            }
+            a = fma(d[q], MA[q], a);
+            b = fma(d[q], MB[q], b);
         }
         if (sizeof(R) == 8 && i > 0)
             F = exp(-((double)(o + m) - mbar) * rate0);
@@ -1639,23 +1585,16 @@ __device__ __forceinline__ void near_tile(char *__restrict__ ws, const ChanDev *
     }
 }
 
-template <typename P, typename R, int MG>
+template <typename P, typename R>
 __global__ __launch_bounds__(kBlock, (sizeof(R) == 4 ? 3 : 1)) void k_near_pass(
     char *__restrict__ ws, const ChanDev *__restrict__ chans, const NodeTile *__restrict__ tiles,
     const int64_t *__restrict__ tcount, int trel, int span, int at,
     const double *__restrict__ tabs)
 {
-    constexpr int kTerms = MG == kFarNearBlock ? 1 : 2 * kFarP<R> * kWave;
-    __shared__ double s_mom[kTerms];
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
-    // node tile of 256 nodes and, with MG = 8, which quarter of it
-    constexpr int kPerTile = MG == kFarNearBlock ? 1 : kBlock / kWave;
-    const int b = MG == kFarNearBlock ? xcd_tile((int)blockIdx.x, (int)gridDim.x)
-                                      : (int)blockIdx.x;
-    const NodeTile tl = tiles[b / kPerTile];
+    const NodeTile tl = tiles[xcd_tile((int)blockIdx.x, (int)gridDim.x)];
     const ChanDev *c = chans + tl.ch;
-    const int n0 = tl.n0 + kWave * (MG == kFarNearBlock ? wave : b % kPerTile);
-    const int mg = MG == kFarNearBlock ? 0 : wave;
+    const int n0 = tl.n0 + kWave * wave;
     if (c->law != 0 || c->finger || c->qb != 0 || n0 >= c->n)
         return;
     if (far_holds(ws, c, n0)) {
@@ -1663,14 +1602,246 @@ __global__ __launch_bounds__(kBlock, (sizeof(R) == 4 ? 3 : 1)) void k_near_pass(
         const int S = far_span(c, span), o = at % S;
         const double *tab = tabs + (size_t)far_class(S) * kFarMaxSteps * kFarP<R>;
         if (c->has_r)
-            near_tile<P, R, MG, true>(ws, c, n0, mg, t0, S, o, tab, s_mom);
+            near_tile<P, R, true>(ws, c, n0, t0, S, o, tab);
         else
-            near_tile<P, R, MG, false>(ws, c, n0, mg, t0, S, o, tab, s_mom);
+            near_tile<P, R, false>(ws, c, n0, t0, S, o, tab);
         return;
     }
     const int n = n0 + (int)(threadIdx.x % kWave);
     if (c->nchunks > 1 && n < c->n)
-        for (int m = mg * MG; m < mg * MG + MG; ++m)
+        for (int m = 0; m < kFarNearBlock; ++m)
+            combine_node<P>(ws, c, n, m);
+}
+
+// Near pass where whole channels are few wavefronts: one workgroup of 4 x PARTS
+// wavefronts per 64 nodes.  A wavefront takes 8 of the block's steps and one
+// part of the rows (in units of 32 rows: the o / 32 pushed since the span's
+// start, then those at the window's end), the parts with their strain counted
+// from the part's own newest row; the parts are added in order in LDS, shifted
+// by the strain before them, as chunks are.  Rows, far terms and output steps
+// are all spread over the wavefronts.  With the rows walked by one part: 19 us
+// a block at 1 x 256 nodes, 55 .. 250 us over 64 channels of up to 64 chunks;
+// so: 16.7 us (a chain of dependent loads by now) and 58 .. 72 us.
+template <typename R>
+constexpr int kNearParts = sizeof(R) == 4 ? 4 : 2;  // FP64: registers for 8 wavefronts
+
+template <typename P, typename R, bool HAS_R>
+__device__ __forceinline__ void near_tile_split(char *__restrict__ ws, const ChanDev *c, int n0,
+                                                int wave, int64_t t0, int S, int o,
+                                                const double *__restrict__ tab, double *s_mom,
+                                                double *s_acc, double *s_T)
+{
+    constexpr int T = kFarP<R>, MG = 8, G = sizeof(R) == 4 ? 8 : 4;
+    constexpr int kParts = kNearParts<R>, kWaves = 4 * kParts, kUnit = kFarNearBlock;
+    const int H = c->n_hist;
+    const size_t np = (size_t)c->np;
+    const int lane = (int)(threadIdx.x % kWave);
+    const int first = n0 + lane;
+    const int node = min(first, c->n - 1);
+    const bool own = first < c->n;
+    const uint32_t off = (uint32_t)node * (uint32_t)sizeof(R);
+    const int p = (int)(t0 % H);
+    const int m0 = wave % 4 * MG, part = wave / 4;
+    R *ring_s = reinterpret_cast<R *>(ws + c->off_ring_s);
+    R *ring_r = reinterpret_cast<R *>(ws + c->off_ring_r);
+    const Decay<R> dec(c);
+    const size_t fplane = (size_t)c->max_chunks * np;
+    const double *far = reinterpret_cast<const double *>(ws + c->off_far) + node;
+
+    // far terms wave, wave + kWaves, .. over the chunks, newest first, and the
+    // strain of the far ages
+    constexpr int kPer = (T + kWaves - 1) / kWaves;
+    double a_[kPer], b_[kPer], Tf = 0.0;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i)
+        a_[i] = b_[i] = 0.0;
+    constexpr int kAhead = 4;  // chunks loaded before any is used
+    for (int k0 = 0; k0 < c->nchunks; k0 += kAhead) {
+        double ta[kAhead][kPer], tb[kAhead][kPer], tt[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const double *f = far + (size_t)min(k0 + u, c->nchunks - 1) * np;
+#pragma unroll
+            for (int i = 0; i < kPer; ++i) {
+                const int q = min(wave + i * kWaves, T - 1);
+                ta[u][i] = f[q * fplane];
+                tb[u][i] = f[(T + q) * fplane];
+            }
+            tt[u] = f[(c->far_mark - 1) * fplane];
+        }
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u)
+            if (k0 + u < c->nchunks) {
+#pragma unroll
+                for (int i = 0; i < kPer; ++i) {
+                    a_[i] += ta[u][i];
+                    b_[i] += fma(Tf, ta[u][i], tb[u][i]);
+                }
+                Tf += tt[u];
+            }
+    }
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        const int q = wave + i * kWaves;
+        if (q < T) {
+            s_mom[q * kWave + lane] = a_[i];
+            s_mom[(T + q) * kWave + lane] = b_[i];
+        }
+    }
+
+    R pa[MG][1], pb[MG][1];
+#pragma unroll
+    for (int i = 0; i < MG; ++i)
+        pa[i][0] = pb[i][0] = R(0);
+    if (part == 0) {
+        // newest entry
+        const P *vel = reinterpret_cast<const P *>(ws + c->off_vel);
+        const int y = node / c->lx, x = node - y * c->lx;
+        P kxx, kxy, kyx, kyy;
+        velocity_gradient<P>(vel, vel + np, c->lx, c->ly, x, y, kxx, kxy, kyx, kyy);
+        const R s = (R)kxy;
+        const R r = HAS_R ? (R)shear_rate<P>(kxx, kxy, kyx, kyy) : fabs(s);
+        if (wave == 0 && own) {
+            ring_s[(size_t)p * np + node] = s;
+            if (HAS_R)
+                ring_r[(size_t)p * np + node] = r;
+        }
+        tail_entry_newest<R, MG>(s, r, m0, dec, pa);
+    }
+    // units of rows of this part; the far ages lie before unit o / 32
+    const int units = S / kUnit, per = (units + kParts - 1) / kParts, near_units = o / kUnit;
+    double loc = 0.0;
+    const auto go_on = [] { return true; };
+    for (int i = part * per; i < min(units, part * per + per); ++i) {
+        if (i == near_units) {
+            if (wave % 4 == 0)
+                s_T[kParts * kWave + lane] = loc;  // strain of the part's newer rows
+            loc += Tf;
+        }
+        const int k = i < near_units ? 1 + i * kUnit : H - S + i * kUnit;
+        if (i < units - 1)
+            walk_rows<R, G, 128, HAS_R, false>(
+                ring_s, ring_r, np, off, H, p, k, k + kUnit,
+                [&](const Pack<R, 1>(&sv)[G], const Pack<R, 1>(&rv)[G], int k1) {
+#pragma unroll
+                    for (int u = 0; u < G; ++u) {
+                        const R s = sv[u].v[0];
+                        near_rows<R, MG>(s, HAS_R ? rv[u].v[0] : fabs(s), k1 + u + m0, dec, loc,
+                                         pa, pb);
+                    }
+                },
+                go_on);
+        else  // the ages that leave in the block
+            walk_rows<R, G, 128, HAS_R, false>(
+                ring_s, ring_r, np, off, H, p, k, H,
+                [&](const Pack<R, 1>(&sv)[G], const Pack<R, 1>(&rv)[G], int k1) {
+#pragma unroll
+                    for (int u = 0; u < G; ++u) {
+                        const R s = sv[u].v[0];
+                        loc += (double)s;
+                        R ta[MG], tb[MG];
+#pragma unroll
+                        for (int j = 0; j < MG; ++j) {
+                            ta[j] = pa[j][0];
+                            tb[j] = pb[j][0];
+                        }
+                        tail_entry<R, MG>(s, HAS_R ? rv[u].v[0] : fabs(s), k1 + u + m0, H,
+                                          (R)loc, dec, ta, tb);
+#pragma unroll
+                        for (int j = 0; j < MG; ++j) {
+                            pa[j][0] = ta[j];
+                            pb[j][0] = tb[j];
+                        }
+                    }
+                },
+                go_on);
+    }
+    if (wave % 4 == 0)
+        s_T[part * kWave + lane] = loc;
+    __syncthreads();
+    // the parts in order, each shifted by the strain before it
+    double O = 0.0, D0 = 0.0;
+#pragma unroll
+    for (int j = 0; j < kParts; ++j) {
+        if (j < part)
+            O += s_T[j * kWave + lane];
+        if (j < near_units / per)
+            D0 += s_T[j * kWave + lane];
+    }
+    D0 += s_T[kParts * kWave + lane];
+    for (int j = 0; j < kParts; ++j) {
+        if (j == part) {
+#pragma unroll
+            for (int i = 0; i < MG; ++i) {
+                double *A = s_acc + (m0 + i) * kWave + lane, *B = A + kFarNearBlock * kWave;
+                const double a = (double)pa[i][0], b = fma(O, a, (double)pb[i][0]);
+                *A = j == 0 ? a : *A + a;
+                *B = j == 0 ? b : *B + b;
+            }
+        }
+        __syncthreads();
+    }
+    if (!own)
+        return;
+    // the far sums at m + o, the block's steps spread over the wavefronts
+    const FarRates<R> fr(c, far_center<R>(ws, c, node, t0 - o), S);
+    const double rate0 = c->inv_tau + fr.rho0;
+    const double mbar = 0.5 * (S - 1);
+    P *sig = reinterpret_cast<P *>(ws + c->off_sig);
+    double *blk = reinterpret_cast<double *>(ws + c->off_blk);
+    for (int m = wave; m < kFarNearBlock; m += kWaves) {
+        const double *d = tab + (size_t)(o + m) * T;
+        double a = 0.0, b = 0.0;
+#pragma unroll
+        for (int q = T - 1; q >= 0; --q) {
+            a = fma(d[q], s_mom[q * kWave + lane], a);
+            b = fma(d[q], s_mom[(T + q) * kWave + lane], b);
+        }
+        const double F = exp(-((double)(o + m) - mbar) * rate0);
+        a *= F;
+        b = fma(D0, a, b * F);
+        const double Am = a + s_acc[m * kWave + lane];
+        // summed with gamma for 2 gamma: doubling is exact
+        const double Bm = 2.0 * (b + s_acc[(kFarNearBlock + m) * kWave + lane]);
+        if (m == 0) {
+            sig[node] = (P)(c->g_inf * Am);
+            sig[np + node] = (P)(c->g_inf * Bm);
+        } else {
+            blk[m * np + node] = Am;
+            blk[(kPlaneB + m) * np + node] = Bm;
+        }
+    }
+}
+
+template <typename P, typename R>
+__global__ __launch_bounds__(4 * kNearParts<R> *kWave) void k_near_split(
+    char *__restrict__ ws, const ChanDev *__restrict__ chans, const NodeTile *__restrict__ tiles,
+    const int64_t *__restrict__ tcount, int trel, int span, int at,
+    const double *__restrict__ tabs)
+{
+    __shared__ double s_mom[2 * kFarP<R> * kWave];
+    __shared__ double s_acc[2 * kFarNearBlock * kWave];
+    __shared__ double s_T[(kNearParts<R> + 1) * kWave];
+    constexpr int kPerTile = kBlock / kWave;  // node tiles of 256 nodes
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    const NodeTile tl = tiles[blockIdx.x / kPerTile];
+    const ChanDev *c = chans + tl.ch;
+    const int n0 = tl.n0 + kWave * (int)(blockIdx.x % kPerTile);
+    if (c->law != 0 || c->finger || c->qb != 0 || n0 >= c->n)
+        return;
+    if (far_holds(ws, c, n0)) {
+        const int64_t t0 = *tcount + trel;
+        const int S = far_span(c, span), o = at % S;
+        const double *tab = tabs + (size_t)far_class(S) * kFarMaxSteps * kFarP<R>;
+        if (c->has_r)
+            near_tile_split<P, R, true>(ws, c, n0, wave, t0, S, o, tab, s_mom, s_acc, s_T);
+        else
+            near_tile_split<P, R, false>(ws, c, n0, wave, t0, S, o, tab, s_mom, s_acc, s_T);
+        return;
+    }
+    const int n = n0 + (int)(threadIdx.x % kWave);
+    if (c->nchunks > 1 && n < c->n)
+        for (int m = wave; m < kFarNearBlock; m += 4 * kNearParts<R>)
             combine_node<P>(ws, c, n, m);
 }
 
@@ -3985,11 +4156,12 @@ void launch_near_pass(int prec, bool split, char *ws, const ChanDev *chans,
     if (n_tiles <= 0)
         return;
     if (split)
-        LBMAX_BY_PREC(prec, hipLaunchKernelGGL((k_near_pass<P, H, 8>),
-                                               dim3(n_tiles * (kBlock / kWave)), dim3(kBlock), 0,
-                                               st, ws, chans, tiles, tcount, trel, span, at, tabs));
+        LBMAX_BY_PREC(prec, hipLaunchKernelGGL((k_near_split<P, H>),
+                                               dim3(n_tiles * (kBlock / kWave)),
+                                               dim3(4 * kNearParts<H> * kWave), 0, st, ws, chans,
+                                               tiles, tcount, trel, span, at, tabs));
     else
-        LBMAX_BY_PREC(prec, hipLaunchKernelGGL((k_near_pass<P, H, kFarNearBlock>), dim3(n_tiles),
+        LBMAX_BY_PREC(prec, hipLaunchKernelGGL((k_near_pass<P, H>), dim3(n_tiles),
                                                dim3(kBlock), 0, st, ws, chans, tiles, tcount,
                                                trel, span, at, tabs));
 }
