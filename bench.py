@@ -99,12 +99,23 @@ def hist_bytes_per_entry(ch) -> int:
     return 4 if unidirectional(ch) else 8
 
 
-def pass_flops_per_entry(block: int) -> int:
-    """Algorithmic FP32 operations per history entry of one pass serving
-    `block` steps: decay rate (fma 2), exponent (1), two exponentials (2),
-    s*E (1), FP64 strain add (1), 2*strain (1); per step of the block: decay
-    factor (1), sigma_xy add (1), sigma_xx fma (2)."""
-    return 8 + 4 * block
+# Steps served by one reading of the window inside a call (the library's longest
+# span of far sums; narrow fast channels take shorter ones).
+SPAN_STEPS = 128
+
+
+def reading_flops_per_entry() -> int:
+    """Algorithmic FP32 operations per history entry of one reading of the
+    window: decay rate (fma 2), exponent (1), exponential (1), s*E (1), u (fma
+    2), FP64 strain add (1); per term of the 12-term expansion: power (1),
+    sigma_xy add (1), sigma_xx fma (2)."""
+    return 8 + 4 * 12
+
+
+def reading_seconds(kt, steps: int) -> float:
+    """History-pass time (far, general and near passes) of `steps` steps in one
+    call, per reading of the window."""
+    return kt[0][0] / 1e3 / -(-steps // SPAN_STEPS)
 
 
 def time_steps(solver, steps: int):
@@ -143,7 +154,8 @@ def bench_large_2d(wl, args, precision: str):
     one_step = None
     if s.block == 1:
         s.profile(True)
-        s.step(8)
+        for _ in range(8):  # calls of one step: no span of far sums
+            s.step(1)
         ms1, n1 = s.kernel_time(0)
         s.profile(False)
         vec1 = s.tiling(0)[1]
@@ -184,33 +196,22 @@ def bench_large_2d(wl, args, precision: str):
     del s
     torch.cuda.empty_cache()
 
-    pass_ms, n_pass = kt[0]
-    pass_s = pass_ms / n_pass / 1e3
+    pass_s = reading_seconds(kt, steps)
     entries = nodes * H
     alg_bytes = entries * hist_bytes_per_entry(ch)
-    alg_flops = entries * pass_flops_per_entry(M)
+    alg_flops = entries * reading_flops_per_entry()
     gbs = alg_bytes / pass_s / 1e9
     tflops = alg_flops / pass_s / 1e12
     hbm_frac = gbs / HBM_PEAK_GBS
     log(f"bench: {precision}: {steps} steps in {el:.3f} s ({el/steps*1e3:.4f} ms/step); "
-        f"history pass {pass_s*1e3:.3f} ms x {n_pass} ({gbs:.0f} GB/s, {tflops:.1f} TFLOP/s); "
+        f"history passes {pass_s*1e3:.3f} ms per {SPAN_STEPS} steps ({gbs:.0f} GB/s, {tflops:.1f} TFLOP/s); "
         f"lattice {kt[1][0]/max(kt[1][1],1):.4f} ms; block step "
         f"{(kt[2][0]/kt[2][1]) if kt[2][1] else 0:.4f} ms")
-    key = (precision, M, cfg["vec"])
-    traffic = measured("traffic_bytes", key)
-    vpe = measured("valu_instr_per_entry", key)
-    vpe_src = "rocprofv3 SQ_INSTS_VALU" if vpe else "model"
-    if not vpe:
-        # Instruction model.  M >= 16: one FMA (or add) per sum and step plus
-        # the seven low and 2 M/8 high powers and the per-entry decay, strain
-        # and compensated-total work (the counted 32-step pass has 91).  Shorter
-        # blocks carry the decay factor along the steps: three instructions per
-        # step.
-        vpe = 2.25 * M + 19 if M >= 16 else 3.5 * M + 10
+    # Instruction model of the far pass: per entry the decay, u and strain work,
+    # per term a power, an add and an FMA, and a sixteenth of the FP64 totals.
+    vpe, vpe_src = 16 + 3 * 12 + 3, "model"
     # Cycles each SIMD spends per wave-level VALU instruction, counted at the
-    # nominal 2.4 GHz engine clock.  Under this load the engine runs below
-    # 2.4 GHz (rocprofv3 GRBM_GUI_ACTIVE counts about 3.7 real cycles per
-    # instruction for the 32-step pass, which holds 2 waves per SIMD).
+    # nominal 2.4 GHz engine clock.
     wave_instr = vpe * entries / 64
     cycles_per_instr = 1024 * 2.4e9 * pass_s / wave_instr
     # The binding published roof: the longer of the algorithmic bytes at the
@@ -222,8 +223,9 @@ def bench_large_2d(wl, args, precision: str):
     else:
         roof = {"bound": "alu", "achieved": tflops, "peak": FP32_PEAK_TFLOPS,
                 "unit": "TFLOP/s", "frac": tflops / FP32_PEAK_TFLOPS}
-    roof.update({"traffic": traffic,
-                 "kernel": f"k_hist_pass ({precision}, {M} steps per pass)",
+    roof.update({"traffic": None,
+                 "kernel": f"k_far_pass, k_near_pass ({precision}, {SPAN_STEPS} steps per "
+                           "reading of the window)",
                  "kernel_avg_ms": pass_s * 1e3, "alg_bytes_per_launch": alg_bytes,
                  "alg_flops_per_launch": alg_flops, "hbm_GBs": gbs, "hbm_frac": hbm_frac,
                  "fp32_TFLOPs": tflops, "fp32_frac": tflops / FP32_PEAK_TFLOPS,
@@ -354,7 +356,7 @@ def bench_finger(steps: int = 128):
     s.close()
     del s
     torch.cuda.empty_cache()
-    pass_s = kt[0][0] / kt[0][1] / 1e3
+    pass_s = reading_seconds(kt, steps)
     # 32 B per entry: kappa (4 x FP32) and exp(kappa dt) - I (4 x FP32)
     alg_bytes = ch.nodes * ch.n_hist * 32
     gbs = alg_bytes / pass_s / 1e9
@@ -366,8 +368,9 @@ def bench_finger(steps: int = 128):
             "config": cfg,
             "roofline": {"bound": "hbm", "achieved": gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                          "frac": gbs / HBM_PEAK_GBS,
-                         "traffic": measured("leg_traffic_bytes", ("full_tensor", 16)),
-                         "kernel": "k_finger_pass_persistent (16 steps per pass)",
+                         "traffic": None,
+                         "kernel": f"k_finger_far, k_finger_near ({SPAN_STEPS} steps per "
+                                   "reading of the ring)",
                          "kernel_avg_ms": pass_s * 1e3, "alg_bytes_per_launch": alg_bytes}}
 
 
@@ -398,14 +401,14 @@ def bench_laws(steps: int = 256):
                "ms_per_step": el / steps * 1e3, "steps_per_pass": block,
                "lattice_kernel_ms": kt[1][0] / max(kt[1][1], 1)}
         if law == "strain_damping":
-            pass_s = kt[0][0] / kt[0][1] / 1e3
+            pass_s = reading_seconds(kt, steps)
             alg = ch.nodes * ch.n_hist * 8
             rec["roofline"] = {"bound": "hbm", "achieved": alg / pass_s / 1e9,
                                "peak": HBM_PEAK_GBS, "unit": "GB/s",
                                "frac": alg / pass_s / 1e9 / HBM_PEAK_GBS,
-                               "traffic": measured("leg_traffic_bytes",
-                                                   ("strain_damping", block)),
-                               "kernel": "k_wm_pass (32 steps per pass)",
+                               "traffic": None,
+                               "kernel": f"k_wm_far, k_wm_near ({SPAN_STEPS} steps per "
+                                         "reading of the window)",
                                "kernel_avg_ms": pass_s * 1e3, "alg_bytes_per_launch": alg}
         name = "nlm_paper_coupling" if coupled else law
         log(f"bench: {name}: {rec['ms_per_step']:.4f} ms/step")
@@ -432,10 +435,10 @@ def bench_batched(steps: int = 2000):
     steps = max(M, steps // M * M)
     s.close()
     batched = nodes * steps / el
-    # the history pass (with its chunk combine) over the 64 windows
-    pass_s = kt[0][0] / kt[0][1] / 1e3
+    # the history passes over the 64 windows, per reading of them
+    pass_s = reading_seconds(kt, steps)
     entries = wl.entries_per_step
-    tflops = entries * pass_flops_per_entry(M) / pass_s / 1e12
+    tflops = entries * reading_flops_per_entry() / pass_s / 1e12
     gbs = entries * 4 / pass_s / 1e9  # unidirectional: FP32 shear rate only
     # plain per-channel FP64: one handle per channel, one step at a time
     handles = [Solver([c], precision="f64") for c in wl.channels]
@@ -460,7 +463,8 @@ def bench_batched(steps: int = 2000):
             "ms_per_step": el / steps * 1e3,
             "roofline": {"bound": "alu", "achieved": tflops, "peak": FP32_PEAK_TFLOPS,
                          "unit": "TFLOP/s", "frac": tflops / FP32_PEAK_TFLOPS, "traffic": None,
-                         "kernel": f"k_hist_pass + k_combine ({M} steps per pass)",
+                         "kernel": f"k_far_pass, k_near_split ({SPAN_STEPS} steps per reading "
+                                   "of the widest windows)",
                          "kernel_avg_ms": pass_s * 1e3, "hbm_GBs": gbs,
                          "hbm_frac": gbs / HBM_PEAK_GBS},
             "plain_per_channel_f64": plain, "speedup_vs_plain_f64": batched / plain}
