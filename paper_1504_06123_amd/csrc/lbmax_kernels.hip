@@ -1277,11 +1277,23 @@ __device__ __forceinline__ bool far_moments(const R *__restrict__ ring_s,
                 const R s = sv[u].v[0];
                 const R r = HAS_R ? rv[u].v[0] : fabs(s);
                 // a filled-up row of a channel without |gamma_dot| rows has r = 0
-                const R w = fused(fr.cu, r, -fr.c0);
-                bad |= !(fabs(w) <= R(1)) && (HAS_R || s != R(0));
+                R w = fused(fr.cu, r, -fr.c0);
+                const bool beyond = !(fabs(w) <= R(1)) && (HAS_R || s != R(0));
                 loc += (double)s;
                 const R g = (R)loc;
                 R x = s * decay_pow(kf, fused(fr.b, r, fr.a));
+                if (__any(beyond)) {
+                    // Beyond the expansion, but damped: the entry's largest term
+                    // of the span, |x| exp(z |u|), below a 2^-40th (FP64: 2^-64th)
+                    // of the sums of the newer entries.  It is taken at u = 1,
+                    // off by no more than twice that.
+                    const R tiny = sizeof(R) == 8 ? R(0x1p-64) : R(0x1p-40);
+                    const R top = fabs(x) * exp(R(kFarZ) * fabs(w));
+                    const bool damped = top <= tiny * fabs((R)A[0] + pa[0]) &&
+                                        top * fabs(g) <= tiny * fabs((R)B[0] + pb[0]);
+                    bad |= beyond && !damped;
+                    w = beyond ? copysign(R(1), w) : w;
+                }
 #pragma unroll
                 for (int q = 0; q < P; ++q) {
                     pa[q] = pa[q] + x;
