@@ -1108,14 +1108,20 @@ __device__ __forceinline__ void combine_node(char *__restrict__ ws, const ChanDe
 // The sums A_m, B_m of an entry set over m < S follow from a few moments of
 // it.  With rate = 1/tau + rho, rho = r / gamma_c, a centre rho_0 per node, the
 // span's middle mbar = (S - 1)/2 and rho_h = z / mbar,
-//   E(k + m) = E(k + mbar) exp(-(m - mbar)(1/tau + rho_0)) exp(-z u v_m),
+//   E(k + m) = exp(-k rate - z u) exp(-m (1/tau + rho_0)) exp(-z u v_m),
 //   u = (rho - rho_0) / rho_h,  v_m = (m - mbar) / mbar,
 // and for |u| <= 1 exp(-z u v) = sum_p d_p(v) u^p with P terms (the Chebyshev
 // expansion in u, its coefficients a table of the span).  So
-//   A_m = F_m sum_p d_p(v_m) MA_p,  MA_p = sum_e s_e E(k + mbar, r_e) u_e^p,
+//   A_m = F_m sum_p d_p(v_m) MA_p,  F_m = exp(-m (1/tau + rho_0)),
+//   MA_p = sum_e s_e exp(-k rate_e - z u_e) u_e^p,
 // likewise B_m with gamma(t0, e) in each term, for every m of the span: the
 // pass costs one exponential and about 3 P operations per entry instead of
 // two and 2 S, and one reading of the window serves S steps instead of 32.
+// The terms are those of the span's first step, up to a factor of e^z either
+// way, whatever the rate: they vanish only where that step's do, F_m never
+// exceeds 1, and the exponent's rounding is that of k rate, as in the general
+// pass (the terms of the span's middle, E(k + mbar), would flush to zero from
+// rates of 1.35 a step on, and be off by mbar rate 2^-24 below).
 // Entries stay inside the window with weight 1 through the span (ages 1 ..
 // H - S - 1 at its start); the rest is the near pass's.
 //
@@ -1138,20 +1144,28 @@ constexpr int kFarP = sizeof(R) == 8 ? far_terms(0) : far_terms(1);
 // Rates of the expansion at a node; t_s: the span's first step.
 template <typename R>
 struct FarRates {
-    R a, b;     // E(k + mbar) = exp(-(2 k + S - 1) (a + b r)), FP32: in powers of 2
+    R a, b;     // rate = a + b r (FP32: in powers of 2, as is z)
     R cu, c0;   // u = cu r - c0
+    R z;
     double rho0;
 
     __device__ __forceinline__ FarRates(const ChanDev *c, R r0, int S)
     {
         const Decay<R> dec(c);
-        a = R(0.5) * dec.a;
-        b = R(0.5) * dec.b;
+        a = dec.a;
+        b = dec.b;
+        z = (R)(sizeof(R) == 4 ? kFarZ * M_LOG2E : kFarZ);
         const double h = kFarZ / (0.5 * (S - 1));
         const double rho = c->inv_gc * (double)r0;
         rho0 = rho > h ? fmax(h, rho - 0.5 * h) : rho;
         cu = (R)(c->inv_gc / h);
         c0 = (R)(rho0 / h);
+    }
+
+    // exp(-k rate - z u)
+    __device__ __forceinline__ R term(R k, R r, R u) const
+    {
+        return decay_pow(R(1), fused(k, fused(b, r, a), z * u));
     }
 };
 
@@ -1251,7 +1265,7 @@ __device__ __forceinline__ bool walk_rows(const R *__restrict__ ring_s,
 template <typename R, int F, bool HAS_R>
 __device__ __forceinline__ bool far_moments(const R *__restrict__ ring_s,
                                             const R *__restrict__ ring_r, size_t np,
-                                            uint32_t off, int H, int p, int ka, int kb, int S,
+                                            uint32_t off, int H, int p, int ka, int kb,
                                             const FarRates<R> &fr, double (&A)[kFarP<R>],
                                             double (&B)[kFarP<R>], double &loc)
 {
@@ -1268,32 +1282,36 @@ __device__ __forceinline__ bool far_moments(const R *__restrict__ ring_s,
 #pragma clang fp contract(off)
 #pragma unroll
             for (int u = 0; u < G; ++u) {
-                // 2 (k + u + mbar), below 2^24 (windows of at most 2^22 entries)
-                const int k2 = 2 * (k + u) + S - 1;
+                // below 2^24 (windows of at most 2^22 entries)
+                const int k1 = k + u;
                 const R kf =
                     sizeof(R) == 4
-                        ? R(small_uniform_to_float((uint32_t)__builtin_amdgcn_readfirstlane(k2)))
-                        : R(k2);
+                        ? R(small_uniform_to_float((uint32_t)__builtin_amdgcn_readfirstlane(k1)))
+                        : R(k1);
                 const R s = sv[u].v[0];
                 const R r = HAS_R ? rv[u].v[0] : fabs(s);
-                // a filled-up row of a channel without |gamma_dot| rows has r = 0
                 R w = fused(fr.cu, r, -fr.c0);
-                const bool beyond = !(fabs(w) <= R(1)) && (HAS_R || s != R(0));
+                if (!HAS_R)  // at rest (and a filled-up row): no term, at any rate
+                    w = s == R(0) ? R(0) : w;
                 loc += (double)s;
                 const R g = (R)loc;
-                R x = s * decay_pow(kf, fused(fr.b, r, fr.a));
-                if (__any(beyond)) {
-                    // Beyond the expansion, but damped: the entry's largest term
-                    // of the span, |x| exp(z |u|), below a 2^-40th (FP64: 2^-64th)
-                    // of the sums of the newer entries.  It is taken at u = 1,
-                    // off by no more than twice that.
+                if (__any(!(fabs(w) <= R(1)))) {
+                    // Beyond the expansion, but at rest or damped: the entry's
+                    // largest term of the span, that of its first step (a rate
+                    // above the centre's) or relative to F_m that of its last,
+                    // below a 2^-40th (FP64: 2^-64th) of the sums of the newer
+                    // entries.  It is taken at u = +-1, off by no more than
+                    // twice that.
                     const R tiny = sizeof(R) == 8 ? R(0x1p-64) : R(0x1p-40);
-                    const R top = fabs(x) * exp(R(kFarZ) * fabs(w));
-                    const bool damped = top <= tiny * fabs((R)A[0] + pa[0]) &&
-                                        top * fabs(g) <= tiny * fabs((R)B[0] + pb[0]);
+                    const R top = fabs(s) * fr.term(kf, r, fmin(R(2) * w, R(0)));
+                    const bool damped =
+                        s == R(0) || (top <= tiny * fabs((R)A[0] + pa[0]) &&
+                                      top * fabs(g) <= tiny * fabs((R)B[0] + pb[0]));
+                    const bool beyond = !(fabs(w) <= R(1));
                     bad |= beyond && !damped;
                     w = beyond ? copysign(R(1), w) : w;
                 }
+                R x = s * fr.term(kf, r, w);
 #pragma unroll
                 for (int q = 0; q < P; ++q) {
                     pa[q] = pa[q] + x;
@@ -1344,7 +1362,7 @@ __device__ __forceinline__ void far_tile(char *__restrict__ ws, const ChanDev *c
     }
     double A[P] = {}, B[P] = {}, loc = 0.0;
     const bool ok =
-        far_moments<R, 16, HAS_R>(ring_s, ring_r, np, off, H, p, ka, kb, S, fr, A, B, loc);
+        far_moments<R, 16, HAS_R>(ring_s, ring_r, np, off, H, p, ka, kb, fr, A, B, loc);
     double *far = reinterpret_cast<double *>(ws + c->off_far) + (size_t)tl.chunk * np + node;
     const size_t fplane = (size_t)c->max_chunks * np;
     if constexpr (SUB == 1) {
@@ -1563,8 +1581,7 @@ __device__ __forceinline__ void near_tile(char *__restrict__ ws, const ChanDev *
     // the far sums at m + o
     const FarRates<R> fr(c, far_center<R>(ws, c, node, t0 - o), S);
     const double rate0 = c->inv_tau + fr.rho0;
-    const double mbar = 0.5 * (S - 1);
-    double F = exp(-((double)(o + m0) - mbar) * rate0);
+    double F = exp(-(double)(o + m0) * rate0);
     const double Fq = exp(-rate0);
     P *sig = reinterpret_cast<P *>(ws + c->off_sig);
     double *blk = reinterpret_cast<double *>(ws + c->off_blk);
@@ -1579,7 +1596,7 @@ __device__ __forceinline__ void near_tile(char *__restrict__ ws, const ChanDev *
             b = fma(d[q], MB[q], b);
         }
         if (sizeof(R) == 8 && i > 0)
-            F = exp(-((double)(o + m) - mbar) * rate0);
+            F = exp(-(double)(o + m) * rate0);
         a *= F;
         b = fma(D0, a, b * F);
         if (sizeof(R) == 4)
@@ -1798,7 +1815,6 @@ __device__ __forceinline__ void near_tile_split(char *__restrict__ ws, const Cha
     // the far sums at m + o, the block's steps spread over the wavefronts
     const FarRates<R> fr(c, far_center<R>(ws, c, node, t0 - o), S);
     const double rate0 = c->inv_tau + fr.rho0;
-    const double mbar = 0.5 * (S - 1);
     P *sig = reinterpret_cast<P *>(ws + c->off_sig);
     double *blk = reinterpret_cast<double *>(ws + c->off_blk);
     for (int m = wave; m < kFarNearBlock; m += kWaves) {
@@ -1809,7 +1825,7 @@ __device__ __forceinline__ void near_tile_split(char *__restrict__ ws, const Cha
             a = fma(d[q], s_mom[q * kWave + lane], a);
             b = fma(d[q], s_mom[(T + q) * kWave + lane], b);
         }
-        const double F = exp(-((double)(o + m) - mbar) * rate0);
+        const double F = exp(-(double)(o + m) * rate0);
         a *= F;
         b = fma(D0, a, b * F);
         const double Am = a + s_acc[m * kWave + lane];
@@ -2363,7 +2379,7 @@ __global__ __launch_bounds__(kBlock, (sizeof(R) == 4 ? 2 : 1)) void k_finger_far
         const R r = finger_rate<R>(v[0], v[1], v[2], v[3]);
         const R u = fused(fr.cu, r, -fr.c0);
         bad |= !(fabs(u) <= R(1));
-        R x = decay_pow(R(2 * k + S - 1), fused(fr.b, r, fr.a));
+        R x = fr.term(R(k), r, u);
         const R fx = (R)pxx, fy = (R)pxy, fz = (R)pyy;
         // the leading sums, whose rounding every step of the span shares, in FP64
         X[0] += (double)(x * fx);
@@ -2571,7 +2587,7 @@ __device__ __forceinline__ void finger_near_node(char *__restrict__ ws, const Ch
         O = mat_mul(O, {d[0], d[fplane], d[2 * fplane], d[3 * fplane]});
     }
     const FarRates<R> fr = finger_far_rates<R>(ws, c, node, t0 - o, S);
-    const double rate0 = c->inv_tau + fr.rho0, mbar = 0.5 * (S - 1);
+    const double rate0 = c->inv_tau + fr.rho0;
     P *sig = reinterpret_cast<P *>(ws + c->off_sig);
     double *blk = reinterpret_cast<double *>(ws + c->off_blk);
 #pragma unroll
@@ -2584,7 +2600,7 @@ __device__ __forceinline__ void finger_near_node(char *__restrict__ ws, const Ch
             y = fma(d[q], Y[q], y);
             z = fma(d[q], Z[q], z);
         }
-        const double Fm = exp(-((double)(o + m) - mbar) * rate0);
+        const double Fm = exp(-(double)(o + m) * rate0);
         x = fma(Fm, x, sx[m]);
         y = fma(Fm, y, sy[m]);
         z = fma(Fm, z, sz[m]);
