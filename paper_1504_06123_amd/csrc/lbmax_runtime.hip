@@ -175,6 +175,7 @@ struct Plan {
     size_t off_tcount = 0, off_chans = 0, off_node_tiles = 0, off_hist_tiles = 0,
            off_far_tiles = 0, off_far_tab = 0, off_stage = 0, stage_bytes = 0;
     int n_node_tiles = 0, n_hist_tiles_max = 0;
+    bool far_room = false;  // some channel's window is long enough for far sums
     // longest and shortest span of far sums over the channels that take them
     // (far_span = 0: none does)
     int far_span = 0, far_span_min = kFarMaxSteps;
@@ -195,25 +196,51 @@ size_t pop_bytes(lb_precision prec) { return prec == LB_F32 ? 4 : 8; }
 size_t history_bytes(lb_precision prec) { return prec == LB_F64 ? 8 : 4; }
 int prec_code(lb_precision prec) { return prec == LB_F64 ? 0 : (prec == LB_F32 ? 1 : 2); }
 
-// Most steps one far pass serves on a channel: 128, 64, 32, or 0 where the
-// general pass is the one to take.  The window has to be a few spans long,
-// since the ages that leave it during a span are summed block by block.  And
-// the rates have to stay within the expansion: their spread over the window is
-// taken as the wall rate 4 u / ly of a channel flow whose peak speed u is two
-// fifths of the Mach guard's.  (A longer span only reads the window less often;
-// six FP64 channels of 32 nodes in a transient, 50-step calls: 0.90 ms a call
-// with 64-step spans, 1.06 ms with 128-step ones, which some tiles leave for
-// the general pass.)
-int far_span_for(const ChanDev &c)
+// Most steps one far pass serves on a channel by its window: 128, 64, 32, or 0
+// where the general pass is the one to take.  The window has to be a few spans
+// long, since the ages that leave it during a span are summed block by block.
+int far_room_for(const ChanDev &c)
 {
     if (c.qb > 0 || c.law == 2 || c.n_hist > (1 << 22))
         return 0;
-    // accumulated-strain damping factorises over time: no rates to bound
-    const double spread = c.law == 1 ? 0.0 : 4.0 * 0.04 / c.ly * c.inv_gc;
     for (int S = kFarMaxSteps; S >= kFarNearBlock; S /= 2)
-        if (c.n_hist >= kFarMinWindow * S && spread <= kFarZ / (0.5 * (S - 1)))
+        if (c.n_hist >= kFarMinWindow * S)
             return S;
     return 0;
+}
+
+// The same by its parameters too: the rates have to stay within the expansion,
+// their spread over the window taken as the wall rate 4 u / ly of a channel
+// flow whose peak speed u is two fifths of the Mach guard's.  (A longer span
+// only reads the window less often; six FP64 channels of 32 nodes in a
+// transient, 50-step calls: 0.90 ms a call with 64-step spans, 1.06 ms with
+// 128-step ones, which some tiles leave for the general pass.)
+int far_span_for(const ChanDev &c)
+{
+    // accumulated-strain damping factorises over time: no rates to bound
+    const double spread = c.law == 1 ? 0.0 : 4.0 * 0.04 / c.ly * c.inv_gc;
+    for (int S = far_room_for(c); S >= kFarNearBlock; S /= 2)
+        if (spread <= kFarZ / (0.5 * (S - 1)))
+            return S;
+    return 0;
+}
+
+// The channels' spans from their present parameters.  Returns whether one
+// changed.
+bool set_spans(Plan &P)
+{
+    bool changed = false;
+    P.far_span = 0;
+    P.far_span_min = kFarMaxSteps;
+    for (ChanDev &c : P.chans) {
+        const int span = far_span_for(c);
+        changed |= span != c.far;
+        c.far = span;
+        P.far_span = std::max(P.far_span, span);
+        if (span > 0)
+            P.far_span_min = std::min(P.far_span_min, span);
+    }
+    return changed;
 }
 
 Plan make_plan(const lb_channel_desc *ch, int32_t n_ch, lb_precision prec)
@@ -253,11 +280,7 @@ Plan make_plan(const lb_channel_desc *ch, int32_t n_ch, lb_precision prec)
         c.l2_gc = M_LOG2E * c.inv_gc;
         c.gx = d.gx;
         c.gy = d.gy;
-        const int span = far_span_for(c);
-        c.far = span;
-        P.far_span = std::max(P.far_span, span);
-        if (span > 0)
-            P.far_span_min = std::min(P.far_span_min, span);
+        P.far_room = P.far_room || far_room_for(c) > 0;
         const int blocks = (c.n + kBlock - 1) / kBlock;
         P.n_node_tiles += blocks;
         // history tiles: at most one per wavefront of nodes and age chunk
@@ -271,7 +294,7 @@ Plan make_plan(const lb_channel_desc *ch, int32_t n_ch, lb_precision prec)
     off = align_up(off + (size_t)P.n_hist_tiles_max * sizeof(HistTile), 256);
     P.off_far_tiles = off;
     P.off_far_tab = off;
-    if (P.far_span > 0) {
+    if (P.far_room) {
         off = align_up(off + (size_t)P.n_hist_tiles_max * sizeof(HistTile), 256);
         P.off_far_tab = off;
         off = align_up(off + (size_t)kFarClasses * kFarMaxSteps * far_terms(prec_code(prec)) *
@@ -310,15 +333,17 @@ Plan make_plan(const lb_channel_desc *ch, int32_t n_ch, lb_precision prec)
             c.max_chunks == 1 ? 0 : (c.finger ? kFingerPartPlanes : kPartPlanes);
         // far sums: in the planes of the chunk partials (a tile takes the one
         // or the other), or their own where the window has a single chunk;
-        // then their strain (deformation) and the markers that tell which
+        // then their strain (deformation) and the markers that tell which.
+        // Room for them by the window alone: lb_set_params may turn them on.
+        const bool room = far_room_for(c) > 0;
         const size_t terms = (size_t)far_terms(prec_code(prec));
         size_t far_planes = 0;
-        if (c.far && c.law == 1)
+        if (room && c.law == 1)
             far_planes = 4;  // A, B, strain, accumulated rate
-        else if (c.far)
+        else if (room)
             far_planes = std::max(part_planes, (c.finger ? 3 : 2) * terms) + (c.finger ? 5 : 2);
         c.off_far = c.off_part;
-        c.far_mark = c.far ? (int)far_planes - 1 : 0;
+        c.far_mark = room ? (int)far_planes - 1 : 0;
         off = align_up(off + std::max(part_planes, far_planes) * c.max_chunks * c.np *
                                  sizeof(double),
                        256);
@@ -335,6 +360,7 @@ Plan make_plan(const lb_channel_desc *ch, int32_t n_ch, lb_precision prec)
             off = align_up(off + 3 * grows * hplane, 256);
     }
     P.total = off;
+    set_spans(P);
     return P;
 }
 
@@ -1410,7 +1436,7 @@ lb_status lb_init(const lb_channel_desc *ch, int32_t n_ch, lb_precision prec, vo
         s = pin_alloc(h);
     if (s != LB_OK)
         return bail(s);
-    if (h->plan.far_span > 0) {
+    if (h->plan.far_room) {
         const std::vector<double> &tab = far_tables(h->pc);
         if (hipMemcpyAsync(const_cast<double *>(h->d_far_tab), tab.data(),
                            tab.size() * sizeof(double), hipMemcpyHostToDevice,
@@ -1875,7 +1901,11 @@ lb_status lb_set_params(lb_handle *h, int32_t ch, double g_inf, double tau_m, do
     // block sums already formed hold the old decay rates: start a new block
     h->block_pos = 0;
     launch_set_params(h->d_chans, ch, g_inf, tau_m, gamma_c, h->stream);
-    return check_launch(h, "set_params");
+    s = check_launch(h, "set_params");
+    if (s != LB_OK || !set_spans(h->plan))
+        return s;
+    build_tiles(h);  // the far tiles follow the spans
+    return upload_tables(h);
 }
 
 size_t lb_adjoint_workspace_bytes(const lb_handle *h, int32_t seg_len)
