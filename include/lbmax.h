@@ -223,8 +223,10 @@ lb_status lb_grad(lb_handle *h, int32_t ch, double *kappa);
  * otherwise):
  *   header, 256 bytes: uint64 magic 0x4C424D4158535431, uint32 version = 6,
  *     uint32 precision, int64 t (completed steps), int32 n_ch,
- *     int32 reserved, uint64 total bytes, int32 block length,
- *     int32 block position (steps of the current block already done);
+ *     int32 span (65536 x the steps of a span of far sums, see lb_set_block,
+ *     + those of the current one already done; 0 outside of one), uint64
+ *     total bytes, int32 block length, int32 block position (steps of the
+ *     current block already done);
  *   then per channel, in order, N = lx*ly:
  *     pop  [9][N] RP post-collision populations of step t-1 minus the
  *                    weights a_i (LB_F32: minus the equilibrium n^eq_i of the
@@ -253,7 +255,8 @@ lb_status lb_grad(lb_handle *h, int32_t ch, double *kappa);
  *                           channels))
  *     blk  [64][N] double   window sums of the block in progress (see
  *                           lb_set_block); read only when the block
- *                           position is not 0 ([96][N] for a full-tensor
+ *                           position is not 0 or the state is inside a block
+ *                           of a span ([96][N] for a full-tensor
  *                           channel; [64 + B][N] on the grid, the last B
  *                           planes the strain of each grid block's entries
  *                           held through the block, oldest grid block first)
@@ -275,9 +278,8 @@ lb_status lb_load_state(lb_handle *h, const void *d_src);
  * lane width in use and the chunk count.  lb_set_graph(h, s) replays s steps per hipGraph launch inside
  * lb_step (0 = plain launches).  All take effect at the next lb_step; only
  * the chunk split changes results, and only through rounding order.
- * (Inside a call of several blocks one reading of the window may serve up to
- * 128 steps, see lb_set_block; the replayed steps per launch then follow that
- * span.)
+ * (Handles that run in spans of far sums, see lb_set_block, take one node per
+ * lane, and the replayed steps per launch follow the span.)
  */
 int32_t lb_max_chunks(const lb_handle *h, int32_t ch);
 lb_status lb_set_tiling(lb_handle *h, int32_t ch, int32_t n_chunks,
@@ -301,16 +303,21 @@ lb_status lb_set_graph(lb_handle *h, int32_t steps_per_graph);
  * (which starts a new block); the graph length (lb_set_graph) must be a
  * multiple of it.  Default 1.
  *
- * Inside one lb_step call, channels with the integral law in the simple-shear
- * reduction and a window of at least 128 entries may take spans of up to 128
- * steps per reading of the window: the sums of all of a span's steps come from
- * an expansion of the decay factors in the entries' rates, to the rounding of
- * the history precision (where the rates are spread too widely for it, 64
- * nodes at a time take the pass described above).  Such calls run in blocks of
- * 32 steps whatever the setting -- the last of them ends with the call when
- * the setting is 1 -- except for handles of 1 step per pass whose channels all
- * are of the kind the adjoint covers.  Nothing of a span outlives the call, and
- * the state written by lb_save_state is as described above.
+ * Channels with the integral law (simple-shear reduction or full tensor) or
+ * its accumulated-strain variant and a window of at least 128 entries may take
+ * spans of up to 128 steps per reading of the window: the sums of all of a
+ * span's steps come from an expansion of the decay factors in the entries'
+ * rates, to the rounding of the history precision (where the rates are spread
+ * too widely for it, 64 nodes at a time take the pass described above; the
+ * accumulated strain's damping factorises exactly).  Such handles run in blocks
+ * of 32 steps (full tensor: 16) whatever the setting, except handles of 1 step
+ * per pass whose channels all are of the kind the adjoint covers, handles with
+ * channels on the quasi-logarithmic grid at another setting than 32, and
+ * handles with full-tensor channels beside others with a window.  Spans
+ * follow one another from the last lb_init, lb_set_block or lb_set_params on
+ * (at 1 step per pass from the step after it), so results do not depend on how
+ * a run is cut into calls, and a state saved inside a span goes on in it, bit
+ * for bit.
  */
 lb_status lb_set_block(lb_handle *h, int32_t steps_per_pass);
 int32_t lb_get_block(const lb_handle *h);

@@ -122,10 +122,10 @@ void launch_init(int prec, char *ws, const ChanDev *chans, int ch,
 void launch_fill_zero(void *p, size_t bytes, hipStream_t st);
 // The lattice kernel also zeroes the persistent-pass tile counters and, at the
 // first step of a channel's far span (`at` steps into a span of `span` steps; 0:
-// none), its far tiles' markers.
+// none) or where the far sums are formed again (`renew`), its far tiles' markers.
 void launch_lb(int prec, char *ws, const ChanDev *chans, const NodeTile *tiles,
                int n_tiles, const int64_t *tcount, int trel, int *tile_counters,
-               int span, int at, hipStream_t st);
+               int span, int at, bool renew, hipStream_t st);
 // History pass (first step of a block of `block` steps) for the tiles of the
 // channels whose lane width is `vec`.  persistent_grid > 0 launches that many
 // persistent workgroups claiming tiles from *counter.  With `far` (32 steps
@@ -138,9 +138,10 @@ int hist_pass_blocks_per_cu(int prec, int vec, int block);
 // blocks of 32 and, per channel, into spans of min(ChanDev::far, span) steps;
 // `at` steps into it (step *tcount + trel) the far pass runs for the
 // channels whose span starts there, each tile split over `sub` wavefronts (1, 4
-// or 8).
+// or 8).  With `renew` it runs for every channel, for the span it is in: the
+// span's entries are in the ring until its end, so the sums come out the same.
 void launch_far_pass(int prec, int sub, char *ws, const ChanDev *chans, const HistTile *tiles,
-                     int n_tiles, const int64_t *tcount, int trel, int span, int at,
+                     int n_tiles, const int64_t *tcount, int trel, int span, int at, bool renew,
                      hipStream_t st);
 // Near pass of the block that starts there: sigma of the block's first step and the block sums
 // of the rest, from the far sums, the entries pushed since the channel's span
@@ -161,7 +162,7 @@ void launch_finger_pass(int prec, int block, char *ws, const ChanDev *chans,
 // Far and near passes of full-tensor channels (blocks of 16 steps); tiles whose
 // far sums do not hold take launch_finger_pass with `far` (16 steps per pass).
 void launch_finger_far(int prec, char *ws, const ChanDev *chans, const HistTile *tiles,
-                       int n_tiles, const int64_t *tcount, int trel, int span, int at,
+                       int n_tiles, const int64_t *tcount, int trel, int span, int at, bool renew,
                        hipStream_t st);
 void launch_finger_near(int prec, char *ws, const ChanDev *chans, const NodeTile *tiles,
                         int n_tiles, const int64_t *tcount, int trel, int span, int at,
@@ -176,7 +177,7 @@ void launch_wm_pass(int prec, int block, char *ws, const ChanDev *chans, const H
 // the near pass.
 void launch_wm_span(int prec, bool split, char *ws, const ChanDev *chans, const NodeTile *tiles,
                     int n_tiles, const int64_t *tcount, int trel, int span, int at, bool far,
-                    hipStream_t st);
+                    bool renew, hipStream_t st);
 // Instantaneous law (Eq. inlM), every step, node-local (other channels return).
 void launch_inst_step(int prec, char *ws, const ChanDev *chans, const NodeTile *tiles,
                       int n_tiles, const int64_t *tcount, int trel, hipStream_t st);

@@ -566,7 +566,7 @@ __global__ __launch_bounds__(kBlock, 5) void k_lb(char *__restrict__ ws,
                                                const NodeTile *__restrict__ tiles,
                                                const int64_t *__restrict__ tcount,
                                                int trel, int *__restrict__ tile_counters,
-                                               int span, int at)
+                                               int span, int at, int renew)
 {
     const NodeTile tl = tiles[xcd_tile((int)blockIdx.x, (int)gridDim.x)];
     const ChanDev *c = chans + tl.ch;
@@ -577,9 +577,10 @@ __global__ __launch_bounds__(kBlock, 5) void k_lb(char *__restrict__ ws,
         tile_counters[threadIdx.x] = 0;
     if (n >= c->n)
         return;
-    // first step of a far span of this channel (span = 0: not a span's step)
+    // first step of a far span of this channel (span = 0: not a span's step), or
+    // its far sums are formed again
     if (span && c->far && c->law == 0 && threadIdx.x % kWave == 0 &&
-        at % far_span(c, span) == 0)
+        (renew || at % far_span(c, span) == 0))
         *far_marker(ws, c, n) = 0.0;
     lb_node<P, S>(ws, c, n, *tcount + trel);
 }
@@ -1437,7 +1438,7 @@ __device__ __forceinline__ void far_tile(char *__restrict__ ws, const ChanDev *c
 template <typename R, int SUB>
 __global__ __launch_bounds__(SUB == 1 ? kBlock : SUB * kWave) void k_far_pass(
     char *__restrict__ ws, const ChanDev *__restrict__ chans, const HistTile *__restrict__ tiles,
-    int n_tiles, const int64_t *__restrict__ tcount, int trel, int span, int at)
+    int n_tiles, const int64_t *__restrict__ tcount, int trel, int span, int at, int renew)
 {
     const int i = SUB == 1 ? (int)blockIdx.x * (kBlock / kWave) +
                                  __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave))
@@ -1448,10 +1449,10 @@ __global__ __launch_bounds__(SUB == 1 ? kBlock : SUB * kWave) void k_far_pass(
     const ChanDev *c = chans + tl.ch;
     if (!c->far)
         return;
-    const int S = far_span(c, span);
-    if (at % S != 0)
+    const int S = far_span(c, span), o = at % S;
+    if (o != 0 && !renew)
         return;  // inside a span of this channel
-    const int64_t t_s = *tcount + trel;
+    const int64_t t_s = *tcount + trel - o;
     if (c->has_r)
         far_tile<R, SUB, true>(ws, c, tl, t_s, S);
     else
@@ -2344,7 +2345,7 @@ __device__ __forceinline__ FarRates<R> finger_far_rates(const char *__restrict__
 template <typename R>
 __global__ __launch_bounds__(kBlock, (sizeof(R) == 4 ? 2 : 1)) void k_finger_far(
     char *__restrict__ ws, const ChanDev *__restrict__ chans, const HistTile *__restrict__ tiles,
-    const int64_t *__restrict__ tcount, int trel, int span, int at)
+    const int64_t *__restrict__ tcount, int trel, int span, int at, int renew)
 {
 #pragma clang fp contract(off)
     constexpr int T = kFarP<R>, U = 4, F = 16;
@@ -2353,11 +2354,11 @@ __global__ __launch_bounds__(kBlock, (sizeof(R) == 4 ? 2 : 1)) void k_finger_far
     const int n0 = tl.n0 + (int)(threadIdx.x & ~63u);
     if (!c->far || n0 >= c->n)
         return;
-    const int S = far_span(c, span);
-    if (at % S != 0)
+    const int S = far_span(c, span), o = at % S;
+    if (o != 0 && !renew)
         return;
     const int H = c->n_hist;
-    const int64_t t_s = *tcount + trel;
+    const int64_t t_s = *tcount + trel - o;
     const size_t np = (size_t)c->np, hplane = (size_t)H * np;
     const int first = tl.n0 + (int)threadIdx.x;
     const int node = min(first, c->n - 1);  // shadow lanes past the end
@@ -2894,7 +2895,7 @@ __global__ __launch_bounds__(kBlock) void k_wm_far(char *__restrict__ ws,
                                                    const ChanDev *__restrict__ chans,
                                                    const NodeTile *__restrict__ tiles,
                                                    const int64_t *__restrict__ tcount, int trel,
-                                                   int span, int at)
+                                                   int span, int at, int renew)
 {
     static_assert(SUB == 1 || SUB * kWave == kBlock, "one workgroup per split tile");
     const NodeTile tl = tiles[SUB == 1 ? blockIdx.x : blockIdx.x / SUB];
@@ -2904,13 +2905,13 @@ __global__ __launch_bounds__(kBlock) void k_wm_far(char *__restrict__ ws,
     const int n0 = tl.n0 + kWave * (SUB == 1 ? wave : (int)(blockIdx.x % SUB));
     if (c->law != 1 || !c->far || n0 >= c->n)
         return;
-    const int S = far_span(c, span);
-    if (at % S != 0)
+    const int S = far_span(c, span), o = at % S;
+    if (o != 0 && !renew)
         return;
     const int H = c->n_hist;
     const size_t np = (size_t)c->np;
     const int first = n0 + lane, node = min(first, c->n - 1);
-    const int p = (int)((*tcount + trel) % H);
+    const int p = (int)((*tcount + trel - o) % H);
     const R *ring_s = reinterpret_cast<const R *>(ws + c->off_ring_s);
     const R *ring_r = reinterpret_cast<const R *>(ws + c->off_ring_r);
     const Decay<R> dec(c);
@@ -4075,12 +4076,12 @@ void launch_fill_zero(void *p, size_t bytes, hipStream_t st)
 }
 
 void launch_lb(int prec, char *ws, const ChanDev *chans, const NodeTile *tiles, int n_tiles,
-               const int64_t *tcount, int trel, int *tile_counters, int span, int at,
+               const int64_t *tcount, int trel, int *tile_counters, int span, int at, bool renew,
                hipStream_t st)
 {
     LBMAX_BY_PREC(prec, hipLaunchKernelGGL((k_lb<P, S>), dim3(n_tiles), dim3(kBlock), 0, st, ws,
                                            chans, tiles, tcount, trel, tile_counters,
-                                           span, at));
+                                           span, at, renew ? 1 : 0));
 }
 
 // Shapes of the history pass: (nodes per lane V, steps per pass M, rows
@@ -4156,7 +4157,7 @@ void launch_hist_pass(int prec, int vec, int block, char *ws, const ChanDev *cha
     } while (0)
 
 void launch_far_pass(int prec, int sub, char *ws, const ChanDev *chans, const HistTile *tiles,
-                     int n_tiles, const int64_t *tcount, int trel, int span, int at,
+                     int n_tiles, const int64_t *tcount, int trel, int span, int at, bool renew,
                      hipStream_t st)
 {
     if (n_tiles <= 0)
@@ -4167,7 +4168,8 @@ void launch_far_pass(int prec, int sub, char *ws, const ChanDev *chans, const Hi
                                            dim3(SUB == 1 ? (n_tiles + per_group - 1) / per_group \
                                                          : n_tiles),                            \
                                            dim3(SUB == 1 ? kBlock : SUB * kWave), 0, st, ws,    \
-                                           chans, tiles, n_tiles, tcount, trel, span, at))
+                                           chans, tiles, n_tiles, tcount, trel, span, at,       \
+                                           renew ? 1 : 0))
     if (sub >= 8)
         LBMAX_FAR(8);
     else if (sub >= 4)
@@ -4289,13 +4291,14 @@ void launch_finger_pass(int prec, int block, char *ws, const ChanDev *chans,
 }
 
 void launch_finger_far(int prec, char *ws, const ChanDev *chans, const HistTile *tiles,
-                       int n_tiles, const int64_t *tcount, int trel, int span, int at,
+                       int n_tiles, const int64_t *tcount, int trel, int span, int at, bool renew,
                        hipStream_t st)
 {
     if (n_tiles <= 0)
         return;
     LBMAX_BY_HIST(prec, hipLaunchKernelGGL((k_finger_far<H>), dim3(n_tiles), dim3(kBlock), 0, st,
-                                           ws, chans, tiles, tcount, trel, span, at));
+                                           ws, chans, tiles, tcount, trel, span, at,
+                                           renew ? 1 : 0));
 }
 
 void launch_finger_near(int prec, char *ws, const ChanDev *chans, const NodeTile *tiles,
@@ -4352,16 +4355,17 @@ void launch_wm_pass(int prec, int block, char *ws, const ChanDev *chans, const H
 
 void launch_wm_span(int prec, bool split, char *ws, const ChanDev *chans, const NodeTile *tiles,
                     int n_tiles, const int64_t *tcount, int trel, int span, int at, bool far,
-                    hipStream_t st)
+                    bool renew, hipStream_t st)
 {
     constexpr int kSub = kBlock / kWave;
     if (far && split)
         LBMAX_BY_HIST(prec, hipLaunchKernelGGL((k_wm_far<H, kSub>), dim3(n_tiles * kSub),
                                                dim3(kBlock), 0, st, ws, chans, tiles, tcount,
-                                               trel, span, at));
+                                               trel, span, at, renew ? 1 : 0));
     else if (far)
         LBMAX_BY_HIST(prec, hipLaunchKernelGGL((k_wm_far<H, 1>), dim3(n_tiles), dim3(kBlock), 0,
-                                               st, ws, chans, tiles, tcount, trel, span, at));
+                                               st, ws, chans, tiles, tcount, trel, span, at,
+                                               renew ? 1 : 0));
     LBMAX_BY_PREC(prec, hipLaunchKernelGGL((k_wm_near<P, H>), dim3(n_tiles), dim3(kBlock), 0, st,
                                            ws, chans, tiles, tcount, trel, span, at));
 }

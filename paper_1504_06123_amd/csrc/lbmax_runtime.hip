@@ -83,7 +83,7 @@ struct StateHeader {
     uint32_t precision;
     int64_t t;
     int32_t n_ch;
-    int32_t reserved;
+    int32_t span;  // steps of the span in effect x 2^16 + span_pos (0: none)
     uint64_t bytes;
     int32_t block_len;
     int32_t block_pos;
@@ -364,6 +364,19 @@ Plan make_plan(const lb_channel_desc *ch, int32_t n_ch, lb_precision prec)
     return P;
 }
 
+// Where the next step falls in the passes over the history.
+struct Place {
+    // without far sums: steps done in the current block (0: next is a pass)
+    int block_pos = 0;
+    // with far sums: steps done in the current span, 1 .. its length (there the
+    // next step starts a span); 0: no span yet, and block_pos says whether a
+    // block begun without far sums (a loaded state's) is to be finished first
+    int span_pos = 0;
+    // the far sums are those of another chunk split, or not there (a loaded
+    // state): the next block of the span forms them again
+    bool stale = false;
+};
+
 }  // namespace
 
 struct lb_handle {
@@ -377,7 +390,7 @@ struct lb_handle {
     std::vector<int> ly, lx, n_hist;
     int64_t t = 0;          // completed steps
     int block = 1;          // steps served by one history pass
-    int block_pos = 0;      // steps done in the current block (0: next is a pass)
+    Place at;
     bool has_out = false;   // readout planes belong to step t-1
     bool poisoned = false;
     int checks = LB_CHECK_FINITE | LB_CHECK_MACH;  // lb_set_checks
@@ -422,7 +435,6 @@ struct lb_handle {
     std::vector<char> upload;
     // graph replay
     int graph_steps = 0;       // lb_set_graph
-    int graph_unit = 0;        // steps of the captured graph
     bool graph_dirty = true;
     hipStream_t cap_stream = nullptr;
     hipGraph_t graph = nullptr;
@@ -696,8 +708,9 @@ lb_status resolve_timing(lb_handle *h)
 
 // Far sums in effect for a block: the span's steps and the block's place in it.
 struct FarBlock {
-    int span = 0;   // 0: the block takes the general pass alone
-    int at = 0;     // steps into the span
+    int span = 0;        // 0: the block takes the general pass alone
+    int at = 0;          // steps into the span
+    bool renew = false;  // form the far sums of the channels' current spans again
 };
 
 // The expansion coefficients of every span (constants of the library), by
@@ -725,12 +738,13 @@ void enqueue_pass(lb_handle *h, hipStream_t st, int trel, int block, FarBlock fa
     static const int kVec[3] = {1, 2, 4};
     // some channel's far span starts at this block
     const bool far_start =
-        far.span > 0 && far.at % std::min(far.span, h->plan.far_span_min) == 0;
+        far.span > 0 &&
+        (far.renew || far.at % std::min(far.span, h->plan.far_span_min) == 0);
     if (far.span > 0 && h->n_far_tiles > 0) {
         const HistTile *tiles = h->far_list < 0 ? h->d_far_tiles : h->d_hist_tiles + h->far_list;
         if (far_start)
             launch_far_pass(h->pc, h->far_sub, h->ws, h->d_chans, tiles, h->n_far_tiles,
-                            h->d_tcount, trel, far.span, far.at, st);
+                            h->d_tcount, trel, far.span, far.at, far.renew, st);
         const int pgrid =
             h->persistent ? h->num_cus * hist_pass_blocks_per_cu(h->pc, 1, block) : 0;
         launch_hist_pass(h->pc, 1, block, h->ws, h->d_chans, tiles, h->n_far_tiles,
@@ -752,12 +766,13 @@ void enqueue_pass(lb_handle *h, hipStream_t st, int trel, int block, FarBlock fa
                        h->hist_group_count[4], h->d_tcount, trel, far.span > 0, st);
     if (h->any_wm && far.span > 0)
         launch_wm_span(h->pc, h->near_split, h->ws, h->d_chans, h->d_node_tiles,
-                       h->n_node_tiles, h->d_tcount, trel, far.span, far.at, far_start, st);
+                       h->n_node_tiles, h->d_tcount, trel, far.span, far.at, far_start, far.renew,
+                       st);
     if (h->any_finger) {
         const HistTile *tiles = h->d_hist_tiles + h->hist_group_begin[3];
         if (far_start)
             launch_finger_far(h->pc, h->ws, h->d_chans, tiles, h->hist_group_count[3],
-                              h->d_tcount, trel, far.span, far.at, st);
+                              h->d_tcount, trel, far.span, far.at, far.renew, st);
         const int pgrid =
             h->persistent ? h->num_cus * finger_pass_blocks_per_cu(h->pc, block) : 0;
         launch_finger_pass(h->pc, block, h->ws, h->d_chans, tiles, h->hist_group_count[3],
@@ -788,7 +803,7 @@ lb_status enqueue_step(lb_handle *h, hipStream_t st, int trel, int m, int block,
     }
     launch_lb(h->pc, h->ws, h->d_chans, h->d_node_tiles, h->n_node_tiles,
               h->d_tcount, trel, h->d_tile_counters,
-              m == 0 ? far.span : 0, far.at, st);
+              m == 0 ? far.span : 0, far.at, far.renew, st);
     if (timed) {
         HIP_TRY(h, hipEventRecord(e[1], st));
         HIP_TRY(h, hipEventRecord(e[2], st));
@@ -855,58 +870,71 @@ lb_status enqueue_span(lb_handle *h, hipStream_t st, int trel, int m, int block,
     return enqueue_step(h, st, trel, m, block, far, timed);
 }
 
-// Steps the next span of far sums covers, from a block's start with `left`
-// steps to go in this call (0: none).  Spans lie inside one lb_step call, so
-// nothing but the block sums outlives it.  Handles set to 32 steps per pass
-// take them as they are; shorter blocks run as blocks of 32 steps inside a
-// span while at least 32 steps are left.  Unblocked handles do so from 8
-// steps on (a far, a general and a near launch against one pass per step),
-// and their last block ends with the call; channels of the kind the adjoint
-// covers stay unblocked, so that a gradient does not depend on how the run is
-// cut into calls.
-// Full-tensor handles do the same in blocks of 16 steps; a handle that mixes
-// such channels with other window channels takes no spans.
+// Steps of one span of far sums (0: the handle takes none).  A handle with
+// channels that take far sums runs in spans, one after the other, cut into
+// blocks of 32 steps (full tensor: 16), whatever its steps per pass; a channel
+// whose own span is shorter starts several inside it.  Where a span begins and
+// ends depends on the steps done since the last lb_set_block or lb_set_params
+// alone, not on how they are cut into calls.  Left out: handles of one step
+// per pass whose channels all are of the kind the adjoint covers, handles with
+// grid channels unless the block is theirs, and full-tensor channels beside
+// other window channels (the blocks differ).
 int far_block(const lb_handle *h) { return h->any_finger ? kMaxFingerBlock : kFarNearBlock; }
 
-int64_t far_steps(const lb_handle *h, int64_t left, int *span)
+int span_in_effect(const lb_handle *h)
 {
-    *span = 0;
-    if (h->plan.far_span == 0 ||
-        (h->any_finger && h->hist_group_count[3] != (int)h->hist_tiles.size()))
+    if (h->any_finger && h->hist_group_count[3] != (int)h->hist_tiles.size())
         return 0;
     const int nb = far_block(h);
-    if (h->block != nb &&
-        (h->any_grid || (h->block == 1 && h->adjoint_kind) || h->block > nb ||
-         left < (h->block == 1 ? 8 : nb)))
+    if (h->block > nb || (h->block != nb && h->any_grid) || (h->block == 1 && h->adjoint_kind))
         return 0;
-    int S = kFarNearBlock;
-    while (S < h->plan.far_span && S < left)
-        S *= 2;
-    *span = S;
-    const int64_t n = std::min<int64_t>(S, left);
-    return h->block == 1 || h->block == nb ? n : n / nb * nb;
+    return h->plan.far_span;
 }
 
-// Enqueue the n steps of a span (n <= span), the first at *tcount + trel.
-lb_status enqueue_far_span(lb_handle *h, hipStream_t st, int trel, int span, int n, bool timed)
+// Enqueue the next launches from `at` on: the rest of a block when the steps
+// after its pass run fused, else one step; at most `left` steps.  Moves `at` on
+// and sets *done to the steps enqueued.
+lb_status enqueue_next(lb_handle *h, hipStream_t st, int trel, Place &at, int64_t left, bool timed,
+                       int *done)
 {
-    const int nb = far_block(h);
-    for (int i = 0, k = 0; i < n; i += k) {
-        const FarBlock far{span, i / nb * nb};
-        lb_status s = enqueue_span(h, st, trel + i, i % nb, nb, far, n - i, timed, &k);
-        if (s != LB_OK)
-            return s;
+    const int S = span_in_effect(h);
+    if (S == 0 || (at.span_pos == 0 && (at.block_pos > 0 || h->block == 1))) {
+        // The general pass; with far sums also a loaded state's block, and the
+        // first step of one step per pass (a caller who changes the
+        // parameters at every step pays for no span).
+        lb_status s = enqueue_span(h, st, trel, at.block_pos, h->block, FarBlock{}, left, timed,
+                                   done);
+        at.block_pos = (at.block_pos + *done) % h->block;
+        if (S > 0 && h->block == 1)
+            at.span_pos = S;
+        return s;
     }
-    return LB_OK;
+    const int nb = far_block(h), pos = at.span_pos % S, m = pos % nb;
+    lb_status s = enqueue_span(h, st, trel, m, nb, {S, pos - m, at.stale && m == 0 && pos > 0},
+                               left, timed, done);
+    if (m == 0)
+        at.stale = false;
+    at.span_pos = pos + *done;
+    return s;
 }
 
-// Steps of one graph: the setting, or the span where far sums are in effect
-// from graph start to graph start.
+// Steps of one captured graph: the setting, or a span.
 int graph_unit(const lb_handle *h)
 {
-    int span = 0;
-    const int64_t n = far_steps(h, kFarMaxSteps, &span);
-    return n > 0 ? (int)n : h->graph_steps;
+    const int S = span_in_effect(h);
+    return S > 0 ? S : h->graph_steps;
+}
+
+// Steps up to the next place where a graph may start: a block's start, a
+// span's with far sums.
+int steps_to_graph(const lb_handle *h)
+{
+    const int S = span_in_effect(h);
+    if (S > 0 && h->at.span_pos > 0)
+        return (S - h->at.span_pos % S) % S;
+    if (S > 0 && h->block == 1)
+        return 1;
+    return (h->block - h->at.block_pos) % h->block;
 }
 
 lb_status capture_graph(lb_handle *h)
@@ -921,16 +949,13 @@ lb_status capture_graph(lb_handle *h)
     }
     if (!h->cap_stream)
         HIP_TRY(h, hipStreamCreateWithFlags(&h->cap_stream, hipStreamNonBlocking));
-    h->graph_unit = graph_unit(h);
+    const int unit = graph_unit(h);
     HIP_TRY(h, hipStreamBeginCapture(h->cap_stream, hipStreamCaptureModeThreadLocal));
-    int span = 0;
+    Place at;
+    at.span_pos = span_in_effect(h);  // a span's start
     lb_status s = LB_OK;
-    if (far_steps(h, h->graph_unit, &span) > 0)
-        s = enqueue_far_span(h, h->cap_stream, 0, span, h->graph_unit, false);
-    else
-        for (int i = 0, k = 0; s == LB_OK && i < h->graph_unit; i += k)
-            s = enqueue_span(h, h->cap_stream, i, i % h->block, h->block, FarBlock{},
-                             h->graph_unit - i, false, &k);
+    for (int i = 0, k = 0; s == LB_OK && i < unit; i += k)
+        s = enqueue_next(h, h->cap_stream, i, at, unit - i, false, &k);
     if (s != LB_OK) {
         hipGraph_t g = nullptr;
         (void)hipStreamEndCapture(h->cap_stream, &g);
@@ -938,7 +963,7 @@ lb_status capture_graph(lb_handle *h)
             (void)hipGraphDestroy(g);
         return s;
     }
-    launch_tick(h->d_tcount, h->graph_unit, h->cap_stream);
+    launch_tick(h->d_tcount, unit, h->cap_stream);
     HIP_TRY(h, hipStreamEndCapture(h->cap_stream, &h->graph));
     HIP_TRY(h, hipGraphInstantiate(&h->graph_exec, h->graph, nullptr, nullptr, 0));
     h->graph_dirty = false;
@@ -1496,46 +1521,34 @@ lb_status lb_step(lb_handle *h, int64_t n_steps)
     if (n_steps < 0)
         return fail(LB_EINVAL, "n_steps must be >= 0");
     int64_t left = n_steps;
-    // Plain launches of a batch of steps starting at the current block
-    // position; the device counter advances once per batch.
+    // Plain launches of a batch of steps from the current place on; the device
+    // counter advances once per batch.
     auto eager = [&](int64_t count) -> lb_status {
         while (count > 0) {
             const int batch = (int)std::min(count, kMaxStepsPerBatch);
-            int i = 0;
-            for (int k = 0; i < batch; i += k) {
-                int span = 0;
-                const int64_t far = h->block_pos == 0 ? far_steps(h, count - i, &span) : 0;
-                if (far > 0 && far <= batch - i) {
-                    k = (int)far;
-                    lb_status e = enqueue_far_span(h, h->stream, i, span, k, h->profile);
-                    if (e != LB_OK)
-                        return e;
-                    h->block_pos = h->block == far_block(h) ? k % h->block : 0;
-                    continue;
-                }
-                if (far > 0 && i > 0)
-                    break;  // the span starts the next batch
-                lb_status e = enqueue_span(h, h->stream, i, h->block_pos, h->block, FarBlock{},
-                                           batch - i, h->profile, &k);
+            for (int i = 0, k = 0; i < batch; i += k) {
+                lb_status e = enqueue_next(h, h->stream, i, h->at, batch - i, h->profile, &k);
                 if (e != LB_OK)
                     return e;
-                h->block_pos = (h->block_pos + k) % h->block;
             }
-            launch_tick(h->d_tcount, i, h->stream);
+            launch_tick(h->d_tcount, batch, h->stream);
             lb_status e = check_launch(h, "tick");
             if (e != LB_OK)
                 return e;
-            count -= i;
+            count -= batch;
         }
         return LB_OK;
     };
     if (h->graph_steps > 0 && !h->profile) {
-        // finish the current block, then replay whole graphs
-        const int64_t head = h->block_pos == 0 ? 0 : std::min<int64_t>(left, h->block - h->block_pos);
-        s = eager(head);
-        if (s != LB_OK)
-            return s;
-        left -= head;
+        // up to where a graph may start (a block begun without far sums: its
+        // end, then the span's), then replay whole graphs
+        for (int n = steps_to_graph(h); n > 0 && left > 0; n = steps_to_graph(h)) {
+            const int64_t head = std::min<int64_t>(left, n);
+            s = eager(head);
+            if (s != LB_OK)
+                return s;
+            left -= head;
+        }
         const int unit = graph_unit(h);
         if (left >= unit) {
             if (h->graph_dirty) {
@@ -1546,6 +1559,8 @@ lb_status lb_step(lb_handle *h, int64_t n_steps)
             while (left >= unit) {
                 HIP_TRY(h, hipGraphLaunch(h->graph_exec, h->stream));
                 left -= unit;
+                h->at.span_pos = span_in_effect(h);
+                h->at.stale = false;
             }
         }
     }
@@ -1614,8 +1629,11 @@ lb_status lb_save_state(lb_handle *h, void *d_dst)
     char *dst = static_cast<char *>(d_dst);
     size_t off = kStateHeader;
     h->upload.assign(state_size(h) > 0 ? kStateHeader + 16 * (size_t)h->n_ch : 0, 0);
-    StateHeader hd{kStateMagic, kStateVersion, (uint32_t)h->prec, h->t, h->n_ch, 0,
-                   state_size(h), h->block, h->block_pos};
+    // the block position: that of a handle whose blocks follow one another
+    const int S = span_in_effect(h), pos = h->at.span_pos;
+    StateHeader hd{kStateMagic, kStateVersion, (uint32_t)h->prec, h->t, h->n_ch,
+                   pos > 0 ? (S << 16) + pos : 0, state_size(h), h->block,
+                   pos > 0 ? pos % h->block : h->at.block_pos};
     std::memcpy(h->upload.data(), &hd, sizeof hd);
     for (int ci = 0; ci < h->n_ch; ++ci) {
         for (const Section &sec : state_sections(h, ci, h->t)) {
@@ -1662,6 +1680,8 @@ lb_status load_state_impl(lb_handle *h, const void *d_src, hipStream_t meta)
     if (hd.block_pos < 0 || hd.block_pos >= std::max(1, hd.block_len) ||
         (hd.block_pos != 0 && hd.block_len != h->block))
         return fail(LB_EINVAL, "state is inside a block of a different length");
+    if (hd.span < 0 || (hd.span & 0xffff) > (hd.span >> 16))
+        return fail(LB_EINVAL, "bad span position in state");
     std::vector<double> forces(2 * (size_t)h->n_ch);
     size_t off = kStateHeader;
     for (int ci = 0; ci < h->n_ch; ++ci) {
@@ -1703,7 +1723,15 @@ lb_status load_state_impl(lb_handle *h, const void *d_src, hipStream_t meta)
         return s;
     h->t = hd.t;
     h->has_out = hd.t > 0;
-    h->block_pos = hd.block_pos;
+    // A state inside a span goes on in it where this handle's spans are as long
+    // (its entries are still in the ring); any other place can start afresh.
+    h->at = Place{};
+    if (hd.span == 0)
+        h->at.block_pos = hd.block_pos;
+    else if ((hd.span >> 16) == span_in_effect(h)) {
+        h->at.span_pos = hd.span & 0xffff;
+        h->at.stale = true;
+    }
     return LB_OK;
 }
 
@@ -1738,6 +1766,7 @@ lb_status lb_set_tiling(lb_handle *h, int32_t ch, int32_t n_chunks, int32_t node
         return fail(LB_EINVAL, "nodes_per_lane must be 1, 2 or 4");
     c.nchunks = n_chunks;
     c.vec = nodes_per_lane;
+    h->at.stale = true;  // the span's far sums lie by the old split
     build_tiles(h);
     return upload_tables(h);
 }
@@ -1782,7 +1811,7 @@ lb_status lb_set_block(lb_handle *h, int32_t steps_per_pass)
         if (c.finger && steps_per_pass > kMaxFingerBlock)
             return fail(LB_EINVAL, "full-tensor channels take at most 16 steps per pass");
     h->block = steps_per_pass;
-    h->block_pos = 0;  // the next step starts a block with a fresh pass
+    h->at = Place{};  // the next step starts a block with a fresh pass
     h->graph_dirty = true;
     build_tiles(h);  // lane widths depend on the block length
     return upload_tables(h);
@@ -1899,7 +1928,7 @@ lb_status lb_set_params(lb_handle *h, int32_t ch, double g_inf, double tau_m, do
     c.l2_tau = M_LOG2E * c.inv_tau;
     c.l2_gc = M_LOG2E * c.inv_gc;
     // block sums already formed hold the old decay rates: start a new block
-    h->block_pos = 0;
+    h->at = Place{};
     launch_set_params(h->d_chans, ch, g_inf, tau_m, gamma_c, h->stream);
     s = check_launch(h, "set_params");
     if (s != LB_OK || !set_spans(h->plan))
