@@ -52,6 +52,11 @@ constexpr int kFarMinWindow = 4;   // windows of at least this many spans take f
 // to the rounding of its FP64 evaluation with 18.
 inline constexpr int far_terms(int prec) { return prec == 0 ? 18 : 12; }
 constexpr double kFarZ = 1.8;
+// z as the exponents hold it: FP32 decays are powers of 2.
+inline constexpr double far_z(int prec)
+{
+    return prec == 0 ? kFarZ : 1.4426950408889634 * kFarZ;
+}
 
 // Per-channel parameters and workspace offsets, read by every kernel.
 // 256 bytes so a table row never straddles two scalar cache lines twice.

@@ -688,6 +688,13 @@ __device__ __forceinline__ float small_uniform_to_float(uint32_t u)
 __device__ __forceinline__ float fused(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double fused(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
+// x held in [-z, z].
+__device__ __forceinline__ float within(float x, float z)
+{
+    return __builtin_amdgcn_fmed3f(x, -z, z);
+}
+__device__ __forceinline__ double within(double x, double z) { return fmax(fmin(x, z), -z); }
+
 template <typename R>
 __device__ __forceinline__ R decay_rate(const Decay<R> &dec, R r)
 {
@@ -1109,12 +1116,12 @@ __device__ __forceinline__ void combine_node(char *__restrict__ ws, const ChanDe
 // The sums A_m, B_m of an entry set over m < S follow from a few moments of
 // it.  With rate = 1/tau + rho, rho = r / gamma_c, a centre rho_0 per node, the
 // span's middle mbar = (S - 1)/2 and rho_h = z / mbar,
-//   E(k + m) = exp(-k rate - z u) exp(-m (1/tau + rho_0)) exp(-z u v_m),
-//   u = (rho - rho_0) / rho_h,  v_m = (m - mbar) / mbar,
-// and for |u| <= 1 exp(-z u v) = sum_p d_p(v) u^p with P terms (the Chebyshev
+//   E(k + m) = exp(-k rate - w) exp(-m (1/tau + rho_0)) exp(-w v_m),
+//   w = z u = z (rho - rho_0) / rho_h,  v_m = (m - mbar) / mbar,
+// and for |u| <= 1 exp(-w v) = sum_p d_p(v) w^p with P terms (the Chebyshev
 // expansion in u, its coefficients a table of the span).  So
 //   A_m = F_m sum_p d_p(v_m) MA_p,  F_m = exp(-m (1/tau + rho_0)),
-//   MA_p = sum_e s_e exp(-k rate_e - z u_e) u_e^p,
+//   MA_p = sum_e s_e exp(-k rate_e - w_e) w_e^p,
 // likewise B_m with gamma(t0, e) in each term, for every m of the span: the
 // pass costs one exponential and about 3 P operations per entry instead of
 // two and 2 S, and one reading of the window serves S steps instead of 32.
@@ -1145,28 +1152,29 @@ constexpr int kFarP = sizeof(R) == 8 ? far_terms(0) : far_terms(1);
 // Rates of the expansion at a node; t_s: the span's first step.
 template <typename R>
 struct FarRates {
-    R a, b;     // rate = a + b r (FP32: in powers of 2, as is z)
-    R cu, c0;   // u = cu r - c0
-    R z;
+    R a, b;     // rate = a + b r (FP32: in powers of 2, as w)
+    R cu, c0;   // w = z u = cu r - c0, whose powers the moments take
     double rho0;
+
+    static constexpr R z = (R)far_z(sizeof(R) == 8 ? 0 : 1);
 
     __device__ __forceinline__ FarRates(const ChanDev *c, R r0, int S)
     {
         const Decay<R> dec(c);
         a = dec.a;
         b = dec.b;
-        z = (R)(sizeof(R) == 4 ? kFarZ * M_LOG2E : kFarZ);
         const double h = kFarZ / (0.5 * (S - 1));
         const double rho = c->inv_gc * (double)r0;
         rho0 = rho > h ? fmax(h, rho - 0.5 * h) : rho;
-        cu = (R)(c->inv_gc / h);
-        c0 = (R)(rho0 / h);
+        const double zh = far_z(sizeof(R) == 8 ? 0 : 1) / h;
+        cu = (R)(c->inv_gc * zh);
+        c0 = (R)(rho0 * zh);
     }
 
-    // exp(-k rate - z u)
-    __device__ __forceinline__ R term(R k, R r, R u) const
+    // exp(-k rate - w)
+    __device__ __forceinline__ R term(R k, R r, R w) const
     {
-        return decay_pow(R(1), fused(k, fused(b, r, a), z * u));
+        return decay_pow(R(1), fused(k, fused(b, r, a), w));
     }
 };
 
@@ -1291,28 +1299,26 @@ __device__ __forceinline__ bool far_moments(const R *__restrict__ ring_s,
                         : R(k1);
                 const R s = sv[u].v[0];
                 const R r = HAS_R ? rv[u].v[0] : fabs(s);
-                R w = fused(fr.cu, r, -fr.c0);
-                if (!HAS_R)  // at rest (and a filled-up row): no term, at any rate
-                    w = s == R(0) ? R(0) : w;
+                const R w0 = fused(fr.cu, r, -fr.c0);
+                const R w = within(w0, fr.z);
                 loc += (double)s;
                 const R g = (R)loc;
-                if (__any(!(fabs(w) <= R(1)))) {
-                    // Beyond the expansion, but at rest or damped: the entry's
-                    // largest term of the span, that of its first step (a rate
-                    // above the centre's) or relative to F_m that of its last,
-                    // below a 2^-40th (FP64: 2^-64th) of the sums of the newer
-                    // entries.  It is taken at u = +-1, off by no more than
-                    // twice that.
-                    const R tiny = sizeof(R) == 8 ? R(0x1p-64) : R(0x1p-40);
-                    const R top = fabs(s) * fr.term(kf, r, fmin(R(2) * w, R(0)));
-                    const bool damped =
-                        s == R(0) || (top <= tiny * fabs((R)A[0] + pa[0]) &&
-                                      top * fabs(g) <= tiny * fabs((R)B[0] + pb[0]));
-                    const bool beyond = !(fabs(w) <= R(1));
-                    bad |= beyond && !damped;
-                    w = beyond ? copysign(R(1), w) : w;
-                }
                 R x = s * fr.term(kf, r, w);
+                if (__builtin_expect(__any(!(fabs(w0) <= fr.z)), 0)) {
+                    // Beyond the expansion, but at rest (or a filled-up row) or
+                    // damped: the entry's largest term of the span, that of its
+                    // first step (a rate above the centre's) or relative to F_m
+                    // that of its last, below a 2^-40th (FP64: 2^-64th) of the
+                    // sums of the newer entries.  It is taken at u = +-1, off by
+                    // no more than twice that.
+                    const R tiny = sizeof(R) == 8 ? R(0x1p-64) : R(0x1p-40);
+                    R rr = r;
+                    asm volatile("" : "+v"(rr));  // the rate again: nothing to carry past here
+                    const R top = fabs(s) * fr.term(kf, rr, fmin(R(2) * w0, R(0)));
+                    const bool damped = top <= tiny * fabs((R)A[0] + pa[0]) &&
+                                        top * fabs(g) <= tiny * fabs((R)B[0] + pb[0]);
+                    bad |= !(fabs(w0) <= fr.z) && !(s == R(0) || damped);
+                }
 #pragma unroll
                 for (int q = 0; q < P; ++q) {
                     pa[q] = pa[q] + x;
@@ -2378,22 +2384,22 @@ __global__ __launch_bounds__(kBlock, (sizeof(R) == 4 ? 2 : 1)) void k_finger_far
         double pxx, pxy, pyy;
         finger_term(E, (double)v[0], (double)v[1], (double)v[2], (double)v[3], pxx, pxy, pyy);
         const R r = finger_rate<R>(v[0], v[1], v[2], v[3]);
-        const R u = fused(fr.cu, r, -fr.c0);
-        bad |= !(fabs(u) <= R(1));
-        R x = fr.term(R(k), r, u);
+        const R w = fused(fr.cu, r, -fr.c0);
+        bad |= !(fabs(w) <= fr.z);
+        R x = fr.term(R(k), r, w);
         const R fx = (R)pxx, fy = (R)pxy, fz = (R)pyy;
         // the leading sums, whose rounding every step of the span shares, in FP64
         X[0] += (double)(x * fx);
         Y[0] += (double)(x * fy);
         Z[0] += (double)(x * fz);
-        x = x * u;
+        x = x * w;
 #pragma unroll
         for (int q = 1; q < T; ++q) {
             px[q] = fused(x, fx, px[q]);
             py[q] = fused(x, fy, py[q]);
             pz[q] = fused(x, fz, pz[q]);
             if (q + 1 < T)
-                x = x * u;
+                x = x * w;
         }
     };
     const auto flush_rows = [&]() {
@@ -4197,7 +4203,8 @@ void launch_near_pass(int prec, bool split, char *ws, const ChanDev *chans,
 }
 
 // d_p(v): the Chebyshev interpolation of exp(-z u v) in u at P nodes, in powers
-// of u (in long double: the powers' coefficients are small differences).
+// of w, far_z(prec) times u (in long double: the powers' coefficients are small
+// differences).
 void fill_far_table(int prec, int span, double *out)
 {
     typedef long double L;
@@ -4227,8 +4234,11 @@ void fill_far_table(int prec, int span, double *out)
             for (int i = 0; i < P; ++i)
                 d[i] += a * T[q][i];
         }
-        for (int i = 0; i < P; ++i)
-            out[m * P + i] = (double)d[i];
+        L scale = 1;
+        for (int i = 0; i < P; ++i) {
+            out[m * P + i] = (double)(d[i] / scale);
+            scale *= (L)far_z(prec);
+        }
     }
 }
 
