@@ -369,6 +369,18 @@ lb_status lb_kernel_time(lb_handle *h, int32_t which, double *total_ms,
                          int64_t *launches);
 
 /*
+ * Where a run stands, for diagnosis and tuning; any pointer may be NULL.
+ * span: steps of one span of far sums under the present settings (0: the
+ * handle takes none, see lb_set_block); span_pos: steps of the current one
+ * already done (0: none begun); graph_launches: hipGraph launches of lb_step
+ * since lb_init; far_tiles: tiles of 64 nodes whose far sums rest on the
+ * expansion in the rates, and marked_tiles: those of them that take the
+ * general pass in the current span (reading it synchronises the stream).
+ */
+lb_status lb_run_info(lb_handle *h, int32_t *span, int32_t *span_pos, int64_t *graph_launches,
+                      int64_t *far_tiles, int64_t *marked_tiles);
+
+/*
  * Material parameters of channel ch from the next step on (G_inf, tau,
  * gamma_c of Eq. nlmax; same validity rules as lb_channel_desc).  The next
  * step starts a new block (see lb_set_block) with a fresh history pass.

@@ -436,6 +436,7 @@ struct lb_handle {
     // graph replay
     int graph_steps = 0;       // lb_set_graph
     bool graph_dirty = true;
+    int64_t graph_launches = 0;
     hipStream_t cap_stream = nullptr;
     hipGraph_t graph = nullptr;
     hipGraphExec_t graph_exec = nullptr;
@@ -1558,6 +1559,7 @@ lb_status lb_step(lb_handle *h, int64_t n_steps)
             }
             while (left >= unit) {
                 HIP_TRY(h, hipGraphLaunch(h->graph_exec, h->stream));
+                h->graph_launches += 1;
                 left -= unit;
                 h->at.span_pos = span_in_effect(h);
                 h->at.stale = false;
@@ -1910,6 +1912,43 @@ lb_status lb_kernel_time(lb_handle *h, int32_t which, double *total_ms, int64_t 
     return LB_OK;
 }
 
+lb_status lb_run_info(lb_handle *h, int32_t *span, int32_t *span_pos, int64_t *graph_launches,
+                      int64_t *far_tiles, int64_t *marked_tiles)
+{
+    lb_status s = usable(h);
+    if (s != LB_OK)
+        return s;
+    const int S = span_in_effect(h);
+    if (span)
+        *span = S;
+    if (span_pos)
+        *span_pos = h->at.span_pos;
+    if (graph_launches)
+        *graph_launches = h->graph_launches;
+    int64_t tiles = 0, marked = 0;
+    for (const ChanDev &c : h->plan.chans) {
+        if (S == 0 || !c.far || c.law != 0)
+            continue;
+        const int n = (c.n + kWave - 1) / kWave;
+        tiles += n;
+        if (!marked_tiles || h->at.span_pos == 0)
+            continue;
+        // one marker per tile, at its first node
+        std::vector<double> m(n);
+        const char *src = h->ws + c.off_far +
+                          (size_t)c.far_mark * c.max_chunks * c.np * sizeof(double);
+        HIP_TRY(h, hipMemcpy2DAsync(m.data(), sizeof(double), src, kWave * sizeof(double),
+                                    sizeof(double), n, hipMemcpyDeviceToHost, h->stream));
+        HIP_TRY(h, hipStreamSynchronize(h->stream));
+        for (double v : m)
+            marked += v != 0.0;
+    }
+    if (far_tiles)
+        *far_tiles = tiles;
+    if (marked_tiles)
+        *marked_tiles = marked;
+    return LB_OK;
+}
 
 lb_status lb_set_params(lb_handle *h, int32_t ch, double g_inf, double tau_m, double gamma_c)
 {

@@ -249,6 +249,16 @@ class Solver:
                                            ctypes.byref(cnt)), "lb_kernel_time")
         return ms.value, cnt.value
 
+    def run_info(self) -> dict:
+        """Where the run stands (lb_run_info): span, span_pos, graph_launches,
+        far_tiles, marked_tiles.  Synchronises the stream."""
+        v = dict(span=ctypes.c_int32(), span_pos=ctypes.c_int32(),
+                 graph_launches=ctypes.c_int64(), far_tiles=ctypes.c_int64(),
+                 marked_tiles=ctypes.c_int64())
+        _lib.check(self.lib.lb_run_info(self.h, *(ctypes.byref(x) for x in v.values())),
+                   "lb_run_info")
+        return {k: x.value for k, x in v.items()}
+
 
 STATE_MAGIC = 0x4C424D4158535431
 STATE_VERSION = 6
