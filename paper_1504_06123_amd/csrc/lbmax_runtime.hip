@@ -438,8 +438,8 @@ struct lb_handle {
     bool graph_dirty = true;
     int64_t graph_launches = 0;
     hipStream_t cap_stream = nullptr;
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t graph_exec = nullptr;
+    // captured steps by the place in the span where they start (0 without spans)
+    std::vector<std::pair<int, hipGraphExec_t>> graph_execs;
     // adjoint sweep
     char *aws = nullptr;
     size_t aws_bytes = 0;
@@ -919,55 +919,67 @@ lb_status enqueue_next(lb_handle *h, hipStream_t st, int trel, Place &at, int64_
     return s;
 }
 
-// Steps of one captured graph: the setting, or a span.
-int graph_unit(const lb_handle *h)
-{
-    const int S = span_in_effect(h);
-    return S > 0 ? S : h->graph_steps;
-}
-
-// Steps up to the next place where a graph may start: a block's start, a
-// span's with far sums.
+// Steps to take before a captured graph may start.  Graphs start at a block's
+// start; in a span at a multiple of its blocks, or of the handle's block where
+// the graph's length is none of those (the places follow one another by that
+// length, so a span of 128 steps has at most 128 / 32 of them, or 128 / block).
 int steps_to_graph(const lb_handle *h)
 {
-    const int S = span_in_effect(h);
-    if (S > 0 && h->at.span_pos > 0)
-        return (S - h->at.span_pos % S) % S;
-    if (S > 0 && h->block == 1)
+    const int S = span_in_effect(h), nb = far_block(h);
+    if (S == 0 || (h->at.span_pos == 0 && h->block > 1))
+        return (h->block - h->at.block_pos) % h->block;
+    if (h->at.span_pos == 0)
         return 1;
-    return (h->block - h->at.block_pos) % h->block;
+    const int pos = h->at.span_pos % S, m = pos % nb;
+    if (h->at.stale && pos > 0)  // to the block that forms the far sums again, and into it
+        return m > 0 ? nb - m : 1;
+    const int unit = h->graph_steps % nb == 0 ? nb : h->block;
+    return (unit - pos % unit) % unit;
 }
 
-lb_status capture_graph(lb_handle *h)
+void drop_graphs(lb_handle *h)
 {
-    if (h->graph_exec) {
-        (void)hipGraphExecDestroy(h->graph_exec);
-        h->graph_exec = nullptr;
-    }
-    if (h->graph) {
-        (void)hipGraphDestroy(h->graph);
-        h->graph = nullptr;
-    }
+    for (auto &e : h->graph_execs)
+        (void)hipGraphExecDestroy(e.second);
+    h->graph_execs.clear();
+    h->graph_dirty = false;
+}
+
+// The graph of the next h->graph_steps steps from the handle's place on,
+// captured once per place.
+lb_status step_graph(lb_handle *h, hipGraphExec_t *out)
+{
+    if (h->graph_dirty)
+        drop_graphs(h);
+    const int S = span_in_effect(h), key = S > 0 ? h->at.span_pos % S : 0;
+    for (auto &e : h->graph_execs)
+        if (e.first == key) {
+            *out = e.second;
+            return LB_OK;
+        }
     if (!h->cap_stream)
         HIP_TRY(h, hipStreamCreateWithFlags(&h->cap_stream, hipStreamNonBlocking));
-    const int unit = graph_unit(h);
     HIP_TRY(h, hipStreamBeginCapture(h->cap_stream, hipStreamCaptureModeThreadLocal));
-    Place at;
-    at.span_pos = span_in_effect(h);  // a span's start
+    Place at = h->at;
     lb_status s = LB_OK;
-    for (int i = 0, k = 0; s == LB_OK && i < unit; i += k)
-        s = enqueue_next(h, h->cap_stream, i, at, unit - i, false, &k);
-    if (s != LB_OK) {
-        hipGraph_t g = nullptr;
-        (void)hipStreamEndCapture(h->cap_stream, &g);
-        if (g)
-            (void)hipGraphDestroy(g);
+    for (int i = 0, k = 0; s == LB_OK && i < h->graph_steps; i += k)
+        s = enqueue_next(h, h->cap_stream, i, at, h->graph_steps - i, false, &k);
+    if (s == LB_OK)
+        launch_tick(h->d_tcount, h->graph_steps, h->cap_stream);
+    hipGraph_t g = nullptr;
+    const hipError_t end = hipStreamEndCapture(h->cap_stream, &g);
+    hipGraphExec_t exec = nullptr;
+    hipError_t inst = hipSuccess;
+    if (s == LB_OK && end == hipSuccess)
+        inst = hipGraphInstantiate(&exec, g, nullptr, nullptr, 0);
+    if (g)
+        (void)hipGraphDestroy(g);
+    if (s != LB_OK)
         return s;
-    }
-    launch_tick(h->d_tcount, unit, h->cap_stream);
-    HIP_TRY(h, hipStreamEndCapture(h->cap_stream, &h->graph));
-    HIP_TRY(h, hipGraphInstantiate(&h->graph_exec, h->graph, nullptr, nullptr, 0));
-    h->graph_dirty = false;
+    HIP_TRY(h, end);
+    HIP_TRY(h, inst);
+    h->graph_execs.push_back({key, exec});
+    *out = exec;
     return LB_OK;
 }
 
@@ -1540,30 +1552,26 @@ lb_status lb_step(lb_handle *h, int64_t n_steps)
         }
         return LB_OK;
     };
-    if (h->graph_steps > 0 && !h->profile) {
-        // up to where a graph may start (a block begun without far sums: its
-        // end, then the span's), then replay whole graphs
-        for (int n = steps_to_graph(h); n > 0 && left > 0; n = steps_to_graph(h)) {
-            const int64_t head = std::min<int64_t>(left, n);
-            s = eager(head);
+    const int G = h->profile ? 0 : h->graph_steps;
+    while (G > 0 && left >= G) {
+        const int64_t n = std::min<int64_t>(left, steps_to_graph(h));
+        if (n > 0) {
+            s = eager(n);
             if (s != LB_OK)
                 return s;
-            left -= head;
+            left -= n;
+            continue;
         }
-        const int unit = graph_unit(h);
-        if (left >= unit) {
-            if (h->graph_dirty) {
-                s = capture_graph(h);
-                if (s != LB_OK)
-                    return s;
-            }
-            while (left >= unit) {
-                HIP_TRY(h, hipGraphLaunch(h->graph_exec, h->stream));
-                h->graph_launches += 1;
-                left -= unit;
-                h->at.span_pos = span_in_effect(h);
-                h->at.stale = false;
-            }
+        hipGraphExec_t exec = nullptr;
+        s = step_graph(h, &exec);
+        if (s != LB_OK)
+            return s;
+        HIP_TRY(h, hipGraphLaunch(exec, h->stream));
+        h->graph_launches += 1;
+        left -= G;
+        if (const int S = span_in_effect(h)) {
+            h->at.span_pos = (h->at.span_pos % S + G - 1) % S + 1;
+            h->at.stale = false;
         }
     }
     s = eager(left);
@@ -2238,10 +2246,7 @@ lb_status lb_destroy(lb_handle *h)
 {
     if (!h)
         return fail(LB_EINVAL, "handle is NULL");
-    if (h->graph_exec)
-        (void)hipGraphExecDestroy(h->graph_exec);
-    if (h->graph)
-        (void)hipGraphDestroy(h->graph);
+    drop_graphs(h);
     drop_adj_graphs(h);
     if (h->adj_stream) {
         (void)hipStreamSynchronize(h->adj_stream);

@@ -98,12 +98,14 @@ def test_a_saved_state_goes_on_inside_its_span(Solver, kind, precision):
                 s.step(90)
                 s.step(60)
                 assert same(outputs(s), want), (block, at, "same handle")
-            with Solver(channels(kind), precision=precision) as s:
-                s.set_block(block)
-                s.set_graph(2 * top)
-                s.load_state(buf)
-                s.step(150)
-                assert same(outputs(s), want), (block, at, "new handle")
+            for graph, n in ((2 * top, 150), (block, 10)):
+                with Solver(channels(kind), precision=precision) as s:
+                    s.set_block(block)
+                    s.set_graph(graph)
+                    s.load_state(buf)
+                    for _ in range(150 // n):
+                        s.step(n)
+                    assert same(outputs(s), want), (block, at, "new handle", graph)
 
 
 def test_states_of_other_settings(Solver):
@@ -184,3 +186,26 @@ def test_a_gradient_does_not_depend_on_the_sampling(Solver):
                 got.append((u[-1].detach().numpy(), theta.grad.numpy()))
     for u, g in got[1:]:
         assert np.array_equal(u, got[0][0]) and np.array_equal(g, got[0][1])
+
+
+@pytest.mark.parametrize("kind,block,graph,calls,launches", [
+    ("2d", 32, 64, (64,) * 6, 6),          # a graph at each of a span's halves
+    ("2d", 32, 96, (96,) * 8, 8),          # four places, one after the other
+    ("2d", 32, 256, (300, 300), 2),        # whole spans: 256 of 300, then from 384 on
+    ("uni", 8, 8, (8,) * 40, 40),          # shorter than a span's block
+    ("uni", 1, 64, (130, 64), 3),          # no spans
+    ("2d", 1, 5, (1,) + (5,) * 30, 30),    # any place
+    ("finger", 16, 48, (48,) * 9, 9),
+])
+def test_graphs_of_the_length_set(Solver, kind, block, graph, calls, launches):
+    """A call of as many steps as the graph is long replays one, wherever in a
+    span it starts, and the results are the plain launches'."""
+    print(f"case graph length {kind} {block} {graph}", flush=True)
+    with Solver(channels(kind), precision="f32") as s:
+        s.set_block(block)
+        s.set_graph(graph)
+        for n in calls:
+            s.step(n)
+        assert s.run_info()["graph_launches"] == launches
+        got = outputs(s)
+    assert same(got, run(Solver, kind, "f32", block, calls))
