@@ -45,6 +45,7 @@ constexpr int kFarMaxSteps = 128;
 constexpr int kFarClasses = 3;  // spans of 32, 64 and 128 steps
 constexpr int kFarMaxTerms = 18;
 constexpr int kFarNearBlock = 32;  // steps served by one near pass
+constexpr int kFarSplitWaves = 4096;  // far tiles are split up to this many wavefronts
 constexpr int kFarMinWindow = 4;   // windows of at least this many spans take far sums
 
 // Expansion terms by history type (code 0: FP64) and the bound z: the

@@ -214,12 +214,19 @@ int far_room_for(const ChanDev &c)
 // flow whose peak speed u is two fifths of the Mach guard's.  (A longer span
 // only reads the window less often; six FP64 channels of 32 nodes in a
 // transient, 50-step calls: 0.90 ms a call with 64-step spans, 1.06 ms with
-// 128-step ones, which some tiles leave for the general pass.)
+// 128-step ones, which some tiles leave for the general pass.)  Spans of 32
+// steps only save part of a walk and waste all of it where some tiles leave
+// them, which channels whose tiles fill the chip unsplit feel in full (1024 x
+// 128 nodes, thinning startup: 43 us a step where they hold, 70 where one tile
+// in ten falls back, 49 by the general pass): not for those.  Spans of 64 steps
+// hold at 52 and fall back at 88 (1024 x 256, general pass 92).
 int far_span_for(const ChanDev &c)
 {
     // accumulated-strain damping factorises over time: no rates to bound
     const double spread = c.law == 1 ? 0.0 : 4.0 * 0.04 / c.ly * c.inv_gc;
-    for (int S = far_room_for(c); S >= kFarNearBlock; S /= 2)
+    const int least =
+        c.law == 0 && !c.finger && c.n > kFarSplitWaves / 4 * kWave ? 64 : kFarNearBlock;
+    for (int S = far_room_for(c); S >= least; S /= 2)
         if (spread <= kFarZ / (0.5 * (S - 1)))
             return S;
     return 0;
@@ -582,7 +589,7 @@ void build_tiles(lb_handle *h)
     // compute unit (4096) and a part keeps at least 32 rows.
     h->far_sub = 1;
     for (int sub : {4, 8})
-        if (far_waves * sub <= 4096 && far_rows >= 32 * sub)
+        if (far_waves * sub <= kFarSplitWaves && far_rows >= 32 * sub)
             h->far_sub = sub;
     h->near_split = wide_tiles <= 1024;
     for (int g = 0; g < 5; ++g)

@@ -20,11 +20,18 @@ def Solver():
     return S
 
 
+JET = np.zeros((2, 60, 8))
+JET[0, 20:24] = 0.08
+
+
 def channels(kind):
     base = workloads.plain_f64().channels[0].replace(lx=3, ly=60, n_hist=600, tau_m=60.0, gx=2e-5)
     uni = base.replace(lx=1)
     return {"2d": [base], "uni": [uni], "finger": [base.replace(finger=True)],
             "strain": [base.replace(law="strain_damping")],
+            # tiles that fall back beside ones that hold
+            "jet": [base.replace(lx=8, gx=0.0, u0=JET)], "jet finger": [
+                base.replace(lx=8, gx=0.0, u0=JET, finger=True)],
             "coupling": [base.replace(paper_coupling=True)],
             # spans of 128, 32 and no steps side by side, and a strain window
             "mixed": [base, uni.replace(ly=20, n_hist=300), uni.replace(n_hist=90),
@@ -51,8 +58,15 @@ def close(a, b):
     return True
 
 
+def split(s, kind):
+    """Windows split into many short chunks: one wavefront per far tile."""
+    if kind.startswith("jet"):
+        s.set_tiling(0, s.max_chunks(0), 1)
+
+
 def run(Solver, kind, precision, block, calls, graph=0, **kw):
     with Solver(channels(kind), precision=precision) as s:
+        split(s, kind)
         s.set_block(block)
         s.set_graph(graph)
         s.set_fused(kw.get("fused", 1))
@@ -65,10 +79,11 @@ CUTS = [(100, 233), (1,) * 40 + (293,), (7, 64, 128, 134), (32, 32, 64, 1, 204),
 
 
 @pytest.mark.parametrize("precision", ["f64", "f32"])
-@pytest.mark.parametrize("kind", ["2d", "uni", "finger", "strain", "coupling", "mixed", "grid"])
+@pytest.mark.parametrize("kind", ["2d", "uni", "finger", "strain", "coupling", "mixed", "grid",
+                                  "jet", "jet finger"])
 def test_cuts_change_nothing(Solver, kind, precision):
     print(f"case cuts {kind} {precision}", flush=True)
-    top = 16 if kind == "finger" else 32
+    top = 16 if kind.endswith("finger") else 32
     for block in (1, 8, top):
         whole = run(Solver, kind, precision, block, (333,))
         for calls in CUTS:
@@ -80,14 +95,16 @@ def test_cuts_change_nothing(Solver, kind, precision):
     assert same(run(Solver, kind, precision, top, CUTS[2], fused=0), whole)
 
 
-@pytest.mark.parametrize("kind", ["2d", "uni", "finger", "strain", "mixed", "grid"])
+@pytest.mark.parametrize("kind", ["2d", "uni", "finger", "strain", "mixed", "grid", "jet",
+                                  "jet finger"])
 @pytest.mark.parametrize("precision", ["f64", "f32"])
 def test_a_saved_state_goes_on_inside_its_span(Solver, kind, precision):
     print(f"case resume {kind} {precision}", flush=True)
-    top = 16 if kind == "finger" else 32
+    top = 16 if kind.endswith("finger") else 32
     for block in (1, 8, top):
         for at in (1, 5, 48, 64, 128, 129, 200):
             with Solver(channels(kind), precision=precision) as s:
+                split(s, kind)
                 s.set_block(block)
                 s.step(at)
                 buf = s.save_state()
@@ -100,6 +117,7 @@ def test_a_saved_state_goes_on_inside_its_span(Solver, kind, precision):
                 assert same(outputs(s), want), (block, at, "same handle")
             for graph, n in ((2 * top, 150), (block, 10)):
                 with Solver(channels(kind), precision=precision) as s:
+                    split(s, kind)
                     s.set_block(block)
                     s.set_graph(graph)
                     s.load_state(buf)

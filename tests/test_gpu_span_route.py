@@ -76,6 +76,10 @@ def test_settings_that_take_no_spans(Solver):
                                ([base(), grid], 8, 0), ([base(), grid], 32, 128),
                                ([base(finger=True), base()], 16, 0),
                                ([base(gamma_c=1e-3)], 32, 0),
+                               # spans of 32 steps: not beyond 65536 nodes
+                               ([base(lx=2048, ly=32, gamma_c=0.05)], 32, 32),
+                               ([base(lx=2049, ly=32, gamma_c=0.05)], 32, 0),
+                               ([base(lx=2049, ly=32)], 32, 64),
                                ([base(law="strain_damping", gamma_c=1e-3)], 32, 128)):
         with Solver(chans, precision="f32") as s:
             s.set_block(block)
@@ -129,3 +133,35 @@ def test_general_pass_block_lengths(Solver, kind):
         s.step(760)
         assert s.run_info()["span_pos"] == 760 % 128
         assert error(outputs(s), want) < 1e-12
+
+
+# old entries far slower than the newest: the oldest far one, one row before it,
+# the older half, one column of nodes alone, and none
+@pytest.mark.parametrize("rows", ["last", "one", "half", "column", "none"])
+@pytest.mark.parametrize("kind,chunks", [("2d", 1), ("2d", 9), ("uni", 1), ("uni", 9),
+                                         ("finger", 1)])
+def test_old_rates_beyond_the_expansion(Solver, kind, chunks, rows):
+    from test_gpu_far_rates import channel, history, run_general, written_state
+    ch = channel(kind, 288, 900, tau_m=1000.0, gamma_c=0.02)
+    print(f"case old rates beyond the expansion {kind} {chunks} {rows}", flush=True)
+    s = history(ch, 0.002)
+    slow = s[0] * np.float32(0.2)
+    if rows in ("last", "one"):
+        s[900 - 128 - 2 - (0 if rows == "last" else 11)] = slow
+    elif rows == "half":
+        s[450:] = slow
+    elif rows == "column":
+        s[450:, 70] = slow[70]
+    want = run_general(Solver, ch, "f64", s, 40)
+    for precision, tol in (("f64", 1e-12), ("f32p64", 1e-5)):
+        with Solver([ch], precision=precision) as sol:
+            sol.set_block(16 if kind == "finger" else 32)
+            sol.set_tiling(0, min(chunks, sol.max_chunks(0)), 1)
+            sol.load_state(written_state(ch, precision, s))
+            sol.step(40)
+            info = sol.run_info()
+            got = outputs(sol)
+        tiles = -(-ch.nodes // 64)
+        assert info["far_tiles"] == tiles
+        assert info["marked_tiles"] == {"none": 0, "column": 1}.get(rows, tiles)
+        assert error(got, tuple(want[k] for k in ("ux", "uy", "sxy", "n1"))) < tol
