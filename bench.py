@@ -154,7 +154,8 @@ def bench_large_2d(wl, args, precision: str):
     one_step = None
     if s.block == 1:
         s.profile(True)
-        for _ in range(8):  # calls of one step: no span of far sums
+        for _ in range(8):  # a new block each: no span of far sums
+            s.set_block(1)
             s.step(1)
         ms1, n1 = s.kernel_time(0)
         s.profile(False)
@@ -182,11 +183,13 @@ def bench_large_2d(wl, args, precision: str):
     M = cfg["block"]
     # sustained: the run length rounded up to whole blocks (or --steps if longer)
     steps = -(-max(args.steps, LARGE_2D_RUN_STEPS) // M) * M
-    s.step(2 * M)
-    # one block alone, in the tuned launch
+    # one span (without spans, one block) alone, in the tuned launch
+    info = s.run_info()
+    alone = info["span"] or M
+    s.step(2 * alone - info["span_pos"] % alone)
     torch.cuda.synchronize()
     t0 = time.perf_counter()
-    s.step(M)
+    s.step(alone)
     torch.cuda.synchronize()
     burst_s = time.perf_counter() - t0
     el, kt = time_steps(s, steps)
@@ -233,8 +236,8 @@ def bench_large_2d(wl, args, precision: str):
                  "valu_cycles_per_instr_at_2p4ghz": cycles_per_instr})
     return {"el": el, "steps": steps, "cfg": cfg, "roof": roof, "one_step": one_step,
             "node_steps_per_s": nodes * steps / el, "ms_per_step": el / steps * 1e3,
-            "burst": {"steps": M, "ms_per_step": burst_s / M * 1e3,
-                      "value": nodes * M / burst_s}}
+            "burst": {"steps": alone, "ms_per_step": burst_s / alone * 1e3,
+                      "value": nodes * alone / burst_s}}
 
 
 def oracle_strip(seconds: float, seed_offset: int = 10):

@@ -7,6 +7,11 @@ uneven channels have similar work), plain vs persistent history pass, and
 the hipGraph replay length.  Each candidate is timed with HIP events on the
 solver's stream for a few blocks of steps; the solver's state is saved before
 and restored after, and the fastest candidate is applied.
+
+A handle that runs in spans of far sums does so whatever its steps per pass,
+with one node per lane: candidates that differ in those alone are one, and a
+trial takes whole spans, from a span's start on (parts of one differ by whether
+they hold its reading of the window).
 """
 from __future__ import annotations
 
@@ -45,11 +50,37 @@ def candidates(solver, blocks: Iterable[int] = (1, 4, 8, 16),
     return out
 
 
+def _distinct(solver, cands: List[Dict]) -> List[Dict]:
+    """The candidates without those that run as another one does: of a group
+    the first of the longest block."""
+    span = {}
+    solver.set_graph(0)
+    for block in {c["block"] for c in cands}:
+        solver.set_block(block)
+        span[block] = solver.run_info()["span"]
+    out = {}
+    for i, c in enumerate(cands):
+        shape = (c["block"], c["vec"]) if span[c["block"]] == 0 else None
+        key = (shape, c["chunk_len"], c["persistent"], c["graph"])
+        if key not in out or out[key][1]["block"] < c["block"]:
+            out[key] = (i, c)
+    return [c for _, c in sorted(out.values(), key=lambda x: x[0])]
+
+
 def time_config(solver, cfg: Dict, steps: int) -> float:
-    """Milliseconds per step of `steps` steps under cfg (after one warm block)."""
+    """Milliseconds per step of `steps` steps under cfg (after one warm block;
+    with spans of far sums of as many whole spans and graphs as hold `steps`,
+    after one)."""
     import torch
     apply(solver, cfg)
-    solver.step(cfg["block"] + (cfg["graph"] or 0))
+    span = solver.run_info()["span"]
+    if span:
+        period = math.lcm(span, cfg["graph"] or 1)
+        steps = -(-steps // period) * period
+        # one step per pass: the first step comes before the first span
+        solver.step(period + (1 if cfg["block"] == 1 else 0))
+    else:
+        solver.step(cfg["block"] + (cfg["graph"] or 0))
     e0 = torch.cuda.Event(enable_timing=True)
     e1 = torch.cuda.Event(enable_timing=True)
     stream = solver.stream
@@ -71,6 +102,7 @@ def tune(solver, cands: Optional[List[Dict]] = None, min_steps: int = 32,
     solver.set_graph(0)
     solver.set_block(1)             # save at a block boundary
     saved = solver.save_state()
+    cands = _distinct(solver, cands)
     results = []
     t_start = time.perf_counter()
     for cfg in cands:
