@@ -179,6 +179,16 @@ lb_status lb_step(lb_handle *h, int64_t n_steps);
 int64_t lb_time(const lb_handle *h);
 
 /*
+ * Host memory.  A handle holds a pinned buffer for its readouts, of 32.1 bytes
+ * per node of its widest channel and at most 16 MiB, and copies large readouts
+ * out with up to four threads, which end with the call.  Where pinned memory is
+ * not to be had, or after lb_set_pinned(h, 0), which gives it back, readouts go
+ * through the workspace instead, a few times slower; lb_set_pinned(h, 1) tries
+ * for the buffer again.  The values are the same.
+ */
+lb_status lb_set_pinned(lb_handle *h, int32_t enable);
+
+/*
  * Failure detection at readouts.  flags (default: both):
  *   LB_CHECK_FINITE: lb_fields, lb_stress and lb_grad return LB_ENONFINITE
  *     when a value they return is NaN or infinite (the run has diverged);

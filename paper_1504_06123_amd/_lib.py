@@ -77,6 +77,7 @@ SIGNATURES = {
     "lb_set_persistent": (ctypes.c_int, [_H, ctypes.c_int32]),
     "lb_profile": (ctypes.c_int, [_H, ctypes.c_int32]),
     "lb_kernel_time": (ctypes.c_int, [_H, ctypes.c_int32, _D, ctypes.POINTER(ctypes.c_int64)]),
+    "lb_set_pinned": (ctypes.c_int, [_H, ctypes.c_int32]),
     "lb_run_info": (ctypes.c_int, [_H, ctypes.POINTER(ctypes.c_int32),
                                    ctypes.POINTER(ctypes.c_int32),
                                    ctypes.POINTER(ctypes.c_int64),

@@ -434,7 +434,8 @@ struct lb_handle {
     int fuse_max_ly = 0;
     int fuse_mode = 1;         // lb_set_fused
     char *pin = nullptr;       // pinned readout buffer
-    size_t pin_nodes = 0;      // nodes one part of it holds
+    size_t pin_nodes = 0;      // nodes one part of the readout buffer holds
+    std::vector<char> host_part;  // without pin: the host's copy of a part
     hipEvent_t pin_ev[2] = {nullptr, nullptr};
     // host mirrors kept alive for asynchronous uploads
     std::vector<NodeTile> node_tiles;
@@ -1001,27 +1002,6 @@ size_t pin_part_bytes(size_t nodes)
                     256);
 }
 
-// Pinned buffer for the handle's widest channel: one part where it fits, else
-// two.
-lb_status pin_alloc(lb_handle *h)
-{
-    size_t nodes = 0;
-    for (const ChanDev &c : h->plan.chans)
-        nodes = std::max(nodes, (size_t)c.n);
-    size_t parts = 1;
-    if (pin_part_bytes(nodes) > kPinPartMax) {
-        nodes = kPinPartMax / (4 * sizeof(double) + 1) / kBlock * kBlock;
-        parts = 2;
-        for (hipEvent_t &e : h->pin_ev)
-            HIP_TRY(h, hipEventCreateWithFlags(&e, hipEventDisableTiming));
-    }
-    h->pin_nodes = nodes;
-    void *p = nullptr;
-    HIP_TRY(h, hipHostMalloc(&p, parts * pin_part_bytes(nodes), hipHostMallocDefault));
-    h->pin = static_cast<char *>(p);
-    return LB_OK;
-}
-
 void pin_free(lb_handle *h)
 {
     if (h->pin)
@@ -1032,6 +1012,40 @@ void pin_free(lb_handle *h)
             (void)hipEventDestroy(e);
         e = nullptr;
     }
+}
+
+// Readout buffer for the handle's widest channel: pinned, one part where it
+// fits, else two; or, where pinned memory is not wanted or not to be had, as
+// many nodes at a time as the workspace's staging area holds.
+void set_readout_buffer(lb_handle *h, bool pinned)
+{
+    pin_free(h);
+    size_t widest = 0;
+    for (const ChanDev &c : h->plan.chans)
+        widest = std::max(widest, (size_t)c.n);
+    if (pinned) {
+        const bool one = pin_part_bytes(widest) <= kPinPartMax;
+        const size_t nodes =
+            one ? widest : kPinPartMax / (4 * sizeof(double) + 1) / kBlock * kBlock;
+        void *p = nullptr;
+        hipError_t e = hipHostMalloc(&p, (one ? 1 : 2) * pin_part_bytes(nodes),
+                                     hipHostMallocDefault);
+        if (e == hipSuccess)
+            h->pin = static_cast<char *>(p);
+        for (int i = 0; e == hipSuccess && !one && i < 2; ++i)
+            e = hipEventCreateWithFlags(&h->pin_ev[i], hipEventDisableTiming);
+        if (e == hipSuccess) {
+            h->pin_nodes = nodes;
+            h->host_part = std::vector<char>();
+            return;
+        }
+        (void)hipGetLastError();
+        pin_free(h);
+    }
+    size_t nodes = std::min(widest, h->plan.stage_bytes / (4 * sizeof(double)));
+    while (pin_part_bytes(nodes) > h->plan.stage_bytes)
+        --nodes;
+    h->pin_nodes = nodes;
 }
 
 // The component planes of `cnt` values at src to their places (from node lo) in
@@ -1077,43 +1091,55 @@ lb_status readout(lb_handle *h, int32_t ch, int which, int comps,
         return fail(LB_EINVAL, "channel index out of range");
     if (!h->has_out)
         return fail(LB_ESTATE, "no completed step to read");
-    // Chunks of nodes through the handle's pinned buffer: the GPU writes one
+    // Chunks of nodes through the handle's buffer; pinned, the GPU writes one
     // part of it while the host copies the other out.
     const int N = h->plan.chans[ch].n;
     const int step = (int)std::min<size_t>(N, h->pin_nodes);
-    const int parts = step < N ? 2 : 1;
+    const bool two = h->pin && step < N;
     double max_speed = 0.0;
     int64_t nonfinite = 0;
-    const auto values = [&](int part) {
-        return reinterpret_cast<double *>(h->pin + (size_t)part * pin_part_bytes(h->pin_nodes));
+    const size_t part_bytes = pin_part_bytes(h->pin_nodes);
+    if (!h->pin)
+        h->host_part.resize(part_bytes);
+    char *const dev = h->pin ? h->pin : reinterpret_cast<char *>(h->d_stage);
+    char *const host = h->pin ? h->pin : h->host_part.data();
+    const auto values = [&](char *at, int part) {
+        return reinterpret_cast<double *>(at + (size_t)part * part_bytes);
     };
-    const auto checks = [&](int part) {
-        return reinterpret_cast<ReadoutCheck *>(values(part) + 4 * h->pin_nodes);
+    const auto checks = [&](char *at, int part) {
+        return reinterpret_cast<ReadoutCheck *>(values(at, part) + 4 * h->pin_nodes);
     };
     const auto launch = [&](int lo, int part) -> lb_status {
         launch_readout(h->pc, which, h->ws, h->d_chans, ch, lo, std::min(N, lo + step),
-                       values(part), checks(part), h->stream);
+                       values(dev, part), checks(dev, part), h->stream);
         lb_status e = check_launch(h, "readout");
-        if (e == LB_OK && parts > 1)
+        if (e == LB_OK && two)
             HIP_TRY(h, hipEventRecord(h->pin_ev[part], h->stream));
+        if (e == LB_OK && !h->pin)
+            HIP_TRY(h, hipMemcpyAsync(host, dev, part_bytes, hipMemcpyDeviceToHost, h->stream));
         return e;
     };
     s = launch(0, 0);
-    for (int lo = 0, part = 0; s == LB_OK && lo < N; lo += step, part ^= 1) {
-        if (lo + step < N)
+    for (int lo = 0, part = 0; s == LB_OK && lo < N; lo += step) {
+        const bool more = lo + step < N;
+        if (two && more)
             s = launch(lo + step, part ^ 1);
         if (s != LB_OK)
             break;
-        if (parts > 1)
+        if (two)
             HIP_TRY(h, hipEventSynchronize(h->pin_ev[part]));
         else
             HIP_TRY(h, hipStreamSynchronize(h->stream));
         const int cnt = std::min(N, lo + step) - lo;
-        copy_out(values(part), cnt, comps, outs, lo);
+        copy_out(values(host, part), cnt, comps, outs, lo);
         for (int b = 0; b < (cnt + kBlock - 1) / kBlock; ++b) {
-            max_speed = std::max(max_speed, checks(part)[b].max_speed);
-            nonfinite += checks(part)[b].nonfinite;
+            max_speed = std::max(max_speed, checks(host, part)[b].max_speed);
+            nonfinite += checks(host, part)[b].nonfinite;
         }
+        if (two)
+            part ^= 1;
+        else if (more)
+            s = launch(lo + step, 0);
     }
     if (s != LB_OK) {
         (void)hipStreamSynchronize(h->stream);
@@ -1477,10 +1503,9 @@ lb_status lb_init(const lb_channel_desc *ch, int32_t n_ch, lb_precision prec, vo
     // the tables and initialise each channel.
     launch_fill_zero(h->ws, h->plan.total, h->stream);
     lb_status s = check_launch(h, "zero fill");
-    if (s == LB_OK)
-        s = pin_alloc(h);
     if (s != LB_OK)
         return bail(s);
+    set_readout_buffer(h, true);
     if (h->plan.far_room) {
         const std::vector<double> &tab = far_tables(h->pc);
         if (hipMemcpyAsync(const_cast<double *>(h->d_far_tab), tab.data(),
@@ -1587,6 +1612,16 @@ lb_status lb_step(lb_handle *h, int64_t n_steps)
     h->t += n_steps;
     if (n_steps > 0)
         h->has_out = true;
+    return LB_OK;
+}
+
+lb_status lb_set_pinned(lb_handle *h, int32_t enable)
+{
+    lb_status s = usable(h);
+    if (s != LB_OK)
+        return s;
+    // no readout is in flight: they end before their call does
+    set_readout_buffer(h, enable != 0);
     return LB_OK;
 }
 

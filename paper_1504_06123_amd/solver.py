@@ -210,6 +210,11 @@ class Solver:
         flags = (_lib.LB_CHECK_FINITE if finite else 0) | (_lib.LB_CHECK_MACH if mach else 0)
         _lib.check(self.lib.lb_set_checks(self.h, flags), "lb_set_checks")
 
+    def set_pinned(self, enable: bool = True) -> None:
+        """Hold a pinned host buffer for readouts, or give it back
+        (lb_set_pinned)."""
+        _lib.check(self.lib.lb_set_pinned(self.h, 1 if enable else 0), "lb_set_pinned")
+
     def stress(self, ch: int = 0):
         sh = self._shape(ch)
         sxy, n1 = np.empty(sh), np.empty(sh)
