@@ -6,14 +6,13 @@ Workload: the large 2D channel, 1024 x 512 nodes, window N_h = 4096, tau =
 1000, g = 5e-6, 1 % seeded velocity perturbation.  Precision of the headline
 number: FP32 populations in split storage (FP32 remainders against the
 equilibrium of FP64 moments), FP32 history ring whose window sums are FP32
-partial sums added into Kahan-compensated FP32 totals, FP64 accumulated
-strain; the mode with FP64 populations is timed beside it.  One step = the whole path for every node:
+partial sums of 16 rows added in FP64, FP64 accumulated strain; the mode with FP64 populations is timed beside it.  One step = the whole path for every node:
 pull-stream + collide with the stress-divergence force, velocity gradient,
 history push and the N_h-entry history integral.  The launch shape (steps
 per history pass, lanes, chunks, persistent pass) is chosen by the
 autotuner before the timed region.  The timed region is sustained: the
 workload's own run length (5000 steps) rounded up to whole blocks, or
---steps if that is longer; the first block alone is reported beside it.
+--steps if that is longer; one span of steps alone is reported beside it.
 
 Beside it ("grid"): the same channel on the quasi-logarithmic history grid
 of Sec. III; ("full_tensor"): the same channel with the full Finger tensor
@@ -50,25 +49,19 @@ LARGE_2D_RUN_STEPS = 5000
 GRAPH_LEN = 64
 
 KERNEL_SOURCE = os.path.join(ROOT, "paper_1504_06123_amd", "csrc", "lbmax_kernels.hip")
-# rocprofv3 counter results for the history pass on this workload (see
-# profiles/history_pass_large_2d_1024x512_nh4096.md), keyed by
-# (precision, steps per pass, nodes per lane).  Valid only for the kernel source they
-# were taken from; otherwise reported as null.
+# rocprofv3 counter results (see profiles/far_spans.md).  Valid only for the
+# kernel source they were taken from; otherwise reported as null.
 MEASURED = {
-    "source_sha256": "4420735c938cc4f3a0b522dceeec0453bbaa654f000d4af98829c3c55b44b196",
-    # HBM bytes per launch: FETCH_SIZE x 2.000 + WRITE_SIZE x 1.000 (copy-calibrated),
-    # from `bench.py --counter-run <leg>` under rocprofv3 --pmc
-    "traffic_bytes": {("f32", 32, 1): 8395456.6 * 1024 * 2 + 266560.0 * 1024,
-                      ("f32", 1, 4): 8411893.1 * 1024 * 2 + 41231.2 * 1024,
-                      ("f32p64", 32, 1): 8394923.6 * 1024 * 2 + 266560.0 * 1024,
-                      ("f32p64", 1, 4): 8411801.9 * 1024 * 2 + 41233.6 * 1024},
-    # SQ_INSTS_VALU x 64 / history entries (both modes run the same pass kernels)
-    "valu_instr_per_entry": {("f32", 32, 1): 90.77, ("f32p64", 32, 1): 90.77,
-                             ("f32", 1, 4): 9.53, ("f32p64", 1, 4): 9.53},
-    # the side legs' dominant kernels, keyed by (leg, steps per pass), same calibration
-    "leg_traffic_bytes": {("grid", 16): 1602534.0 * 1024 * 2 + 211968.0 * 1024,
-                          ("full_tensor", 16): 33557838.6 * 1024 * 2 + 213072.0 * 1024,
-                          ("strain_damping", 32): 8395973.2 * 1024 * 2 + 266240.0 * 1024},
+    "source_sha256": "4d4417ff3a1eb3d0c941865b079fc604673f8232a3dd7264835edafeb2bd875b",
+    # HBM bytes per reading of the window, the far pass and the near passes of its
+    # span (grid: per pass): FETCH_SIZE x 2.000 + WRITE_SIZE x 1.000
+    # (copy-calibrated), from `bench.py --counter-run <leg>` under rocprofv3 --pmc
+    "traffic_bytes": {"f32": 16.7489e9 + 4 * 0.9949e9, "f32p64": 16.7489e9 + 4 * 0.9946e9,
+                      "f32 one step": 17.2684e9, "f32p64 one step": 17.2689e9,
+                      "full_tensor": 66.7237e9 + 8 * 2.7311e9,
+                      "strain_damping": 16.6605e9 + 4 * 0.8962e9, "grid": 3.4990e9},
+    # SQ_INSTS_VALU x 64 / history entries, of the same passes
+    "valu_instr_per_entry": {"f32": 52.32 + 4 * 4.32, "f32p64": 52.32 + 4 * 4.32},
 }
 
 
@@ -99,7 +92,7 @@ def hist_bytes_per_entry(ch) -> int:
     return 4 if unidirectional(ch) else 8
 
 
-# Steps served by one reading of the window inside a call (the library's longest
+# Steps served by one reading of the window (the library's longest
 # span of far sums; narrow fast channels take shorter ones).
 SPAN_STEPS = 128
 
@@ -164,7 +157,7 @@ def bench_large_2d(wl, args, precision: str):
         gbs1 = ch.nodes * ch.n_hist * hist_bytes_per_entry(ch) / one_s / 1e9
         one_step = {"bound": "hbm", "achieved": gbs1, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                     "frac": gbs1 / HBM_PEAK_GBS,
-                    "traffic": measured("traffic_bytes", (precision, 1, vec1)),
+                    "traffic": measured("traffic_bytes", precision + " one step"),
                     "kernel": f"k_hist_pass (one step per pass, {vec1} nodes per lane, "
                               f"{s.tiling(0)[0]} age chunks; with the chunk combine)",
                     "kernel_avg_ms": one_s * 1e3}
@@ -210,9 +203,12 @@ def bench_large_2d(wl, args, precision: str):
         f"history passes {pass_s*1e3:.3f} ms per {SPAN_STEPS} steps ({gbs:.0f} GB/s, {tflops:.1f} TFLOP/s); "
         f"lattice {kt[1][0]/max(kt[1][1],1):.4f} ms; block step "
         f"{(kt[2][0]/kt[2][1]) if kt[2][1] else 0:.4f} ms")
-    # Instruction model of the far pass: per entry the decay, u and strain work,
-    # per term a power, an add and an FMA, and a sixteenth of the FP64 totals.
-    vpe, vpe_src = 16 + 3 * 12 + 3, "model"
+    # Without counters a model of the far pass: per entry the decay, w and
+    # strain work, per term a power, an add and an FMA, and a sixteenth of the
+    # FP64 totals.
+    vpe = measured("valu_instr_per_entry", precision)
+    vpe_src = "rocprofv3 SQ_INSTS_VALU" if vpe else "model"
+    vpe = vpe or 16 + 3 * 12 + 3
     # Cycles each SIMD spends per wave-level VALU instruction, counted at the
     # nominal 2.4 GHz engine clock.
     wave_instr = vpe * entries / 64
@@ -226,7 +222,7 @@ def bench_large_2d(wl, args, precision: str):
     else:
         roof = {"bound": "alu", "achieved": tflops, "peak": FP32_PEAK_TFLOPS,
                 "unit": "TFLOP/s", "frac": tflops / FP32_PEAK_TFLOPS}
-    roof.update({"traffic": None,
+    roof.update({"traffic": measured("traffic_bytes", precision),
                  "kernel": f"k_far_pass, k_near_pass ({precision}, {SPAN_STEPS} steps per "
                            "reading of the window)",
                  "kernel_avg_ms": pass_s * 1e3, "alg_bytes_per_launch": alg_bytes,
@@ -335,7 +331,7 @@ def bench_grid(steps: int = 256, B: int = 6, C: int = 128, block: int = 16):
             "dtype": "f32 history + f64 lattice", "steps_per_pass": block,
             "roofline": {"bound": "hbm", "achieved": gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                          "frac": gbs / HBM_PEAK_GBS,
-                         "traffic": measured("leg_traffic_bytes", ("grid", block)),
+                         "traffic": measured("traffic_bytes", "grid"),
                          "kernel": f"k_grid_pass ({block} steps per pass)",
                          "kernel_avg_ms": pass_s * 1e3, "alg_bytes_per_launch": alg_bytes,
                          "in_block_step_avg_ms": edge_s * 1e3}}
@@ -371,7 +367,7 @@ def bench_finger(steps: int = 128):
             "config": cfg,
             "roofline": {"bound": "hbm", "achieved": gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                          "frac": gbs / HBM_PEAK_GBS,
-                         "traffic": None,
+                         "traffic": measured("traffic_bytes", "full_tensor"),
                          "kernel": f"k_finger_far, k_finger_near ({SPAN_STEPS} steps per "
                                    "reading of the ring)",
                          "kernel_avg_ms": pass_s * 1e3, "alg_bytes_per_launch": alg_bytes}}
@@ -409,7 +405,7 @@ def bench_laws(steps: int = 256):
             rec["roofline"] = {"bound": "hbm", "achieved": alg / pass_s / 1e9,
                                "peak": HBM_PEAK_GBS, "unit": "GB/s",
                                "frac": alg / pass_s / 1e9 / HBM_PEAK_GBS,
-                               "traffic": None,
+                               "traffic": measured("traffic_bytes", "strain_damping"),
                                "kernel": f"k_wm_far, k_wm_near ({SPAN_STEPS} steps per "
                                          "reading of the window)",
                                "kernel_avg_ms": pass_s * 1e3, "alg_bytes_per_launch": alg}
@@ -548,8 +544,9 @@ def counter_run(leg: str, copy_mib: int = 4096):
     """A short plain-launch run for hardware-counter collection (no HIP
     events, no graphs): `copy` copies `copy_mib` MiB device to device (the
     calibration of FETCH_SIZE and WRITE_SIZE); the other legs build the
-    channel as their timed leg does, take 32 warm-up steps in the default
-    launch shape (one-step passes), then 4 blocks in the leg's shape."""
+    channel as their timed leg does, from rest (no tile of the far sums falls
+    back), take 8 one-step passes in the default launch shape, then one span of
+    128 steps in the leg's shape."""
     import numpy as np
     import torch
     import workloads
@@ -562,7 +559,7 @@ def counter_run(leg: str, copy_mib: int = 4096):
         dst.copy_(src)
         torch.cuda.synchronize()
         return {"counter_run": leg, "bytes": n * 4}
-    base = workloads.large_2d().channels[0]
+    base = workloads.large_2d(perturb=False).channels[0]
     prec, block, persistent = "f32p64", 32, True
     if leg in ("f32", "f32p64"):
         ch, prec = base, leg
@@ -579,10 +576,12 @@ def counter_run(leg: str, copy_mib: int = 4096):
         s.set_block(block)
         s.step(2 * 128)
     else:
-        s.step(32)
+        for _ in range(8):
+            s.set_block(1)
+            s.step(1)
         autotune.apply(s, dict(block=block, vec=1, chunk_len=1 << 30,
                                persistent=persistent, graph=0))
-    s.step(4 * block)
+    s.step(SPAN_STEPS)
     torch.cuda.synchronize()
     _, ux, _ = s.fields(0)
     assert np.isfinite(ux).all()
@@ -709,7 +708,7 @@ def main():
         "scaling": "weak",
         "vs_baseline": None,
         "dtype": "f32 (populations: FP32 remainders on FP64 moments; history: FP32 ring, "
-                 "FP32 partial sums into Kahan-compensated FP32 totals; FP64 strain)",
+                 "FP32 partial sums of 16 rows added in FP64; FP64 strain)",
         "data": "synthetic",
         "config": {"workload": "large 2D channel 1024x512, N_h=4096, tau=1000 steps, "
                                "g=5e-6, 1% seeded velocity perturbation",
@@ -721,7 +720,7 @@ def main():
         # pass replaces): HBM-bound
         "history_pass_one_step": main["one_step"],
         "entry_updates_per_s": entries * steps / el,
-        # the first block alone (one history pass and its in-block steps)
+        # one span alone (one reading of the window and its steps)
         "burst": main["burst"],
         "f32p64": side and {"value": side["node_steps_per_s"],
                             "ms_per_step": side["ms_per_step"], "steps": side["steps"],

@@ -70,9 +70,10 @@ typedef enum {
  *          FP32 rounding from step to step (FP32 deviations n_i - a_i drift:
  *          a velocity that grows by a small amount per step loses part of
  *          each increment to FP32 rounding, coherently).  History ring in
- *          FP32; each window sum is formed as FP32 partial sums over groups
- *          of up to 128 rows, each added into a Kahan-compensated FP32 total
- *          (sum and compensation, read out as their FP64 difference).
+ *          FP32; each window sum is formed as FP32 partial sums: of 16 rows,
+ *          added in FP64, in spans of far sums (see lb_set_block), else of up
+ *          to 128 rows, each added into a Kahan-compensated FP32 total (sum
+ *          and compensation, read out as their FP64 difference).
  *  LB_F32_P64: populations as FP64 deviations n_i - a_i, history as in
  *          LB_F32.
  */

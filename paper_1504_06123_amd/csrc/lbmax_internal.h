@@ -140,7 +140,7 @@ void launch_hist_pass(int prec, int vec, int block, char *ws, const ChanDev *cha
                       const HistTile *tiles, int n_tiles, const int64_t *tcount,
                       int trel, int persistent_grid, int *counter, bool far, hipStream_t st);
 int hist_pass_blocks_per_cu(int prec, int vec, int block);
-// Far sums.  A call-level span of `span` steps (32, 64 or 128) is cut into
+// Far sums.  A span of `span` steps (32, 64 or 128) is cut into
 // blocks of 32 and, per channel, into spans of min(ChanDev::far, span) steps;
 // `at` steps into it (step *tcount + trel) the far pass runs for the
 // channels whose span starts there, each tile split over `sub` wavefronts (1, 4

@@ -552,7 +552,7 @@ __device__ __forceinline__ double *far_marker(char *ws, const ChanDev *c, int n0
            (size_t)c->far_mark * c->max_chunks * c->np + n0;
 }
 
-// Steps of channel c's spans inside a call-level span of `span` steps.
+// Steps of channel c's spans inside the handle's spans of `span` steps.
 __device__ __forceinline__ int far_span(const ChanDev *c, int span) { return min(c->far, span); }
 
 __device__ __forceinline__ bool far_holds(char *ws, const ChanDev *c, int n0)
@@ -1139,12 +1139,13 @@ __device__ __forceinline__ void combine_node(char *__restrict__ ws, const ChanDe
 // with an entry beyond |u| = 1 (or a NaN) is marked, and takes the general
 // pass, block by block, for the whole span.
 //
-// What bounds it: the window's bytes for wide channels (1024 x 512 nodes, 4096
-// entries: 3.30 ms, 5.2 TB/s, the rate of a large copy; the general pass 5.27
-// ms, and four times as often), vector issue for narrow ones, whose tiles are
-// split over 4 or 8 wavefronts of a workgroup and put together in LDS (1 x 256
-// nodes, 8192 entries in 8 chunks: 29 us against 211 us).  256 steps of the
-// 1024 x 512 channel, far and near passes: 9 ms against 42 ms.
+// What bounds it: the window's bytes and vector issue alike for wide channels
+// (1024 x 512 nodes, 4096 entries: 3.34 ms while the engine clock is high, 5.0
+// TB/s, near the rate of a large copy, 3.9 ms in a sustained run; the general
+// pass 5.27 ms, and four times as often), vector issue for narrow ones, whose
+// tiles are split over 4 or 8 wavefronts of a workgroup and put together in LDS
+// (1 x 256 nodes, 8192 entries in 8 chunks: 32 us against 211 us).  256 steps
+// of the 1024 x 512 channel, far and near passes: 10 ms against 42 ms.
 // ---------------------------------------------------------------------------
 template <typename R>
 constexpr int kFarP = sizeof(R) == 8 ? far_terms(0) : far_terms(1);
