@@ -290,7 +290,8 @@ lb_status lb_load_state(lb_handle *h, const void *d_src);
  * lb_step (0 = plain launches).  All take effect at the next lb_step; only
  * the chunk split changes results, and only through rounding order.
  * (Handles that run in spans of far sums, see lb_set_block, take one node per
- * lane, and keep a graph for each place of a span where one starts.)
+ * lane, keep a graph for each place of a span where one starts, and replay a
+ * whole span in one where a call holds it.)
  */
 int32_t lb_max_chunks(const lb_handle *h, int32_t ch);
 lb_status lb_set_tiling(lb_handle *h, int32_t ch, int32_t n_chunks,

@@ -209,6 +209,7 @@ def test_a_gradient_does_not_depend_on_the_sampling(Solver):
 @pytest.mark.parametrize("kind,block,graph,calls,launches", [
     ("2d", 32, 64, (64,) * 6, 6),          # a graph at each of a span's halves
     ("2d", 32, 96, (96,) * 8, 8),          # four places, one after the other
+    ("2d", 32, 64, (64, 340), 4),          # to a span's end, two whole spans, 20 by themselves
     ("2d", 32, 256, (300, 300), 2),        # whole spans: 256 of 300, then from 384 on
     ("uni", 8, 8, (8,) * 40, 40),          # shorter than a span's block
     ("uni", 1, 64, (130, 64), 3),          # no spans
