@@ -211,10 +211,13 @@ int far_room_for(const ChanDev &c)
 
 // The same by its parameters too: the rates have to stay within the expansion,
 // their spread over the window taken as the wall rate 4 u / ly of a channel
-// flow whose peak speed u is two fifths of the Mach guard's.  (A longer span
-// only reads the window less often; six FP64 channels of 32 nodes in a
-// transient, 50-step calls: 0.90 ms a call with 64-step spans, 1.06 ms with
-// 128-step ones, which some tiles leave for the general pass.)  Spans of 32
+// flow whose peak speed u is two fifths of the Mach guard's.  A longer span only
+// reads the window less often, and a tile that leaves it takes the general pass,
+// five times a far pass on narrow channels: where spans of 32 steps are to be
+// had, ones of 64 keep a quarter more of the expansion free (six FP64 channels
+// of 32 nodes in a transient, 50-step calls, six runs: 0.56 ms in spans of 32
+// steps, 0.82 in one run; 0.50 in spans of 64, 0.90 to 1.39 in three runs, whose
+// tiles left them; 64 channels of 16 to 1024 nodes 7.1 against 7.2).  Spans of 32
 // steps only save part of a walk and waste all of it where some tiles leave
 // them, which channels whose tiles fill the chip unsplit feel in full (1024 x
 // 128 nodes, thinning startup: 43 us a step where they hold, 70 where one tile
@@ -226,9 +229,11 @@ int far_span_for(const ChanDev &c)
     const double spread = c.law == 1 ? 0.0 : 4.0 * 0.04 / c.ly * c.inv_gc;
     const int least =
         c.law == 0 && !c.finger && c.n > kFarSplitWaves / 4 * kWave ? 64 : kFarNearBlock;
-    for (int S = far_room_for(c); S >= least; S /= 2)
-        if (spread <= kFarZ / (0.5 * (S - 1)))
+    for (int S = far_room_for(c); S >= least; S /= 2) {
+        const double keep = S == 2 * kFarNearBlock && least < S ? 1.25 : 1.0;
+        if (keep * spread <= kFarZ / (0.5 * (S - 1)))
             return S;
+    }
     return 0;
 }
 

@@ -76,6 +76,7 @@ def test_settings_that_take_no_spans(Solver):
                                ([base(), grid], 8, 0), ([base(), grid], 32, 128),
                                ([base(finger=True), base()], 16, 0),
                                ([base(gamma_c=1e-3)], 32, 0),
+                               ([base(ly=32)], 32, 32), ([base(ly=36)], 32, 64),
                                # spans of 32 steps: not beyond 65536 nodes
                                ([base(lx=2048, ly=32, gamma_c=0.05)], 32, 32),
                                ([base(lx=2049, ly=32, gamma_c=0.05)], 32, 0),
