@@ -151,7 +151,11 @@ typedef struct {
 typedef struct lb_handle lb_handle;
 
 /* Bytes of device workspace needed for these channels (0 if the
- * description is invalid; lb_last_error says why).  Pure host call. */
+ * description is invalid; lb_last_error says why).  Pure host call.  Beside
+ * the state it holds the block sums, the partial sums of split windows and,
+ * for windows of at least 128 entries, room for far sums (see lb_set_block):
+ * where a window is not split 26 doubles a node (FP64 history 38; full tensor
+ * 41 and 59; accumulated strain 4), whatever the parameters. */
 size_t lb_workspace_bytes(const lb_channel_desc *ch, int32_t n_ch,
                           lb_precision prec);
 
@@ -236,8 +240,8 @@ lb_status lb_grad(lb_handle *h, int32_t ch, double *kappa);
  *     uint32 precision, int64 t (completed steps), int32 n_ch,
  *     int32 span (65536 x the steps of a span of far sums, see lb_set_block,
  *     + those of the current one already done; 0 outside of one), uint64
- *     total bytes, int32 block length, int32 block position (steps of the
- *     current block already done);
+ *     total bytes, int32 block length (lb_set_block), int32 block position
+ *     (steps already done of the current block of that length);
  *   then per channel, in order, N = lx*ly:
  *     pop  [9][N] RP post-collision populations of step t-1 minus the
  *                    weights a_i (LB_F32: minus the equilibrium n^eq_i of the
