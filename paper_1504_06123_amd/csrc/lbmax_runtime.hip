@@ -969,8 +969,11 @@ void drop_graphs(lb_handle *h)
 // per place and number.
 lb_status step_graph(lb_handle *h, int steps, hipGraphExec_t *out)
 {
-    if (h->graph_dirty)
+    if (h->graph_dirty) {
+        if (!h->graph_execs.empty())  // none may be in flight when it is destroyed
+            HIP_TRY(h, hipStreamSynchronize(h->stream));
         drop_graphs(h);
+    }
     const int S = span_in_effect(h);
     const int key = 4096 * (S > 0 ? h->at.span_pos % S : 0) + steps - 1;
     for (auto &e : h->graph_execs)
